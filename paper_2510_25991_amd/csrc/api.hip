@@ -231,7 +231,11 @@ void run_sweeps(ddst_op *op, const SweepPlan &plan, const SweepBuffers &buf, hip
         g.A = a.D;
         g.B = (k > 1) ? sweep_Y(op, w, k - 1, buf) : nullptr;
         g.C = sweep_Y(op, w, k, buf);
-        g.bscale = Ebwd(op, w, P);
+        // Y_k is kept with its rows scaled by the coupling of the plane after
+        // it, which every product with it takes (the next plane's, or the
+        // interface's after the last)
+        if (k == 1) g.bscale = Ebwd(op, w, P);
+        g.cscale = Ebwd(op, w, P + w.dir);
         yj.push_back(g);
       }
     }
@@ -241,9 +245,9 @@ void run_sweeps(ddst_op *op, const SweepPlan &plan, const SweepBuffers &buf, hip
     ny_at[k - 1] = (int)yj.size();
   }
   tab.upload(s);
-  DeviceMem gjw(gj_workspace_bytes(nsw, ld, sizeof(T)));
+  DeviceMem gjw(gj_workspace_bytes(nsw, ld, sizeof(T), op->sym));
   GjStreams gs;
-  HIPCHK(gs.create());
+  HIPCHK(gs.create(ld, op->M, sizeof(T)));
   // The transfer chain of plane k needs only G_k: it runs on a second
   // stream, overlapping the inversion of plane k+1 with its
   // (matrix-core-bound) GEMM.  Before plane k+2 is assembled into the
@@ -276,7 +280,7 @@ void run_sweeps(ddst_op *op, const SweepPlan &plan, const SweepBuffers &buf, hip
       if (k == 1)
         launch_scale_cols<T>(tab.at<GemmJob>(off_y[0]), ny_at[0], ld, -1.0, s2);
       else
-        launch_gemm<T>(tab.at<GemmJob>(off_y[k - 1]), ny_at[k - 1], ld, op->M, -1.0, 0.0, s2);
+        launch_gemm<T>(tab.at<GemmJob>(off_y[k - 1]), ny_at[k - 1], ld, op->M, -1.0, false, s2);
       HIPCHK(hipEventRecord(ev_y[k], s2));
     };
     for (int k = 1; k <= m - 1; ++k) {
@@ -365,8 +369,14 @@ int build_impl(ddst_op *op, int keep, int blocks, hipStream_t s) {
     const int wk = keep ? -1 : take(hasY);
     plan.sw.push_back({sl, +1, hasY ? ny++ : -1, wk, hasY ? 2 : 1});
   }
-  for (int sl = 1; sl < nsl; ++sl) {  // right-to-left, towards Gamma_sl
-    const bool hasY = blocks && sl <= nsl - 2;
+  // right-to-left, towards Gamma_sl.  For a symmetric operator the chain of
+  // this direction is the transpose of the other one's (with the couplings
+  // at both its ends, diag(E) (A^{-1})_{m-1,1} diag(E) against
+  // diag(E) (A^{-1})_{1,m-1} diag(E), A the slab's matrix), so only the
+  // left-to-right chains are formed: half of the chain products, which were
+  // half of the 3D build (63^3 on 8 slabs: see k_gemm).
+  for (int sl = 1; sl < nsl; ++sl) {
+    const bool hasY = blocks && sl <= nsl - 2 && !op->sym;
     const int wk = take(hasY);
     plan.sw.push_back({sl, -1, hasY ? ny++ : -1, wk, hasY ? 2 : 1});
   }
@@ -390,7 +400,7 @@ int build_impl(ddst_op *op, int keep, int blocks, hipStream_t s) {
   // interface centres and transfer blocks
   std::vector<AsmJob> cj;
   std::vector<void *> smats;
-  std::vector<GemmJob> sj;
+  std::vector<GemmJob> sj, sjt;  // sjt: with the transposed chain
   for (int j = 1; j <= nds; ++j) {
     const int c = j * m;
     const Sweep &L = plan.sw[j - 1];        // slab j-1, left-to-right
@@ -412,29 +422,29 @@ int build_impl(ddst_op *op, int keep, int blocks, hipStream_t s) {
       g.A = a.D;
       g.B = sweep_Y(op, L, m - 1, buf);
       g.C = mat(op->S, 2 * (j - 1) + 0, op->mat_bytes);
-      g.bscale = op->Em + (size_t)c * op->ld;
       sj.push_back(g);
     }
     if (j <= nds - 1) {
       GemmJob g{};
       g.A = a.D;
-      g.B = sweep_Y(op, R, m - 1, buf);
+      g.B = sweep_Y(op, op->sym ? plan.sw[j] : R, m - 1, buf);  // of slab j
       g.C = mat(op->S, 2 * (j - 1) + 1, op->mat_bytes);
-      g.bscale = op->Ep + (size_t)c * op->ld;
-      sj.push_back(g);
+      (op->sym ? sjt : sj).push_back(g);
     }
   }
   JobTable tab;
-  const size_t oc = tab.add(cj), om = tab.add(smats), os = tab.add(sj);
+  const size_t oc = tab.add(cj), om = tab.add(smats), os = tab.add(sj), ot = tab.add(sjt);
   tab.upload(s);
   launch_assemble<T>(tab.at<AsmJob>(oc), nds, op->coef, op->n, op->dim, op->M, op->ld, s);
-  DeviceMem gjw(gj_workspace_bytes(nds, op->ld, sizeof(T)));
+  DeviceMem gjw(gj_workspace_bytes(nds, op->ld, sizeof(T), op->sym));
   GjStreams gs;
-  HIPCHK(gs.create());
+  HIPCHK(gs.create(op->ld, op->M, sizeof(T)));
   HIPCHK(gj_invert<T>(tab.at<void *>(om), nds, op->ld, op->M, gjw.p, op->flag, op->indefinite,
                       op->sym, gs, s));
   if (!sj.empty())
-    launch_gemm<T>(tab.at<GemmJob>(os), (int)sj.size(), op->ld, op->M, -1.0, 0.0, s);
+    launch_gemm<T>(tab.at<GemmJob>(os), (int)sj.size(), op->ld, op->M, -1.0, false, s);
+  if (!sjt.empty())
+    launch_gemm<T>(tab.at<GemmJob>(ot), (int)sjt.size(), op->ld, op->M, -1.0, true, s);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return check_flag(op, s, "ddst_build_transfer");
@@ -1925,9 +1935,9 @@ int ddst_test_gemm(int32_t precision, int32_t ld, int32_t batch, const void *A, 
     const size_t o = t.add(jobs);
     t.upload(stream);
     if (precision == DDST_FP32)
-      launch_gemm<float>(t.at<GemmJob>(o), batch, ld, ld, alpha, beta, stream);
+      launch_gemm_full<float>(t.at<GemmJob>(o), batch, ld, bscale != nullptr, alpha, beta, stream);
     else
-      launch_gemm<double>(t.at<GemmJob>(o), batch, ld, ld, alpha, beta, stream);
+      launch_gemm_full<double>(t.at<GemmJob>(o), batch, ld, bscale != nullptr, alpha, beta, stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(stream));
     return DDST_OK;
@@ -1949,9 +1959,9 @@ static int test_invert(int32_t precision, int32_t ld, int32_t batch, void *A, in
     t.upload(stream);
     DeviceMem fl(sizeof(ElimStatus));
     HIPCHK(hipMemsetAsync(fl.p, 0, sizeof(ElimStatus), stream));
-    DeviceMem w(gj_workspace_bytes(batch, ld, esize(precision)));
+    DeviceMem w(gj_workspace_bytes(batch, ld, esize(precision), sym));
     GjStreams gs;
-    HIPCHK(gs.create());
+    HIPCHK(gs.create(ld, ld, esize(precision)));
     int *flag = static_cast<int *>(fl.p);
     if (precision == DDST_FP32)
       HIPCHK(gj_invert<float>(t.at<void *>(o), batch, ld, ld, w.p, flag, 0, sym, gs, stream));

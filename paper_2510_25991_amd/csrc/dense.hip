@@ -11,12 +11,14 @@
 // * k_scale_cols : C = alpha A diag(s) (first link of a transfer chain).
 //
 // All matrices are ld x ld row-major, ld a multiple of 128, padded with the
-// identity, so no kernel tests edges.  Work-group tiles are 128 x 128 with 4
-// wavefronts of 64 lanes, each owning a 64 x 64 sub-tile (4 x 4 MFMA tiles).
+// identity; products over the padding are left out.  Work-group tiles are
+// 128 x 128 with 4 wavefronts of 64 lanes, each owning a 64 x 64 sub-tile (4 x
+// 4 MFMA tiles); FP32 products of many tiles take those of tiles.h.
 #include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
+#include "tiles.h"
 
 namespace ddst {
 namespace {
@@ -35,22 +37,9 @@ __device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-constexpr int BK = 16;           // k-depth of one LDS stage
+constexpr int BK = 8;            // k-depth of one FP64 LDS stage
 constexpr int LW = kTile + 16;   // LDS row width (padding spreads banks)
 
-template <typename T>
-__device__ __forceinline__ void ld8(const T *p, T *r) {
-  constexpr int V = 16 / sizeof(T);
-#pragma unroll
-  for (int i = 0; i < 8 / V; ++i) {
-    const typename V16<T>::type v = ld16(p + V * i);
-#pragma unroll
-    for (int e = 0; e < V; ++e) r[V * i + e] = v[e];
-  }
-}
-
-// N consecutive elements (N * sizeof(T) a multiple of 16, p 16-byte aligned)
-// with 16-byte loads.
 template <int N, typename T>
 __device__ __forceinline__ void ld16n(const T *p, T *r) {
   constexpr int V = 16 / sizeof(T);
@@ -146,13 +135,15 @@ __device__ __forceinline__ f32x4 mfma_x6(const Split3 &a, const Split3 &b, f32x4
   return mfma_bf16(a.h, b.h, c);
 }
 
-// LDS of one tile product: FP64 operands staged 16 deep ([16][LW] each);
+// LDS of one tile product: FP64 operands staged 8 deep ([8][LW] each) and
+// double-buffered (one barrier a stage; the update of 31 matrices of 1024 rows
+// 180 us, with single stages of 16 and the exchange that FP32 uses 186);
 // FP32 operands as their three BF16 parts, 32 deep, in fragment order
 // ([part][row or column][k], k contiguous, rows padded to 40 entries).
-constexpr int XK = 2 * BK;       // 32: k per stage of the split products
+constexpr int XK = 32;           // k per stage of the split products
 constexpr int XKP = XK + 8;      // padded row of one BF16 part
 template <typename T> struct MmaLds {
-  static constexpr int bytes = 2 * BK * LW * (int)sizeof(T);
+  static constexpr int bytes = 2 * 2 * BK * LW * (int)sizeof(T);
 };
 template <> struct MmaLds<float> {
   static constexpr int bytes = 2 * 3 * kTile * XKP * 2;
@@ -164,11 +155,12 @@ template <> struct MmaLds<float> {
 // operands (a thread holds 16 values of one row of A and of one column of
 // B), splits them once and stores the three parts in fragment order, so the
 // product loop reads whole 8-element fragments (16 bytes) from LDS.
-template <bool NEG_A, bool TA>
+template <bool NEG_A, bool TA, bool PART>
 __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda,
                                             const float *__restrict__ B, int ldb,
                                             const double *__restrict__ bscale, int K,
-                                            unsigned char *smem, Tile<float> &acc) {
+                                            unsigned char *smem, Tile<float> &acc, int ni,
+                                            int nj) {
   typedef __bf16 Part[kTile][XKP];
   Part *Ap = reinterpret_cast<Part *>(smem);         // Ap[part][row][k]
   Part *Bp = Ap + 3;                                 // Bp[part][col][k]
@@ -183,8 +175,7 @@ __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda
 #pragma unroll
       for (int e = 0; e < 16; ++e) ra[e] = gp(A)[(size_t)(k0 + kh + e) * lda + rr];
     } else {
-      ld8(A + (size_t)rr * lda + k0 + kh, ra);
-      ld8(A + (size_t)rr * lda + k0 + kh + 8, ra + 8);
+      ld16n<16>(A + (size_t)rr * lda + k0 + kh, ra);
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e) rb[e] = gp(B)[(size_t)(k0 + kh + e) * ldb + rr];
@@ -225,13 +216,15 @@ __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      if (PART && i >= ni) continue;
       const int row = wm + i * 16 + c;
       Split3 as;
       as.h = *reinterpret_cast<const bf16x8 *>(&Ap[0][row][8 * g]);
       as.m = *reinterpret_cast<const bf16x8 *>(&Ap[1][row][8 * g]);
       as.l = *reinterpret_cast<const bf16x8 *>(&Ap[2][row][8 * g]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc.v[i][j] = mfma_x6(as, bs[j], acc.v[i][j]);
+      for (int j = 0; j < 4; ++j)
+        if (!PART || j < nj) acc.v[i][j] = mfma_x6(as, bs[j], acc.v[i][j]);
     }
   }
 }
@@ -241,66 +234,107 @@ __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda
 // B row-major with leading dim ldb (points at the tile's first column).
 // TA: the operand is the transpose of a row-major matrix G, A[i][k] =
 // G[k][i]; A then points at G's column of the tile's first row.
-// FP32 operands go to mma_tile_x6 (BF16 matrix cores, 32-deep stages of
-// stages), FP64 ones to the FP64 matrix cores (16 deep).
-template <typename T, bool NEG_A = false, bool TA = false>
-__device__ __forceinline__ void mma_tile(const T *__restrict__ A, int lda,
+// TB (FP64): the right operand is the transpose of a row-major matrix H,
+// B[k][j] = H[j][k]; B then points at H's row of the tile's first column.
+// rows, cols: how many of the tile's rows and columns are wanted; 16 x 16
+// tiles past them are skipped and stay as they are (products over the padding
+// of ragged matrices, see k_gemm).  FP32 operands go to mma_tile_x6 (BF16
+// matrix cores, K a multiple of 32), FP64 ones to the FP64 matrix cores (of 8).
+template <typename T, bool NEG_A, bool TA, bool TB, bool PART>
+__device__ __forceinline__ void mma_part(const T *__restrict__ A, int lda,
                                          const T *__restrict__ B, int ldb,
                                          const double *__restrict__ bscale, int K,
-                                         T (*As)[LW], T (*Bs)[LW], Tile<T> &acc) {
-  if constexpr (std::is_same<T, float>::value) {
-    // As is the start of an MmaLds<float>::bytes buffer
-    mma_tile_x6<NEG_A, TA>(A, lda, B, ldb, bscale, K, reinterpret_cast<unsigned char *>(As), acc);
-    return;
-  }
+                                         T (*As)[LW], Tile<T> &acc, int rows,
+                                         int cols) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-  const int ar = tid >> 1, ak = (tid & 1) * 8;    // A tile: 128 rows x 16
-  const int br = tid >> 4, bc = (tid & 15) * 8;   // B tile: 16 rows x 128
-  T ra[8], rb[8];
+  const int ni = __builtin_amdgcn_readfirstlane(min(4, max(0, (rows - wm + 15) / 16)));
+  const int nj = __builtin_amdgcn_readfirstlane(min(4, max(0, (cols - wn + 15) / 16)));
+  if constexpr (std::is_same<T, float>::value) {
+    static_assert(!TB, "FP32: see k_gemm_big");
+    // As is the start of an MmaLds<float>::bytes buffer
+    mma_tile_x6<NEG_A, TA, PART>(A, lda, B, ldb, bscale, K,
+                                 reinterpret_cast<unsigned char *>(As), acc, ni, nj);
+    return;
+  }
+  // An operand stage of BK k.  Rows of k (A, TB): 128 rows, two threads each;
+  // rows of columns (B, TA): BK rows, 256 / BK threads each.
+  constexpr int NS = BK / 2;
+  const int ar = tid >> 1, ak = (tid & 1) * NS;
+  const int br = tid / (256 / BK), bc = tid % (256 / BK) * NS;
+  T ra[NS], rb[NS];
   auto load = [&](int k0) {
     if (TA)
-      ld8(A + (size_t)(k0 + br) * lda + bc, ra);
+      ld16n<NS>(A + (size_t)(k0 + br) * lda + bc, ra);
     else
-      ld8(A + (size_t)ar * lda + k0 + ak, ra);
-    ld8(B + (size_t)(k0 + br) * ldb + bc, rb);
-    if (bscale) {
-      const T s = (T)gp(bscale)[k0 + br];
+      ld16n<NS>(A + (size_t)ar * lda + k0 + ak, ra);
+    if (TB) {
+      ld16n<NS>(B + (size_t)ar * ldb + k0 + ak, rb);
+    } else {
+      ld16n<NS>(B + (size_t)(k0 + br) * ldb + bc, rb);
+      if (bscale) {
+        const T s = (T)gp(bscale)[k0 + br];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) rb[q] *= s;
+        for (int q = 0; q < NS; ++q) rb[q] *= s;
+      }
     }
   };
+  auto store = [&](int buf) {
+    T (*Ad)[LW] = As + buf * 2 * BK, (*Bd)[LW] = Ad + BK;
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+      (TA ? Ad[br][bc + q] : Ad[ak + q][ar]) = NEG_A ? -ra[q] : ra[q];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) (TB ? Bd[ak + q][ar] : Bd[br][bc + q]) = rb[q];
+  };
   load(0);
+  store(0);
+  if (BK < K) load(BK);
+  __syncthreads();
   for (int k0 = 0; k0 < K; k0 += BK) {
-    __syncthreads();
-    if (TA) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) As[br][bc + q] = NEG_A ? -ra[q] : ra[q];
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) As[ak + q][ar] = NEG_A ? -ra[q] : ra[q];
+    const int buf = (k0 / BK) & 1;
+    if (k0 + BK < K) {
+      store(buf ^ 1);
+      if (k0 + 2 * BK < K) load(k0 + 2 * BK);
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) Bs[br][bc + q] = rb[q];
-    __syncthreads();
-    if (k0 + BK < K) load(k0 + BK);
+    const T (*Ac)[LW] = As + buf * 2 * BK, (*Bc)[LW] = Ac + BK;
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
       T a[4], b[4];
       const int kr = kk + (lane >> 4);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kr][wm + i * 16 + (lane & 15)];
+      for (int i = 0; i < 4; ++i) a[i] = Ac[kr][wm + i * 16 + (lane & 15)];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kr][wn + j * 16 + (lane & 15)];
+      for (int j = 0; j < 4; ++j) b[j] = Bc[kr][wn + j * 16 + (lane & 15)];
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc.v[i][j] = mfma16(a[i], b[j], acc.v[i][j]);
+        for (int j = 0; j < 4; ++j)
+          if (!PART || (i < ni && j < nj)) acc.v[i][j] = mfma16(a[i], b[j], acc.v[i][j]);
     }
+    __syncthreads();
   }
 }
+template <typename T, bool NEG_A = false, bool TA = false, bool TB = false>
+__device__ __forceinline__ void mma_tile(const T *__restrict__ A, int lda,
+                                         const T *__restrict__ B, int ldb,
+                                         const double *__restrict__ bscale, int K,
+                                         T (*As)[LW], Tile<T> &acc,
+                                         int rows = kTile, int cols = kTile) {
+  // a loop of its own, for the whole work-group: tests between the products
+  // cost full tiles a tenth of their rate
+  if (rows > kTile - 16 && cols > kTile - 16)
+    mma_part<T, NEG_A, TA, TB, false>(A, lda, B, ldb, bscale, K, As, acc, rows, cols);
+  else
+    mma_part<T, NEG_A, TA, TB, true>(A, lda, B, ldb, bscale, K, As, acc, rows, cols);
+}
+
+// Rows, columns or k of a 128-wide tile from i0 that are not padding, and the
+// depth of a product over k of them.
+__device__ __forceinline__ int part_of_tile(int M, int i0) { return max(0, min(kTile, M - i0)); }
+__device__ __forceinline__ int depth_of(int k) { return max(32, (k + 31) & ~31); }
 
 // Row / column of accumulator element (i, j, r) inside the 128 x 128 tile.
 // Lane l holds column l % 16 of each 16 x 16 MFMA output; the row of
@@ -317,18 +351,18 @@ __device__ __forceinline__ int acc_col(int j) {
   return (wave & 1) * 64 + j * 16 + (lane & 15);
 }
 
-// FP64: at least two wavefronts per SIMD, as for the update
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_gemm(
-    const GemmJob *__restrict__ jobs, int ld, int tiles_per_mat, T alpha, T beta) {
+// C = alpha diag(cscale) A diag(bscale) B + beta C (TB: A B^T), 128 x 128 tiles.
+// Matrix-core bound.  Only the first M rows, columns and k are multiplied:
+// what lies past them is padding, whose products are zero (M = 899 in
+// ld = 1024: 0.71 of the multiply-adds).
+template <typename T, bool TB>
+__global__ __launch_bounds__(256, 2) void k_gemm(const GemmJob *__restrict__ jobs, int ld, int M,
+                                                 T alpha, T beta) {
   __shared__ __align__(16) unsigned char smem[MmaLds<T>::bytes];
   T (*As)[LW] = reinterpret_cast<T (*)[LW]>(smem);
-  T (*Bs)[LW] = As + BK;
-  const int total = gridDim.x;
-  const int lin = xcd_remap(blockIdx.x, total);
-  const int b = lin / tiles_per_mat;
-  const int t = lin % tiles_per_mat;
   const int nt = ld / kTile;
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = lin / (nt * nt), t = lin % (nt * nt);
   const int bm = (t / nt) * kTile, bn = (t % nt) * kTile;
   const GemmJob J = jobs[b];
   const T *A = static_cast<const T *>(J.A);
@@ -336,18 +370,42 @@ __global__ __launch_bounds__(256, 2) void k_gemm(
   auto *C = gp(static_cast<T *>(J.C));
   Tile<T> acc;
   acc.zero();
-  mma_tile<T>(A + (size_t)bm * ld, ld, B + bn, ld, J.bscale, ld, As, Bs, acc);
+  mma_tile<T, false, false, TB>(A + (size_t)bm * ld, ld, TB ? B + (size_t)bn * ld : B + bn, ld,
+                                J.bscale, depth_of(min(ld, M)), As, acc, M - bm, M - bn);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int r = 0; r < 4; ++r) {
+      const int row = bm + acc_row<T>(i, r);
+      const T f = J.cscale ? alpha * (T)gp(J.cscale)[row] : alpha;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const size_t idx = (size_t)(bm + acc_row<T>(i, r)) * ld + bn + acc_col(j);
-        T v = alpha * acc.v[i][j][r];
+      for (int j = 0; j < 4; ++j) {
+        const size_t idx = (size_t)row * ld + bn + acc_col(j);
+        T v = f * acc.v[i][j][r];
         if (beta != T(0)) v += beta * C[idx];
         C[idx] = v;
       }
+    }
+}
+
+// The same for FP32 with 256 x 256 tiles (tiles.h), without bscale and beta.
+template <bool TB>
+__global__ __launch_bounds__(512, 2) void k_gemm_big(const GemmJob *__restrict__ jobs, int ld,
+                                                     int M, float alpha) {
+  using W = WgTile<2>;
+  __shared__ __align__(16) unsigned char smem[W::lds];
+  const int nt = (ld + W::TM - 1) / W::TM;
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = lin / (nt * nt), t = lin % (nt * nt);
+  const int bm = (t / nt) * W::TM, bn = (t % nt) * W::TN;
+  const GemmJob J = jobs[b];
+  const float *B = static_cast<const float *>(J.B);
+  W w;
+  w.product(Opnd{static_cast<const float *>(J.A) + (size_t)bm * ld, ld, ld - bm, true},
+            Opnd{TB ? B + (size_t)bn * ld : B + bn, ld, ld - bn, TB}, min(ld, (M + 15) & ~15),
+            M - bm, M - bn, smem);
+  w.put_to(static_cast<float *>(J.C) + (size_t)bm * ld + bn, ld, alpha,
+           J.cscale ? J.cscale + bm : nullptr, ld - bm, ld - bn);
 }
 
 // Broadcast lane src (wave-uniform) of a double to the whole wavefront.
@@ -363,7 +421,7 @@ __device__ __forceinline__ double bcast_lane(double x, int src) {
 __device__ __forceinline__ int dpp_row_bcast(int x, int k) {
   switch (k) {
 #define DDST_BC(K) \
-  case K: return __builtin_amdgcn_update_dpp(0, x, 0x150 + K, 0xF, 0xF, false);
+  case K: return __builtin_amdgcn_mov_dpp(x, 0x150 + K, 0xF, 0xF, false);
     DDST_BC(0) DDST_BC(1) DDST_BC(2) DDST_BC(3) DDST_BC(4) DDST_BC(5) DDST_BC(6) DDST_BC(7)
     DDST_BC(8) DDST_BC(9) DDST_BC(10) DDST_BC(11) DDST_BC(12) DDST_BC(13) DDST_BC(14)
     DDST_BC(15)
@@ -392,40 +450,41 @@ __device__ __forceinline__ bool leaf_invert16(double (&v)[4]) {
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
     const int kg = k & 3, kc = k >> 2;  // column k: lanes with g == kg, v[kc]
-    const double colk = __shfl(v[kc], kg * 16 + i);  // P[i][k]
-    double prow[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) prow[c] = row_bcast(v[c], k);  // P[k][g + 4c]
     const double piv = bcast_lane(v[kc], kg * 16 + k);
+    const double colk = __shfl(v[kc], kg * 16 + i);  // P[i][k]
     ok = ok && isfinite(piv) && (ANY_SIGN ? piv != 0.0 : piv > 0.0);
-    const double inv = 1.0 / piv;
+    // 1 / piv to about an ulp (the bits of an IEEE division cost the chain
+    // of 128 eliminations a third of its length)
+    double inv = __builtin_amdgcn_rcp(piv);
+    inv = fma(fma(-piv, inv, 1.0), inv, inv);
+    inv = fma(fma(-piv, inv, 1.0), inv, inv);
+    // column k becomes the unit vector: the pivot row then gives 1 / piv and
+    // the other rows -P[i][k] / piv there
+    if (g == kg) v[kc] = i == k ? 1.0 : 0.0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const bool isk = (g == kg) && (c == kc);
-      const double rk = isk ? inv : prow[c] * inv;  // new pivot row
-      // other rows: P[i][j] - P[i][k] rk[j]; column k itself -P[i][k] / piv
-      const double other = fma(-colk, rk, isk ? 0.0 : v[c]);
-      v[c] = (i == k) ? rk : other;
+      const double rk = row_bcast(v[c], k) * inv;  // new pivot row
+      v[c] = i == k ? rk : fma(-colk, rk, v[c]);
     }
   }
   return ok;
 }
 
-// One Gauss-Jordan step, pivot part: one work-group (4 wavefronts) per
+// One Gauss-Jordan step, pivot part: one work-group (5 wavefronts) per
 // matrix inverts the kNB x kNB (128 x 128) pivot block P = D[p, p] in FP64,
 // without pivoting, and writes P^{-1} (row-major, rounded to T) to Pinv[b],
 // the operand of the panel product.  FP64 throughout: the transfer blocks
 // inherit the error of these inverses amplified by the conditioning of the
 // interface Schur block.
 //
-// The block stays in registers for the whole inversion, as 16 x 16 tiles in
-// the FP64 MFMA output layout: wave w owns column tiles 2w and 2w + 1 of all
-// eight row tiles.  It is inverted by blocked Gauss-Jordan with 16-wide
-// leaves.  Sub-step q: the row block q and the column block q go to LDS
-// (double-buffered, one barrier per sub-step); every wave inverts the leaf
-// P_qq itself (the same arithmetic in each wave, so no second barrier), forms
-// R_J = P_qq^{-1} P_qJ for its column tiles and applies the rank-16 update
-// to them on the matrix cores, with the tiles as accumulators:
+// The block stays in the registers of wavefronts 0..3 for the whole
+// inversion, as 16 x 16 tiles in the FP64 MFMA output layout: wave w owns
+// column tiles 2w and 2w + 1 of all eight row tiles.  It is inverted by
+// blocked Gauss-Jordan with 16-wide leaves.  Sub-step q: the row block q and
+// the column block q are in LDS (double-buffered), the inverted leaf
+// P_qq^{-1} too; the four wavefronts form R_J = P_qq^{-1} P_qJ for their
+// column tiles and apply the rank-16 update on the matrix cores, with the
+// tiles as accumulators:
 //   row tile q:        T_qJ = R_J                   (R_q = P_qq^{-1})
 //   column tile q:     T_Iq = -P_Iq P_qq^{-1}       (formed from zero)
 //   others:            T_IJ = T_IJ - P_Iq R_J
@@ -433,28 +492,58 @@ __device__ __forceinline__ bool leaf_invert16(double (&v)[4]) {
 // B-operand layout of the update's k-step r, and the leaf layout is the
 // A-operand layout, so no data moves between the two.  The sub-step loop is
 // unrolled so that every tile index is static, and no vector ALU operation
-// touches a tile.  The register cap keeps the whole work-group within about
-// 190 registers per SIMD lane, so it can be placed on a CU next to the
-// update and GEMM work-groups that run concurrently on other streams (a
-// larger footprint waits for a CU to drain).
+// touches a tile.
+//
+// What bounds it: a serial chain of 128 eliminations, and 64 FP64 MFMAs of 64
+// cycles per sub-step and wavefront (33 k cycles in all).  The next leaf is
+// therefore updated first and inverted by wavefront 4 beside the other
+// tiles' MFMAs, so that a sub-step takes the longer of the two instead of
+// their sum (63 matrices: 38 us; with each of four wavefronts inverting the
+// leaf itself, between two rounds of MFMAs, 51, of which the leaves were 32;
+// with three wavefronts of tiles and the leaf on a SIMD of its own, 38).
+// With Rprev and Cprev (the previous step's panels), that step's update of
+// the block is applied first.
 constexpr int kLeaf = 16;
 constexpr int kCqS = 20;        // LDS row stride of the column block (doubles)
 constexpr int kRqS = kNB + 16;  // LDS row stride of the row block (doubles)
 static_assert(kNB == 128, "the register layout below assumes 128-wide pivots");
 
 template <typename T, bool ANY_SIGN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj_pivot(void *const *__restrict__ mats,
-                                                  T *__restrict__ Pinv,
-                                                  const T *__restrict__ Rprev,
-                                                  const T *__restrict__ Cprev, int ld, int p,
-                                                  int M, int *__restrict__ flag) {
+__global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ mats,
+                                                     T *__restrict__ Pinv,
+                                                     const T *__restrict__ Rprev,
+                                                     const T *__restrict__ Cprev, int ld, int o,
+                                                     int lw, int p, int M,
+                                                     int *__restrict__ flag) {
   constexpr int kCqN = 2 * kNB * kCqS, kRqN = 2 * kLeaf * kRqS;
-  __shared__ double lds[kCqN + kRqN];
+  constexpr int KS = sizeof(T) == 4 ? 32 : 16;  // operand slices of the previous update
+  __shared__ __align__(16) double lds[kCqN + kRqN];
   double (*Cq)[kNB][kCqS] = reinterpret_cast<double (*)[kNB][kCqS]>(lds);
   double (*Rq)[kLeaf][kRqS] = reinterpret_cast<double (*)[kLeaf][kRqS]>(lds + kCqN);
+  __shared__ double Lt[kLeaf][kLeaf + 1];  // the next leaf
+  __shared__ double Lv[4][64];             // the inverted leaf, in leaf_invert16's layout
   const int b = blockIdx.x, l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int lr = l >> 4, lc = l & 15;
-  const auto *D = gp(static_cast<const T *>(mats[b]) + (size_t)p * kNB * ld + p * kNB);
+  constexpr int NQ = kNB / kLeaf;
+  if (w == 4) {
+    if (Rprev)
+      for (int i = 0; i < 2 * (kNB / KS) + 1; ++i) __syncthreads();  // those of the product
+    bool ok = true;
+    for (int q = 0; q < NQ; ++q) {
+      __syncthreads();  // the leaf q is in Lt
+      double v[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = Lt[lc][lr + 4 * c];
+      ok = leaf_invert16<ANY_SIGN>(v) && ok;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) Lv[c][l] = v[c];
+      __syncthreads();  // row block q, column block q and the inverted leaf are in LDS
+    }
+    if (!ok && l == 0) atomicOr(flag, 1);
+    return;
+  }
+  const int g0 = o + p * kNB;  // the block's row and column in the matrix
+  const auto *D = gp(static_cast<const T *>(mats[b]) + (size_t)g0 * ld + g0);
   f64x4 t[8][2];  // t[I][jj][r] = P[16 I + 4 r + lr][16 (2 w + jj) + lc]
   auto load_block = [&]() {
 #pragma unroll
@@ -474,12 +563,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj
     // the FP64 layout of t.  FP64: accumulated into the block itself (a
     // second set of FP64 accumulators would not fit next to it).  Operands
     // are staged through LDS in KS-deep slices.
-    constexpr int KS = sizeof(T) == 4 ? 32 : 16;
     static_assert(2 * KS * LW * sizeof(T) <= sizeof(lds), "operand slices fit the LDS");
     T (*As)[LW] = reinterpret_cast<T (*)[LW]>(lds);
     T (*Bs)[LW] = reinterpret_cast<T (*)[LW]>(reinterpret_cast<T *>(lds) + KS * LW);
-    const T *A = Cprev + (size_t)b * ld * kNB + (size_t)p * kNB * kNB;  // rows p, kNB wide
-    const T *B = Rprev + (size_t)b * kNB * ld + p * kNB;               // kNB rows, cols p
+    const T *A = Cprev + ((size_t)b * lw + p * kNB) * kNB;  // rows p, kNB wide
+    const T *B = Rprev + (size_t)b * kNB * lw + p * kNB;  // kNB rows, cols p
     const int tid = threadIdx.x;
     constexpr int AE = kNB * KS / 256;  // A elements per thread (128 rows x KS)
     constexpr int BE = KS * kNB / 256;  // B elements per thread (KS rows x 128)
@@ -490,7 +578,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj
       for (int k0 = 0; k0 < kNB; k0 += KS) {
         T ra[AE], rb[BE];
         ld16n<AE>(A + (size_t)ar * kNB + k0 + ak, ra);
-        ld16n<BE>(B + (size_t)(k0 + bk) * ld + bc, rb);
+        ld16n<BE>(B + (size_t)(k0 + bk) * lw + bc, rb);
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < AE; ++e) As[ak + e][ar] = sign * ra[e];
@@ -537,26 +625,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj
   } else {
     load_block();
   }
-  bool ok = true;
+  auto put_leaf = [&](const f64x4 &x) {
 #pragma unroll
-  for (int q = 0; q < kNB / kLeaf; ++q) {
-    const int buf = q & 1, qj = q & 1;
-    const bool owner = w == (q >> 1);  // this wave holds column tile q (as jj = qj)
+    for (int r = 0; r < 4; ++r) Lt[4 * r + lr][lc] = x[r];
+  };
+  // row block q and column block q (its owner holds it as jj = q & 1) to LDS
+  auto put_blocks = [&](int q) {
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) Rq[buf][4 * r + lr][16 * (2 * w + jj) + lc] = t[q][jj][r];
-    if (owner) {
+      for (int r = 0; r < 4; ++r) Rq[q & 1][4 * r + lr][16 * (2 * w + jj) + lc] = t[q][jj][r];
+    if (w == (q >> 1)) {
 #pragma unroll
       for (int I = 0; I < 8; ++I)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Cq[buf][16 * I + 4 * r + lr][lc] = t[I][qj][r];
+        for (int r = 0; r < 4; ++r) Cq[q & 1][16 * I + 4 * r + lr][lc] = t[I][q & 1][r];
     }
-    __syncthreads();
+  };
+  if (w == 0) put_leaf(t[0][0]);
+  __syncthreads();
+  put_blocks(0);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int buf = q & 1, qj = q & 1;
+    const bool owner = w == (q >> 1);  // this wave holds column tile q (as jj = qj)
     double v[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = Rq[buf][lc][16 * q + lr + 4 * c];
-    ok = leaf_invert16<ANY_SIGN>(v) && ok;
+    for (int c = 0; c < 4; ++c) v[c] = Lv[c][l];
     f64x4 R[2];
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj) {
@@ -570,9 +666,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj
         R[jj] = mfma16(v[s], bs, R[jj]);
       }
     }
-#pragma unroll
-    for (int I = 0; I < 8; ++I) {
-      if (I == q) continue;
+    auto update = [&](int I) {
       double a[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) a[s] = -Cq[buf][16 * I + lc][4 * s + lr];
@@ -587,34 +681,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(96))) void k_gj
 #pragma unroll
         for (int s = 0; s < 4; ++s) t[I][qj] = mfma16(a[s], R[qj][s], t[I][qj]);
       }
+    };
+    if (q + 1 < NQ) {  // the next leaf first
+      update(q + 1);
+      if (w == ((q + 1) >> 1)) put_leaf(t[q + 1][(q + 1) & 1]);
+      __syncthreads();
     }
+#pragma unroll
+    for (int I = 0; I < 8; ++I)
+      if (I != q && I != q + 1) update(I);
     t[q][0] = R[0];
     t[q][1] = R[1];
+    if (q + 1 < NQ) {
+      put_blocks(q + 1);
+      __syncthreads();
+    }
   }
-  if (!ok && threadIdx.x == 0) atomicOr(flag, 1);
   T *out = Pinv + (size_t)b * kNB * kNB;
   // largest |entry| of the inverse outside the identity padding (rows and
   // columns >= M), for the pivot growth
   double amax = 0.0;
-  const int lim = M - p * kNB;  // local rows / columns below M
+  const int lim = M - g0;  // local rows / columns below M
 #pragma unroll
   for (int I = 0; I < 8; ++I)
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * I + 4 * r + lr, col = 16 * (2 * w + jj) + lc;
-        out[row * kNB + col] = (T)t[I][jj][r];
-        if (row < lim && col < lim) amax = fmax(amax, fabs(t[I][jj][r]));
-      }
+      for (int r = 0; r < 4; ++r)
+        put<T>(out + (16 * I + 4 * r) * kNB + 16 * jj,
+               (unsigned)sizeof(T) * (lr * kNB + 32 * w + lc), (T)t[I][jj][r]);
+#pragma unroll
+  for (int I = 0; I < 8; ++I)
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+      if (16 * (2 * w + jj) + lc < lim)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (lim >= kNB || 16 * I + 4 * r + lr < lim) amax = fmax(amax, fabs(t[I][jj][r]));
   for (int off = 32; off > 0; off >>= 1) amax = fmax(amax, __shfl_xor(amax, off));
   if (l == 0)
     atomicMax(reinterpret_cast<unsigned long long *>(flag) + 1,
               (unsigned long long)__double_as_longlong(amax));
 }
 
-// One Gauss-Jordan step, panel part.  Work-group (jt, b), 4 wavefronts,
-// for the 128 columns j0 = 128 jt:
+// One Gauss-Jordan step, panel part (o: row and column where the block being
+// inverted begins, lw its width, M its rows that are not padding; here and
+// below products over the padding are left out).  Work-group (jt, b), 4
+// wavefronts, for the 128 columns j0 = 128 jt:
 //  * R[:, j0..j0+127] = P^{-1} D[p, j0..j0+127], a 128 x 128 x 128 product
 //    on the matrix cores through the LDS-staged tile routine (R = P^{-1}
 //    itself on the pivot block);
@@ -625,14 +738,14 @@ template <typename T>
 __global__ __launch_bounds__(256, 2) void k_gj_panel(void *const *__restrict__ mats,
                                                   const T *__restrict__ Pinv,
                                                   T *__restrict__ Rbuf, T *__restrict__ Cbuf,
-                                                  int ld, int p, int copy_c) {
+                                                  int ld, int o, int lw, int M, int p,
+                                                  int copy_c) {
   __shared__ __align__(16) unsigned char smem[MmaLds<T>::bytes];
   T (*As)[LW] = reinterpret_cast<T (*)[LW]>(smem);
-  T (*Bs)[LW] = As + BK;
   const int b = blockIdx.y, jt = blockIdx.x, tid = threadIdx.x;
-  const T *D = static_cast<const T *>(mats[b]);
-  T *R = Rbuf + (size_t)b * kNB * ld;
-  T *Cb = Cbuf + (size_t)b * ld * kNB;
+  const T *D = static_cast<const T *>(mats[b]) + (size_t)o * ld + o;
+  T *R = Rbuf + (size_t)b * kNB * lw;
+  T *Cb = Cbuf + (size_t)b * lw * kNB;
   const T *Pi = Pinv + (size_t)b * kNB * kNB;
   const int p0 = p * kNB, j0 = jt * kTile;
   constexpr int V = 16 / sizeof(T);  // elements per 16-byte access
@@ -643,20 +756,22 @@ __global__ __launch_bounds__(256, 2) void k_gj_panel(void *const *__restrict__ m
   if (jt == p) {
     for (int e = tid * V; e < kNB * kTile; e += 256 * V) {
       const int r = e / kTile, c = e % kTile;
-      st16(R + (size_t)r * ld + j0 + c, ld16(Pi + r * kNB + c));
+      st16(R + (size_t)r * lw + j0 + c, ld16(Pi + r * kNB + c));
     }
     return;
   }
   Tile<T> acc;
   acc.zero();
-  mma_tile<T>(Pi, kNB, D + (size_t)p0 * ld + j0, ld, nullptr, kNB, As, Bs, acc);
+  const int rows = part_of_tile(M, p0);
+  mma_tile<T>(Pi, kNB, D + (size_t)p0 * ld + j0, ld, nullptr, depth_of(rows), As, acc, rows,
+              part_of_tile(M, j0));
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        R[(size_t)acc_row<T>(i, r) * ld + j0 + acc_col(j)] = acc.v[i][j][r];
+        R[(size_t)acc_row<T>(i, r) * lw + j0 + acc_col(j)] = acc.v[i][j][r];
 }
 
 // (i, j) of the t-th tile of a lower triangle of tiles, in row order
@@ -702,31 +817,32 @@ template <typename T>
 __global__ __launch_bounds__(256, 2) void k_gj_panel_sym(void *const *__restrict__ mats,
                                                       const T *__restrict__ Pinv,
                                                       T *__restrict__ Rbuf, T *__restrict__ Cbuf,
-                                                      int ld, int p) {
+                                                      int ld, int o, int lw, int M, int p) {
   __shared__ __align__(16) unsigned char smem[MmaLds<T>::bytes];
   static_assert(32 * (kTile + 1) * sizeof(T) <= MmaLds<T>::bytes, "transpose chunk fits");
   T (*As)[LW] = reinterpret_cast<T (*)[LW]>(smem);
-  T (*Bs)[LW] = As + BK;
   const int b = blockIdx.y, it = blockIdx.x, tid = threadIdx.x;
-  const T *D = static_cast<const T *>(mats[b]);
-  T *R = Rbuf + (size_t)b * kNB * ld;
-  T *Cb = Cbuf + (size_t)b * ld * kNB;
+  const T *D = static_cast<const T *>(mats[b]) + (size_t)o * ld + o;
+  T *R = Rbuf + (size_t)b * kNB * lw;
+  T *Cb = Cbuf + (size_t)b * lw * kNB;
   const T *Pi = Pinv + (size_t)b * kNB * kNB;
   const int p0 = p * kNB, i0 = it * kTile;
   constexpr int V = 16 / sizeof(T);
   if (it == p) {
     for (int e = tid * V; e < kNB * kTile; e += 256 * V) {
       const int r = e / kTile, c = e % kTile;
-      st16(R + (size_t)r * ld + p0 + c, ld16(Pi + r * kNB + c));
+      st16(R + (size_t)r * lw + p0 + c, ld16(Pi + r * kNB + c));
     }
     return;
   }
   Tile<T> acc;
   acc.zero();
+  const int cols = part_of_tile(M, p0), rows = part_of_tile(M, i0), K = depth_of(cols);
   if (it > p)
-    mma_tile<T>(D + (size_t)i0 * ld + p0, ld, Pi, kNB, nullptr, kNB, As, Bs, acc);
+    mma_tile<T>(D + (size_t)i0 * ld + p0, ld, Pi, kNB, nullptr, K, As, acc, rows, cols);
   else
-    mma_tile<T, true, true>(D + (size_t)p0 * ld + i0, ld, Pi, kNB, nullptr, kNB, As, Bs, acc);
+    mma_tile<T, true, true>(D + (size_t)p0 * ld + i0, ld, Pi, kNB, nullptr, K, As, acc, rows,
+                            cols);
   // Rbuf[c][i0 + r] = W_i[r][c]
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -734,7 +850,7 @@ __global__ __launch_bounds__(256, 2) void k_gj_panel_sym(void *const *__restrict
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        R[(size_t)acc_col(j) * ld + i0 + acc_row<T>(i, r)] = acc.v[i][j][r];
+        R[(size_t)acc_col(j) * lw + i0 + acc_row<T>(i, r)] = acc.v[i][j][r];
   if (it > p) {
     for (int e = tid * V; e < kTile * kNB; e += 256 * V) {
       const int r = e / kNB, c = e % kNB;
@@ -775,11 +891,13 @@ __global__ __launch_bounds__(256) void k_sym_diag(void *const *__restrict__ mats
 
 // Upper triangle of every matrix from its lower triangle (the inverse left
 // by the symmetric elimination is symmetric): work-group (t, b) copies the
-// transpose of the t-th tile strictly below the diagonal to its mirror.
+// transpose of the t-th tile strictly below the diagonal to its mirror, in
+// the block that begins at row and column o.
 template <typename T>
-__global__ __launch_bounds__(256) void k_mirror_lower(void *const *__restrict__ mats, int ld) {
+__global__ __launch_bounds__(256) void k_mirror_lower(void *const *__restrict__ mats, int ld,
+                                                      int o) {
   __shared__ T X[32][kTile + 1];
-  T *D = static_cast<T *>(mats[blockIdx.y]);
+  T *D = static_cast<T *>(mats[blockIdx.y]) + (size_t)o * ld + o;
   int ti, tj;
   tri_index(blockIdx.x, ti, tj);
   ti += 1;  // strictly lower: the t-th tile of the triangle of nt - 1 rows, shifted
@@ -791,14 +909,13 @@ __global__ __launch_bounds__(256) void k_mirror_lower(void *const *__restrict__ 
 //   pivot rows               D[p, :] = R             (P^{-1} on the block p)
 //   other rows, column p     D[i, p] = -D[i, p] P^{-1}
 //   other rows, other cols   D[i, j] -= D[i, p] P^{-1} D[p, j]
-// The 128 x 128 tile of D is read and written with 16-byte accesses, each
-// wavefront covering whole rows (VEC elements per lane).  It is read after
-// the product, half a tile at a time, and the MFMA accumulators are
+// The 128 x 128 tile of D is read after the product.  FP32: it is read and
+// written with 16-byte accesses, each wavefront covering whole rows (VEC
+// elements per lane), half a tile at a time, and the MFMA accumulators are
 // exchanged into its row layout through LDS (64 rows, the two wavefronts
 // holding them write, all four read; the operand stages live in the same
-// buffer).  Keeping D out of registers during the product and the LDS
-// buffer at 34 KB lets four work-groups share a CU (FP32), whose products
-// hide each other's D latency.  With Cnext, tiles of column block p + 1 are
+// buffer).  FP64: in the accumulators' own layout, whose 16 lanes cover a
+// 128-byte line of a row.  With Cnext, tiles of column block p + 1 are
 // also written to the next step's column panel.  The product is formed from
 // zero and subtracted once, keeping the rounding at the scale of the update
 // rather than of D; the pivot column is written as -acc rather than
@@ -816,26 +933,24 @@ template <> struct UpdGeom<double> {
 };
 
 // Tile subsets of one update (q = p + 1, the next pivot block): all tiles
-// (last step); the row and column blocks of q without the tile (q, q)
-// (whose update the next pivot kernel does itself); everything outside
-// them.
-enum { kSelAll = 0, kSelCross = 1, kSelRest = 2 };
+// (last step); the row and column blocks of q, with the block (q, q) or without
+// it; everything outside them.
+enum { kSelAll = 0, kSelCross, kSelArms, kSelRest };
 __host__ __device__ inline int sel_tiles(int sel, int nt) {
-  return sel == kSelAll ? nt * nt : sel == kSelCross ? 2 * nt - 2 : (nt - 1) * (nt - 1);
+  return sel == kSelAll    ? nt * nt
+         : sel == kSelRest ? (nt - 1) * (nt - 1)
+                           : 2 * nt - 1 - (sel == kSelArms);
 }
 __device__ __forceinline__ void sel_tile(int sel, int nt, int q, int t, int &tr, int &tc) {
   if (sel == kSelAll) {
     tr = t / nt;
     tc = t % nt;
-  } else if (sel == kSelCross) {  // row block q, then column block q, both without (q, q)
-    if (t < nt - 1) {
-      tr = q;
+  } else if (sel != kSelRest) {  // row block q, column block q, (q, q)
+    tr = tc = q;
+    if (t < nt - 1)
       tc = t + (t >= q);
-    } else {
-      const int u = t - (nt - 1);
-      tr = u + (u >= q);
-      tc = q;
-    }
+    else if (t < 2 * nt - 2)
+      tr = t - (nt - 1) + (t - (nt - 1) >= q);
   } else {  // everything outside row and column block q
     tr = t / (nt - 1);
     tc = t % (nt - 1);
@@ -845,23 +960,23 @@ __device__ __forceinline__ void sel_tile(int sel, int nt, int q, int t, int &tr,
 }
 
 // Tile subsets of the symmetric elimination, which updates only the lower
-// triangle of tiles (tr >= tc): all of them (last step); row block q left of
+// triangle of tiles (tr >= tc): all of them (last step); row block q up to
 // (q, q) and column block q below it; everything outside row and column
 // block q.
 __host__ __device__ inline int sel_tiles_sym(int sel, int nt) {
-  return sel == kSelAll ? nt * (nt + 1) / 2 : sel == kSelCross ? nt - 1 : (nt - 1) * nt / 2;
+  return sel == kSelAll    ? nt * (nt + 1) / 2
+         : sel == kSelRest ? (nt - 1) * nt / 2
+                           : nt - (sel == kSelArms);
 }
 __device__ __forceinline__ void sel_tile_sym(int sel, int nt, int q, int t, int &tr, int &tc) {
   if (sel == kSelAll) {
     tri_index(t, tr, tc);
-  } else if (sel == kSelCross) {  // (q, 0..q-1), then (q+1..nt-1, q)
-    if (t < q) {
-      tr = q;
+  } else if (sel != kSelRest) {  // (q, 0..q-1), (q+1..nt-1, q), (q, q)
+    tr = tc = q;
+    if (t < q)
       tc = t;
-    } else {
+    else if (t < nt - 1)
       tr = t + 1;
-      tc = q;
-    }
   } else {  // the lower triangle of the nt - 1 blocks other than q
     tri_index(t, tr, tc);
     tr += tr >= q;
@@ -869,9 +984,6 @@ __device__ __forceinline__ void sel_tile_sym(int sel, int nt, int q, int t, int 
   }
 }
 
-// FP64: at least two wavefronts per SIMD (its accumulators would otherwise
-// take the register file of two)
-//
 // SYM: the symmetric elimination (a symmetric matrix, Gauss-Jordan without
 // pivoting in block order).  After the steps 0..p-1 the matrix is
 //   [ A_SS^{-1}              A_SS^{-1} A_SN          ]
@@ -885,24 +997,21 @@ __device__ __forceinline__ void sel_tile_sym(int sel, int nt, int q, int t, int 
 // Rbuf holds W^T (kNB x ld, W_p^T taken as P^{-1}), so every product is the
 // one of the general update, only its sign and the pivot-row copy differ.
 template <typename T, bool SYM>
-__global__ __launch_bounds__(256, 2) void k_gj_update(
-    void *const *__restrict__ mats,
+__global__ __launch_bounds__(256, 2) void k_gj_update(void *const *__restrict__ mats,
                                                    const T *__restrict__ Rbuf,
                                                    const T *__restrict__ Cbuf,
-                                                   T *__restrict__ Cnext, int ld, int p,
-                                                   int sel) {
+                                                   T *__restrict__ Cnext, int ld, int o, int nt,
+                                                   int M, int p, int sel) {
   using G = UpdGeom<T>;
   constexpr int XW = kTile + 4;  // exchange row width
   constexpr int HR = kTile / 2;  // rows per exchange half
   // the staging buffers of the product live inside the exchange buffer
-  constexpr int LDSN = HR * XW * (int)sizeof(T) > MmaLds<T>::bytes ? HR * XW * (int)sizeof(T)
-                                                                    : MmaLds<T>::bytes;
-  __shared__ __align__(16) unsigned char smem[LDSN];
+  static_assert(HR * XW * (int)sizeof(float) <= MmaLds<float>::bytes);
+  __shared__ __align__(16) unsigned char smem[MmaLds<T>::bytes];
   T *lds = reinterpret_cast<T *>(smem);
   T (*As)[LW] = reinterpret_cast<T (*)[LW]>(lds);
-  T (*Bs)[LW] = As + BK;
   T (*Xs)[XW] = reinterpret_cast<T (*)[XW]>(lds);
-  const int nt = ld / kTile;
+  const int lw = nt * kTile;  // width of the block being inverted
   const int tiles_per_mat = SYM ? sel_tiles_sym(sel, nt) : sel_tiles(sel, nt);
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
   const int b = lin / tiles_per_mat;
@@ -912,22 +1021,22 @@ __global__ __launch_bounds__(256, 2) void k_gj_update(
   else
     sel_tile(sel, nt, p + 1, lin % tiles_per_mat, tr, tc);
   const int bm = tr * kTile, bn = tc * kTile;
-  T *D = static_cast<T *>(mats[b]);
-  const T *R = Rbuf + (size_t)b * kNB * ld;
-  const T *Cb = Cbuf + (size_t)b * ld * kNB;
+  T *D = static_cast<T *>(mats[b]) + (size_t)o * ld + o;
+  const T *R = Rbuf + (size_t)b * kNB * lw;
+  const T *Cb = Cbuf + (size_t)b * lw * kNB;
   const int p0 = p * kNB;
   const int tid = threadIdx.x;
   constexpr int LPR = kTile / G::VEC;           // lanes per row
   const int trow = tid / LPR, tcol = (tid % LPR) * G::VEC;
   using VT = typename V16<T>::type;
   // tiles of column block p + 1 also go to the next step's column panel
-  T *Cn = (!SYM && Cnext && bn == p0 + kNB) ? Cnext + (size_t)b * ld * kNB : nullptr;
+  T *Cn = (!SYM && Cnext && bn == p0 + kNB) ? Cnext + (size_t)b * lw * kNB : nullptr;
   if (bm == p0) {  // pivot rows: D[p, :] = R (SYM: -W^T left of the pivot), no product
     const T sg = (SYM && bn < p0) ? T(-1) : T(1);
 #pragma unroll
     for (int q = 0; q < G::NQ; ++q) {
       const int row = bm + q * G::RPI + trow;
-      VT v = ld16(R + (size_t)(row - p0) * ld + bn + tcol);
+      VT v = ld16(R + (size_t)(row - p0) * lw + bn + tcol);
 #pragma unroll
       for (int e = 0; e < G::VEC; ++e) v[e] *= sg;
       st16(D + (size_t)row * ld + bn + tcol, v);
@@ -937,9 +1046,40 @@ __global__ __launch_bounds__(256, 2) void k_gj_update(
   }
   Tile<T> acc;
   acc.zero();
-  mma_tile<T>(Cb + (size_t)bm * kNB, kNB, R + bn, ld, nullptr, kNB, As, Bs, acc);
-  const bool pivcols = (bn + tcol >= p0) && (bn + tcol < p0 + kNB);
+  mma_tile<T>(Cb + (size_t)bm * kNB, kNB, R + bn, lw, nullptr, depth_of(part_of_tile(M, p0)), As,
+              acc, part_of_tile(M, bm), part_of_tile(M, bn));
   const bool plus = SYM && bn < p0;  // s_j = -1: the product is added
+  if constexpr (sizeof(T) == 8) {
+    const double f = plus ? 1.0 : -1.0;
+    const unsigned off = 8u * (unsigned)(acc_row<T>(0, 0) * ld + acc_col(0));
+    const unsigned cof = 8u * (unsigned)(acc_row<T>(0, 0) * kNB + acc_col(0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      double dv[4][4];
+      if (bn == p0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dv[r][j] = 0.0;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            dv[r][j] = at<double>(D + (size_t)(bm + 16 * i + 4 * r) * ld + bn + 16 * j, off);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double v = dv[r][j] + f * acc.v[i][j][r];
+          put<double>(D + (size_t)(bm + 16 * i + 4 * r) * ld + bn + 16 * j, off, v);
+          if (Cn) put<double>(Cn + (size_t)(bm + 16 * i + 4 * r) * kNB + 16 * j, cof, v);
+        }
+    }
+    return;
+  }
+  const bool pivcols = (bn + tcol >= p0) && (bn + tcol < p0 + kNB);
   const int wave = tid >> 6;
   constexpr int NH = G::NQ / 2;  // row passes per half
 #pragma unroll
@@ -970,6 +1110,179 @@ __global__ __launch_bounds__(256, 2) void k_gj_update(
       if (Cn) st16(Cn + (size_t)(bm + h * HR + lrow) * kNB + tcol, v);
     }
   }
+}
+
+// ---- outer elimination: blocks of kOuter = 512 ------------------------------
+// Matrices of more than kOuter rows are eliminated in outer blocks P: D[P, P]
+// is inverted by the 128-wide steps above, and the rest of the matrix takes
+// one step of rank w <= 512 per outer block:
+//   left     D[P, j] = P^{-1} D[P, j]                       (over its operand)
+//   update   D[i, j] -= D[i, P] D[P, j]
+//   right    D[i, P] = -D[i, P] P^{-1}                      (over its operand)
+// Why: an update of rank 128 moves D once for 128 multiply-adds an entry,
+// which is 81 us of HBM time a step for 63 matrices of 1023 rows and left the
+// matrix cores 21% busy; rank 512 moves it a quarter as often, and the serial
+// chain of pivots runs on 512 x 512 blocks alone, beside which the
+// remaining products of the previous outer block run on another stream.
+// Work-groups of left and right own all the rows, or columns, that they read
+// of their operand, so both write over it, with no panel copies.
+constexpr int kOuter = 512;
+using OuterLeft = WgTile<4>;   // 512 x 128
+using OuterRight = WgTile<1>;  // 128 x 512
+using OuterUpd = WgTile<2>;    // 256 x 256
+
+// An outer step: n rows eliminated in all (a multiple of 128), M of them not
+// padding, P = [p0, p1), the next block Q = [p1, q1).
+struct OuterStep {
+  int ld, n, M, p0, p1, q1;
+  __host__ __device__ int w() const { return p1 - p0; }
+  __host__ __device__ int k() const { return ((M < p1 ? M : p1) - p0 + 15) & ~15; }
+};
+// First row or column of tile t (width tw) outside P; p0 is a multiple of tw.
+__host__ __device__ inline int outside_tiles(const OuterStep &s, int tw) {
+  return s.p0 / tw + (s.n - s.p1 + tw - 1) / tw;
+}
+__device__ __forceinline__ int outside_tile(const OuterStep &s, int tw, int t) {
+  const int nl = s.p0 / tw;
+  return t < nl ? t * tw : s.p1 + (t - nl) * tw;
+}
+
+__global__ __launch_bounds__(512, 2) void k_gj_left(void *const *__restrict__ mats, OuterStep s) {
+  using W = OuterLeft;
+  __shared__ __align__(16) unsigned char smem[W::lds];
+  const int tpm = outside_tiles(s, W::TN);
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  float *D = static_cast<float *>(mats[lin / tpm]);
+  const int j0 = outside_tile(s, W::TN, lin % tpm);
+  float *X = D + (size_t)s.p0 * s.ld + j0;
+  const int rows = min(s.w(), s.M - s.p0), cols = s.M - j0;
+  W w;
+  w.product(Opnd{D + (size_t)s.p0 * s.ld + s.p0, s.ld, s.w(), true},
+            Opnd{X, s.ld, s.n - j0, false}, s.k(), rows, cols, smem);
+  w.put_to(X, s.ld, 1.f, nullptr, rows, cols);
+}
+
+__global__ __launch_bounds__(512, 2) void k_gj_right(void *const *__restrict__ mats, OuterStep s) {
+  using W = OuterRight;
+  __shared__ __align__(16) unsigned char smem[W::lds];
+  const int tpm = outside_tiles(s, W::TM);
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  float *D = static_cast<float *>(mats[lin / tpm]);
+  const int i0 = outside_tile(s, W::TM, lin % tpm);
+  float *X = D + (size_t)i0 * s.ld + s.p0;
+  const int rows = s.M - i0, cols = min(s.w(), s.M - s.p0);
+  W w;
+  w.product(Opnd{X, s.ld, s.n - i0, true},
+            Opnd{D + (size_t)s.p0 * s.ld + s.p0, s.ld, s.w(), false}, s.k(), rows, cols, smem);
+  w.put_to(X, s.ld, -1.f, nullptr, rows, cols);
+}
+
+// Symmetric elimination (lower tiles only, see k_gj_update): the products with
+// P^{-1} are formed once, R_j = P^{-1} C_j^T with C_j the lower-triangle
+// column block (D[P, j] left of P, D[j, P]^T below it), into a buffer, since
+// the update still reads the old blocks.
+__global__ __launch_bounds__(512, 2) void k_gj_left_sym(void *const *__restrict__ mats,
+                                                        float *__restrict__ Rbuf, OuterStep s) {
+  using W = OuterLeft;
+  __shared__ __align__(16) unsigned char smem[W::lds];
+  const int tpm = outside_tiles(s, W::TN);
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = lin / tpm;
+  const float *D = static_cast<const float *>(mats[b]);
+  const int j0 = outside_tile(s, W::TN, lin % tpm);
+  const int rows = min(s.w(), s.M - s.p0), cols = s.M - j0;
+  const Opnd A{D + (size_t)s.p0 * s.ld + s.p0, s.ld, s.w(), true};
+  W w;
+  if (j0 < s.p0)
+    w.product(A, Opnd{D + (size_t)s.p0 * s.ld + j0, s.ld, s.n - j0, false}, s.k(), rows, cols,
+              smem);
+  else
+    w.product(A, Opnd{D + (size_t)j0 * s.ld + s.p0, s.ld, s.n - j0, true}, s.k(), rows, cols,
+              smem);
+  // whole tiles (the padding's zeros are read by the update)
+  w.put_to(Rbuf + (size_t)b * kOuter * s.ld + j0, s.ld, 1.f, nullptr, s.w(), s.n - j0);
+}
+// ... and go to their places after the update: D[P, j] = R_j left of P,
+// D[i, P] = -R_i^T below it.  Work-group (t, b): a 128 x 128 tile.
+__global__ __launch_bounds__(256) void k_gj_out_sym(void *const *__restrict__ mats,
+                                                    const float *__restrict__ Rbuf, OuterStep s) {
+  __shared__ float X[32][kTile + 1];
+  const int pr = s.w() / kTile, nl = s.p0 / kTile;
+  const int r0 = (blockIdx.x % pr) * kTile, t = blockIdx.x / pr;
+  float *D = static_cast<float *>(mats[blockIdx.y]);
+  const float *R = Rbuf + (size_t)blockIdx.y * kOuter * s.ld + (size_t)r0 * s.ld;
+  if (t < nl) {
+    constexpr int V = 4;
+    for (int e = threadIdx.x * V; e < kTile * kTile; e += 256 * V) {
+      const int r = e / kTile, c = t * kTile + e % kTile;
+      st16(D + (size_t)(s.p0 + r0 + r) * s.ld + c, ld16(R + (size_t)r * s.ld + c));
+    }
+    return;
+  }
+  const int i0 = s.p1 + (t - nl) * kTile;
+  tile_transpose<float>(R + i0, s.ld, D + (size_t)i0 * s.ld + s.p0 + r0, s.ld, -1.f, X);
+}
+
+// Tiles of the outer update: those of the next block's diagonal (kOutNext),
+// all others (kOutRest), or all (kOutAll, last block), outside row and
+// column block P; in the symmetric elimination only tiles with an entry on
+// or below the diagonal.  Counts the tiles up to the wanted one, column by
+// column; returns their number (`want` < 0: none wanted).
+enum { kOutAll = 0, kOutNext = 1, kOutRest = 2 };
+__host__ __device__ inline int outer_tiles(const OuterStep &s, int sel, bool sym, int want,
+                                           int &i0, int &j0) {
+  constexpr int W = OuterUpd::TM;
+  static_assert(OuterUpd::TN == W && kOuter % W == 0, "square tiles that fit the blocks");
+  const int nt = (s.n + W - 1) / W;
+  const int p0 = s.p0 / W, p1 = (s.p1 + W - 1) / W, q1 = (s.q1 + W - 1) / W;
+  int count = 0;
+  for (int c = sel == kOutNext ? p1 : 0; c < (sel == kOutNext ? q1 : nt); ++c) {
+    if (c >= p0 && c < p1) continue;
+    // rows [a, e) without [h0, h1)
+    int a = sym ? c : 0, e = nt, h0 = p0, h1 = p1;
+    if (sel == kOutNext) {
+      a = a > p1 ? a : p1;
+      e = q1;
+    } else if (sel == kOutRest && c >= p1 && c < q1) {
+      h1 = q1;  // P and Q are neighbours
+    }
+    // clip the hole to [a, e)
+    h0 = h0 < a ? a : h0 > e ? e : h0;
+    h1 = h1 < h0 ? h0 : h1 > e ? e : h1;
+    const int m = (e - a) - (h1 - h0);
+    if (want >= count && want < count + m) {
+      int r = a + (want - count);
+      if (r >= h0) r += h1 - h0;
+      i0 = r * W;
+      j0 = c * W;
+    }
+    count += m;
+  }
+  return count;
+}
+
+template <bool SYM>
+__global__ __launch_bounds__(512, 2) void k_gj_update_outer(void *const *__restrict__ mats,
+                                                            const float *__restrict__ Rbuf,
+                                                            OuterStep s, int sel, int tpm) {
+  using W = OuterUpd;
+  __shared__ __align__(16) unsigned char smem[W::lds];
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = lin / tpm;
+  float *D = static_cast<float *>(mats[b]);
+  int i0 = 0, j0 = 0;
+  outer_tiles(s, sel, SYM, lin % tpm, i0, j0);
+  const Opnd B{SYM ? Rbuf + (size_t)b * kOuter * s.ld + j0 : D + (size_t)s.p0 * s.ld + j0, s.ld,
+               s.n - j0, false};
+  const int rows = s.M - i0, cols = s.M - j0;
+  W w;
+  if (SYM && i0 < s.p0)  // left of P: C_i = -D[P, i]^T
+    w.product(Opnd{D + (size_t)s.p0 * s.ld + i0, s.ld, s.n - i0, false}, B, s.k(), rows, cols,
+              smem);
+  else
+    w.product(Opnd{D + (size_t)i0 * s.ld + s.p0, s.ld, s.n - i0, true}, B, s.k(), rows, cols,
+              smem);
+  w.add_to(D + (size_t)i0 * s.ld + j0, s.ld, SYM && i0 < s.p0 ? 1.f : -1.f, rows, cols);
 }
 
 // D = A_plane - diag(r1) G1 diag(c1) - diag(r2) G2 diag(c2).  Streams G
@@ -1044,18 +1357,17 @@ __global__ __launch_bounds__(256) void k_assemble(const AsmJob *__restrict__ job
   }
 }
 
-// C = alpha * A * diag(s), one block per row.
 // Products of the sampling chains: C (ld x ldc) = alpha op(A) diag(bscale) B
-// + beta C with A ld x ld (op(A) = A, or A^T when TRANS), B and C ld x ldc
-// (ldc a multiple of 128), all row-major; 128 x 128 output tiles as k_gemm.
+// with A ld x ld (op(A) = A, or A^T when TRANS), B and C ld x ldc (ldc a
+// multiple of 128), all row-major; 128 x 128 output tiles and padding left out
+// as in k_gemm.
 template <typename T, bool TRANS>
-__global__ __launch_bounds__(256, 2) void k_gemm_rect(
-    const GemmJob *__restrict__ jobs, int ld, int ldc, int tiles_per_job, T alpha, T beta) {
+__global__ __launch_bounds__(256, 2) void k_gemm_rect(const GemmJob *__restrict__ jobs, int ld,
+                                                      int ldc, int M, int tiles_per_job,
+                                                      T alpha) {
   __shared__ __align__(16) unsigned char smem[MmaLds<T>::bytes];
   T (*As)[LW] = reinterpret_cast<T (*)[LW]>(smem);
-  T (*Bs)[LW] = As + BK;
-  const int total = gridDim.x;
-  const int lin = xcd_remap(blockIdx.x, total);
+  const int lin = xcd_remap(blockIdx.x, gridDim.x);
   const int b = lin / tiles_per_job;
   const int t = lin % tiles_per_job;
   const int ntc = ldc / kTile;
@@ -1066,21 +1378,15 @@ __global__ __launch_bounds__(256, 2) void k_gemm_rect(
   auto *C = gp(static_cast<T *>(J.C));
   Tile<T> acc;
   acc.zero();
-  if (TRANS)
-    mma_tile<T, false, true>(A + bm, ld, B + bn, ldc, J.bscale, ld, As, Bs, acc);
-  else
-    mma_tile<T>(A + (size_t)bm * ld, ld, B + bn, ldc, J.bscale, ld, As, Bs, acc);
+  mma_tile<T, false, TRANS>(TRANS ? A + bm : A + (size_t)bm * ld, ld, B + bn, ldc, J.bscale,
+                            depth_of(min(ld, M)), As, acc, M - bm);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const size_t idx = (size_t)(bm + acc_row<T>(i, r)) * ldc + bn + acc_col(j);
-        T v = alpha * acc.v[i][j][r];
-        if (beta != T(0)) v += beta * C[idx];
-        C[idx] = v;
-      }
+      for (int r = 0; r < 4; ++r)
+        C[(size_t)(bm + acc_row<T>(i, r)) * ldc + bn + acc_col(j)] = alpha * acc.v[i][j][r];
 }
 
 template <typename T>
@@ -1090,6 +1396,7 @@ __global__ __launch_bounds__(256) void k_scale_cols(const GemmJob *__restrict__ 
   const int r = blockIdx.x;
   const auto *A = gp(static_cast<const T *>(J.A) + (size_t)r * ld);
   auto *C = gp(static_cast<T *>(J.C) + (size_t)r * ld);
+  if (J.cscale) alpha *= (T)gp(J.cscale)[r];
   for (int c = threadIdx.x; c < ld; c += blockDim.x)
     C[c] = alpha * A[c] * (T)gp(J.bscale)[c];
 }
@@ -1113,60 +1420,121 @@ void launch_scale_cols(const GemmJob *jobs, int njobs, int ld, double alpha, hip
   hipLaunchKernelGGL(k_scale_cols<T>, dim3(ld, njobs), dim3(256), 0, s, jobs, ld, (T)alpha);
 }
 
+// 256 x 256 tiles from which k_gemm_big is the faster one: the build of 1023^2
+// on 64 slabs (62 chains of 16 tiles) took 65.5 ms with it against 69.0, that
+// on 32 (30 chains) 57.8 ms with either; fewer tiles leave CUs idle.
+constexpr int kGemmMany = 900;
 template <typename T>
-void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, double beta,
+void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, bool trans_b,
                  hipStream_t s) {
   if (njobs <= 0) return;
-  const int tpm = (ld / kTile) * (ld / kTile);
+  const int nt = ld / kTile, nbig = (ld + WgTile<2>::TM - 1) / WgTile<2>::TM;
   const ProfSpan ps = prof_open(KK_GEMM);
-  hipExtLaunchKernelGGL(k_gemm<T>, dim3(tpm * njobs), dim3(256), 0, s, ps.a, ps.b, 0, jobs, ld,
-                        tpm, (T)alpha, (T)beta);
+  if constexpr (std::is_same<T, float>::value) {
+    if (trans_b || njobs * nbig * nbig >= kGemmMany)
+      hipExtLaunchKernelGGL(trans_b ? k_gemm_big<true> : k_gemm_big<false>,
+                            dim3(nbig * nbig * njobs), dim3(512), 0, s, ps.a, ps.b, 0, jobs, ld, M,
+                            (float)alpha);
+    else
+      hipExtLaunchKernelGGL((k_gemm<float, false>), dim3(nt * nt * njobs), dim3(256), 0, s, ps.a,
+                            ps.b, 0, jobs, ld, M, (float)alpha, 0.f);
+  } else {
+    hipExtLaunchKernelGGL((trans_b ? k_gemm<T, true> : k_gemm<T, false>), dim3(nt * nt * njobs),
+                          dim3(256), 0, s, ps.a, ps.b, 0, jobs, ld, M, (T)alpha, T(0));
+  }
   prof_close(ps, KK_GEMM, 2.0 * njobs * (double)M * M * M);
 }
 
 template <typename T>
+void launch_gemm_full(const GemmJob *jobs, int njobs, int ld, bool bscale, double alpha,
+                      double beta, hipStream_t s) {
+  if (njobs <= 0) return;
+  if (!bscale && beta == 0.0) return launch_gemm<T>(jobs, njobs, ld, ld, alpha, false, s);
+  const int nt = ld / kTile;
+  const ProfSpan ps = prof_open(KK_GEMM);
+  hipExtLaunchKernelGGL((k_gemm<T, false>), dim3(nt * nt * njobs), dim3(256), 0, s, ps.a, ps.b, 0,
+                        jobs, ld, ld, (T)alpha, (T)beta);
+  prof_close(ps, KK_GEMM, 2.0 * njobs * (double)ld * ld * ld);
+}
+
+template <typename T>
 void launch_gemm_rect(const GemmJob *jobs, int njobs, int ld, int ldc, int M, int ncols,
-                      int trans, double alpha, double beta, hipStream_t s) {
+                      int trans, double alpha, hipStream_t s) {
   if (njobs <= 0) return;
   const int tpj = (ld / kTile) * (ldc / kTile);
   const ProfSpan ps = prof_open(KK_GEMM);
   hipExtLaunchKernelGGL(trans ? k_gemm_rect<T, true> : k_gemm_rect<T, false>, dim3(tpj * njobs),
-                        dim3(256), 0, s, ps.a, ps.b, 0, jobs, ld, ldc, tpj, (T)alpha, (T)beta);
+                        dim3(256), 0, s, ps.a, ps.b, 0, jobs, ld, ldc, M, tpj, (T)alpha);
   prof_close(ps, KK_GEMM, 2.0 * njobs * (double)M * M * ncols);
 }
 
-hipError_t GjStreams::create() {
-  hipError_t e = hipStreamCreateWithFlags(&h, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&x, hipStreamNonBlocking);
-  for (hipEvent_t *ev : {&panel, &rest[0], &rest[1], &cross[0], &cross[1]})
-    if (e == hipSuccess)
-      e = hipEventCreateWithFlags(ev, hipEventDisableTiming | hipEventDisableSystemFence);
-  return e;
-}
-
 GjStreams::~GjStreams() {
-  for (hipStream_t st : {h, x})
+  for (hipStream_t st : {h, x, o})
     if (st) (void)hipStreamSynchronize(st);
-  for (hipEvent_t ev : {panel, rest[0], rest[1], cross[0], cross[1]})
+  for (hipEvent_t ev : {panel, arms, upd, left, next, rest})
     if (ev) (void)hipEventDestroy(ev);
-  for (hipStream_t st : {h, x})
+  for (hipStream_t st : {h, x, o})
     if (st) (void)hipStreamDestroy(st);
 }
 
-// Schedule of one inversion (q = p + 1; buffers of step p: R, Cbuf index
-// p & 1; Ux(p) = the tiles of row and column block q except (q, q), Ur(p) =
-// all tiles outside them):
-//   s   : pivot(0) panel(0) | pivot(1) . panel(1) | pivot(2) . panel(2) ...
-//   gs.x:                     Ux(0)                 Ux(1)
-//   gs.h:                     Ur(0)                 Ur(1) ...
+// Steps from which the look-ahead schedule pays (below, its events and streams
+// cost more than the overlap gives: 361 rows, 3.2 ms against 2.25 in all).
+constexpr int kLookAhead = 4;
+// Matrices of more rows than this are eliminated in outer blocks (FP32 only: an
+// FP64 update of rank 128 takes as long on the matrix cores as in memory).
+// 1024 rows: the chains' GEMMs fill the chip beside the 128-wide steps, and
+// outer blocks put a second inversion in series: 1023^2 on 8 slabs 145 ms
+// against 104, on 64 57 against 65; above, 63^3 on 8 slabs 112 against 124 ms.
+constexpr int kSingle = 1024;
+static int block_width(int ld, size_t esz) { return esz == 4 && ld > kSingle ? kOuter : ld; }
+
+// A stream costs more to make (and end) than the elimination of a small block
+// takes: only those that the schedule uses.
+hipError_t GjStreams::create(int ld, int M, size_t esz) {
+  const int n = (M + kTile - 1) / kTile * kTile;
+  hipError_t e = hipSuccess;
+  auto stream = [&](hipStream_t &st) {
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+  };
+  auto events = [&](std::initializer_list<hipEvent_t *> evs) {
+    for (hipEvent_t *ev : evs)
+      if (e == hipSuccess)
+        e = hipEventCreateWithFlags(ev, hipEventDisableTiming | hipEventDisableSystemFence);
+  };
+  if (n / kTile >= kLookAhead) {
+    stream(h);
+    stream(x);
+    events({&panel, &arms, &upd});
+  }
+  if (n > block_width(ld, esz)) {
+    stream(o);
+    events({&left, &next, &rest});
+  }
+  return e;
+}
+
+size_t gj_workspace_bytes(int nmat, int ld, size_t esz, int sym) {
+  const size_t lw = block_width(ld, esz);
+  return (size_t)nmat * esz *
+         (4 * (size_t)kNB * lw + (size_t)kNB * kNB +
+          (sym && lw != (size_t)ld ? (size_t)kOuter * ld : 0));
+}
+
+// Inversion of the nt x nt tiles from row and column o, in steps of 128 (buffers
+// of step p: R, Cbuf index p & 1; q = p + 1; Ux(p) = the tiles of row and
+// column block q except (q, q), Ur(p) = all tiles outside them):
+//   s    : pivot(0) panel(0) | pivot(1) . panel(1) | pivot(2) . panel(2) ...
+//   gs.x :                     Ux(0)                 Ux(1)
+//   gs.h :                     Ur(0)                 Ur(1) ...
 // pivot(q) first applies step p's update to the block (q, q) itself, so the
 // next pivot is inverted while the other tiles are updated; Ux(p), which
 // the panel of step q needs, runs beside the larger Ur(p) rather than before
-// it.  Ux(p) also writes column block q to the column panel of step q.
+// it (behind it on one stream: 188 ms against 180, 1023^2 FP64 on 16 slabs).
+// Ux(p) also writes column block q to the column panel of step q.
 // Dependencies: Ux(p) and Ur(p) wait for panel(p); Ux(p) and pivot(q) wait
 // for Ur(p - 1) (which last wrote their tiles and read the buffers that
-// Ux(p) and panel(q) overwrite); Ur(p) waits for Ux(p - 1) (same reason);
-// panel(q) waits for Ux(p).  The last step updates all tiles on s.
+// Ux(p) and panel(q) overwrite); panel(q) waits for Ux(p), and with it
+// Ur(q).  The last step updates all tiles on s.  Few steps run in order on s.
 //
 // sym: the matrices are symmetric; the updates touch only the lower
 // triangle of tiles (about half the work, see k_gj_update), the panel
@@ -1174,99 +1542,185 @@ GjStreams::~GjStreams() {
 // triangle of the (symmetric) inverse into the upper one.  The pivot
 // kernel is the same: W_q^T is the block q of its R operand.
 template <typename T>
-hipError_t gj_invert(void *const *mats, int nmat, int ld, int M, void *work, int *flag,
-                     int any_sign, int sym, GjStreams &gs, hipStream_t s) {
-  if (nmat <= 0) return hipSuccess;
-  static_assert(kNB == kTile, "one pivot block per tile row");
-  const int nt = ld / kTile;
-  const size_t pan = (size_t)nmat * kNB * ld;
-  T *w = static_cast<T *>(work);
-  T *Rb[2] = {w, w + 2 * pan}, *Cb[2] = {w + pan, w + 3 * pan};
-  T *PinvT = w + 4 * pan;  // nmat kNB x kNB inverses, rounded to T
-  // blocks that hold only identity padding need no elimination step
-  const int nreal = (M + kNB - 1) / kNB;
-  // algorithmic flops of one step: rank-kNB update of the M - kNB other rows
-  const double step_flops = 2.0 * nmat * (double)kNB * M * std::max(M - kNB, 0);
+static hipError_t invert_block(void *const *mats, int nmat, int ld, int o, int nt, int M, T *work,
+                               int *flag, int any_sign, int sym, GjStreams &gs, hipStream_t s) {
+  const int lw = nt * kTile;
+  const size_t pan = (size_t)nmat * kNB * lw;
+  T *Rb[2] = {work, work + 2 * pan}, *Cb[2] = {work + pan, work + 3 * pan};
+  T *PinvT = work + 4 * pan;  // nmat kNB x kNB inverses, rounded to T
+  const double m = std::min(lw, M - o);  // rows that are not padding
+  const double step_flops = 2.0 * nmat * kNB * m * std::max(m - kNB, 0.0);
   const double mfma_tiles = (double)nt * (nt - 1);  // tiles off the pivot rows
-  // Each launch signals its completion through the profiler's stop event
-  // when its class is timed, else through `done` (attached either way).
-  auto pivot = [&](int p) {
-    const ProfSpan ps = prof_open(KK_GJ_PANEL);
-    const T *Rp = p >= 1 ? Rb[(p - 1) & 1] : nullptr;
-    const T *Cp = p >= 1 ? Cb[(p - 1) & 1] : nullptr;
-    hipExtLaunchKernelGGL(any_sign ? k_gj_pivot<T, true> : k_gj_pivot<T, false>, dim3(nmat),
-                          dim3(256), 0, s, ps.a, ps.b, 0, mats, PinvT, Rp, Cp, ld, p, M, flag);
-    prof_close(ps, KK_GJ_PANEL, (p >= 1 ? 4.0 : 2.0) * nmat * (double)kNB * kNB * kNB);
-  };
-  auto panel = [&](int p, hipEvent_t done) {
-    const ProfSpan ps = prof_open(KK_GJ_PANEL);
-    if (sym)
-      hipExtLaunchKernelGGL(k_gj_panel_sym<T>, dim3(nt, nmat), dim3(256), 0, s, ps.a,
-                            ps.b ? ps.b : done, 0, mats, PinvT, Rb[p & 1], Cb[p & 1], ld, p);
-    else
-      hipExtLaunchKernelGGL(k_gj_panel<T>, dim3(nt, nmat), dim3(256), 0, s, ps.a,
-                            ps.b ? ps.b : done, 0, mats, PinvT, Rb[p & 1], Cb[p & 1], ld, p,
-                            p == 0 ? 1 : 0);
-    prof_close(ps, KK_GJ_PANEL, 2.0 * nmat * (double)kNB * kNB * std::max(M - kNB, 0));
-    return ps.b ? ps.b : done;
-  };
-  auto update = [&](int p, int sel, hipStream_t st, hipEvent_t done) {
+  auto update = [&](int p, int sel, hipStream_t st) {
     const int ntiles = sym ? sel_tiles_sym(sel, nt) : sel_tiles(sel, nt);
-    // tiles that take a product (the pivot-row tiles are copies; the
-    // symmetric sets hold p + 1 of them outside the cross set)
-    const double tiles = sym ? (sel == kSelCross ? nt - 1.0 : ntiles - (p + 1.0))
-                         : sel == kSelAll   ? mfma_tiles
-                         : sel == kSelCross ? 2.0 * nt - 3
-                                            : (nt - 1.0) * (nt - 2);
-    T *Cn = (!sym && sel == kSelCross) ? Cb[(p + 1) & 1] : nullptr;
+    // tiles that take a product (the pivot-row tiles are copies)
+    const bool cross = sel != kSelAll && sel != kSelRest;
+    const double tiles = sym ? (cross ? ntiles : ntiles - (p + 1.0))
+                         : sel == kSelAll ? mfma_tiles
+                         : cross          ? ntiles - 1.0
+                                          : (nt - 1.0) * (nt - 2);
+    T *Cn = (!sym && cross) ? Cb[(p + 1) & 1] : nullptr;
     const ProfSpan ps = prof_open(KK_GJ_UPDATE);
     hipExtLaunchKernelGGL(sym ? k_gj_update<T, true> : k_gj_update<T, false>,
-                          dim3(ntiles * nmat), dim3(256), 0, st, ps.a, ps.b ? ps.b : done, 0,
-                          mats, Rb[p & 1], Cb[p & 1], Cn, ld, p, sel);
+                          dim3(ntiles * nmat), dim3(256), 0, st, ps.a, ps.b, 0, mats,
+                          (const T *)Rb[p & 1], (const T *)Cb[p & 1], Cn, ld, o, nt, M - o, p, sel);
     prof_close(ps, KK_GJ_UPDATE, mfma_tiles > 0 ? step_flops * tiles / mfma_tiles : 0.0);
-    return ps.b ? ps.b : done;
   };
   hipError_t e = hipSuccess;
 #define GJCHK(call)                           \
   do {                                        \
     if ((e = (call)) != hipSuccess) return e; \
   } while (0)
-  if (sym && nreal > 0)
-    hipLaunchKernelGGL(k_sym_diag<T>, dim3(nreal, nmat), dim3(256), 0, s, mats, ld);
-  pivot(0);
-  hipEvent_t ev_panel = panel(0, gs.panel);
-  hipEvent_t ev_rest[2] = {nullptr, nullptr}, ev_cross[2] = {nullptr, nullptr};
-  for (int p = 0; p < nreal; ++p) {
-    if (p + 1 < nreal) {
-      GJCHK(hipStreamWaitEvent(gs.x, ev_panel, 0));
-      if (p >= 1) GJCHK(hipStreamWaitEvent(gs.x, ev_rest[(p - 1) & 1], 0));
-      ev_cross[p & 1] = update(p, kSelCross, gs.x, gs.cross[p & 1]);
-      GJCHK(hipStreamWaitEvent(gs.h, ev_panel, 0));
-      if (p >= 1) GJCHK(hipStreamWaitEvent(gs.h, ev_cross[(p - 1) & 1], 0));
-      ev_rest[p & 1] = update(p, kSelRest, gs.h, gs.rest[p & 1]);
-      if (p >= 1) GJCHK(hipStreamWaitEvent(s, ev_rest[(p - 1) & 1], 0));
-      pivot(p + 1);
-      GJCHK(hipStreamWaitEvent(s, ev_cross[p & 1], 0));
-      ev_panel = panel(p + 1, gs.panel);
+  const bool look = nt >= kLookAhead;
+  for (int p = 0; p < nt; ++p) {
+    const bool fused = p > 0 && look;  // the pivot kernel applies step p - 1 to its block
+    if (p > 0 && !look) {
+      update(p - 1, kSelCross, s);
+      update(p - 1, kSelRest, s);
+    } else if (p > 0) {
+      if (p > 1) GJCHK(hipStreamWaitEvent(s, gs.upd, 0));
+      GJCHK(hipEventRecord(gs.panel, s));
+      GJCHK(hipStreamWaitEvent(gs.h, gs.panel, 0));
+      GJCHK(hipStreamWaitEvent(gs.x, gs.panel, 0));
+      if (p > 1) GJCHK(hipStreamWaitEvent(gs.x, gs.upd, 0));
+      update(p - 1, kSelArms, gs.x);
+      GJCHK(hipEventRecord(gs.arms, gs.x));
+      update(p - 1, kSelRest, gs.h);
+      GJCHK(hipEventRecord(gs.upd, gs.h));
+    }
+    ProfSpan ps = prof_open(KK_GJ_PANEL);
+    hipExtLaunchKernelGGL(any_sign ? k_gj_pivot<T, true> : k_gj_pivot<T, false>, dim3(nmat),
+                          dim3(320), 0, s, ps.a, ps.b, 0, mats, PinvT,
+                          fused ? (const T *)Rb[(p - 1) & 1] : nullptr,
+                          (const T *)Cb[(p - 1) & 1], ld, o, lw, p, M, flag);
+    prof_close(ps, KK_GJ_PANEL, (fused ? 4.0 : 2.0) * nmat * (double)kNB * kNB * kNB);
+    if (fused) GJCHK(hipStreamWaitEvent(s, gs.arms, 0));
+    ps = prof_open(KK_GJ_PANEL);
+    if (sym)
+      hipExtLaunchKernelGGL(k_gj_panel_sym<T>, dim3(nt, nmat), dim3(256), 0, s, ps.a, ps.b, 0,
+                            mats, (const T *)PinvT, Rb[p & 1], Cb[p & 1], ld, o, lw, M - o, p);
+    else
+      hipExtLaunchKernelGGL(k_gj_panel<T>, dim3(nt, nmat), dim3(256), 0, s, ps.a, ps.b, 0, mats,
+                            (const T *)PinvT, Rb[p & 1], Cb[p & 1], ld, o, lw, M - o, p,
+                            p == 0 ? 1 : 0);
+    prof_close(ps, KK_GJ_PANEL, 2.0 * nmat * (double)kNB * kNB * std::max(m - kNB, 0.0));
+  }
+  if (nt > 1 && look) GJCHK(hipStreamWaitEvent(s, gs.upd, 0));
+  update(nt - 1, kSelAll, s);
+  if (sym && nt > 1)
+    hipLaunchKernelGGL(k_mirror_lower<T>, dim3(nt * (nt - 1) / 2, nmat), dim3(256), 0, s, mats, ld,
+                       o);
+#undef GJCHK
+  return hipSuccess;
+}
+
+// The outer elimination.  Schedule (Q the block after P):
+//   s    : invert(P) left(P) | next(P), invert(Q)    | left(Q) ...
+//   gs.o :                   | rest(P), right(P)     |
+// next(P) updates D[Q, Q], so that Q is inverted while the other products of P
+// run (right(P) waits for next(P), which reads column block P); left(Q) waits
+// for them.
+static hipError_t invert_outer(void *const *mats, int nmat, int ld, int n, int M, float *w,
+                               int *flag, int any_sign, int sym, GjStreams &gs, hipStream_t s) {
+  float *R = w + (size_t)nmat * (4 * (size_t)kNB * kOuter + (size_t)kNB * kNB);  // sym only
+  hipError_t e = hipSuccess;
+#define GJCHK(call)                           \
+  do {                                        \
+    if ((e = (call)) != hipSuccess) return e; \
+  } while (0)
+  auto rows = [&](int a, int b) { return (double)std::max(std::min(b, M) - a, 0); };
+  for (int p0 = 0; p0 < n; p0 += kOuter) {
+    const OuterStep st{ld, n, M, p0, std::min(p0 + kOuter, n), std::min(p0 + 2 * kOuter, n)};
+    const bool last = st.p1 == n;
+    GJCHK(invert_block<float>(mats, nmat, ld, p0, st.w() / kTile, M, w, flag, any_sign, sym, gs,
+                              s));
+    if (p0 > 0) GJCHK(hipStreamWaitEvent(s, gs.rest, 0));
+    const double kf = 2.0 * nmat * rows(p0, st.p1);
+    const double out = (double)M - rows(p0, st.p1);
+    const int nleft = outside_tiles(st, OuterLeft::TN);
+    ProfSpan ps = prof_open(KK_GJ_UPDATE);
+    if (sym)
+      hipExtLaunchKernelGGL(k_gj_left_sym, dim3(nleft * nmat), dim3(512), 0, s, ps.a, ps.b, 0,
+                            mats, R, st);
+    else
+      hipExtLaunchKernelGGL(k_gj_left, dim3(nleft * nmat), dim3(512), 0, s, ps.a, ps.b, 0, mats,
+                            st);
+    prof_close(ps, KK_GJ_UPDATE, kf * rows(p0, st.p1) * out);
+    auto update = [&](int sel, hipStream_t q) {
+      int i0, j0;
+      const int tpm = outer_tiles(st, sel, sym != 0, -1, i0, j0);
+      if (tpm <= 0) return;
+      const ProfSpan pu = prof_open(KK_GJ_UPDATE);
+      hipExtLaunchKernelGGL(sym ? k_gj_update_outer<true> : k_gj_update_outer<false>,
+                            dim3(tpm * nmat), dim3(512), 0, q, pu.a, pu.b, 0, mats,
+                            (const float *)R, st, sel, tpm);
+      const double qn = rows(st.p1, st.q1), nx = sym ? qn * (qn + 1) / 2 : qn * qn;
+      const double all = sym ? out * (out + 1) / 2 : out * out;
+      prof_close(pu, KK_GJ_UPDATE, kf * (sel == kOutNext ? nx : sel == kOutRest ? all - nx : all));
+    };
+    auto finish = [&](hipStream_t q) {  // column block P (and row block P if sym)
+      if (sym) {
+        hipLaunchKernelGGL(k_gj_out_sym, dim3((n - st.w()) / kTile * (st.w() / kTile), nmat),
+                           dim3(256), 0, q, mats, (const float *)R, st);
+        return;
+      }
+      const ProfSpan pu = prof_open(KK_GJ_UPDATE);
+      hipExtLaunchKernelGGL(k_gj_right, dim3(outside_tiles(st, OuterRight::TM) * nmat), dim3(512),
+                            0, q, pu.a, pu.b, 0, mats, st);
+      prof_close(pu, KK_GJ_UPDATE, kf * rows(p0, st.p1) * out);
+    };
+    if (last) {
+      update(kOutAll, s);
+      finish(s);
     } else {
-      if (p >= 1) GJCHK(hipStreamWaitEvent(s, ev_rest[(p - 1) & 1], 0));
-      update(p, kSelAll, s, nullptr);
+      GJCHK(hipEventRecord(gs.left, s));
+      GJCHK(hipStreamWaitEvent(gs.o, gs.left, 0));
+      update(kOutNext, s);
+      GJCHK(hipEventRecord(gs.next, s));
+      update(kOutRest, gs.o);
+      // column block P is overwritten: the update of the next diagonal reads it
+      GJCHK(hipStreamWaitEvent(gs.o, gs.next, 0));
+      finish(gs.o);
+      GJCHK(hipEventRecord(gs.rest, gs.o));
     }
   }
-  if (sym && nt > 1)
-    hipLaunchKernelGGL(k_mirror_lower<T>, dim3(nt * (nt - 1) / 2, nmat), dim3(256), 0, s, mats,
-                       ld);
+  if (sym) {
+    const int nt = n / kTile;
+    hipLaunchKernelGGL(k_mirror_lower<float>, dim3(nt * (nt - 1) / 2, nmat), dim3(256), 0, s, mats,
+                       ld, 0);
+  }
 #undef GJCHK
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+template <typename T>
+hipError_t gj_invert(void *const *mats, int nmat, int ld, int M, void *work, int *flag,
+                     int any_sign, int sym, GjStreams &gs, hipStream_t s) {
+  if (nmat <= 0) return hipSuccess;
+  static_assert(kNB == kTile && kOuter % kTile == 0, "one pivot block per tile row");
+  T *w = static_cast<T *>(work);
+  const int n = (M + kTile - 1) / kTile * kTile;  // blocks of padding alone need no step
+  if (sym && n > 0)
+    hipLaunchKernelGGL(k_sym_diag<T>, dim3(n / kTile, nmat), dim3(256), 0, s, mats, ld);
+  hipError_t e;
+  if (n <= block_width(ld, sizeof(T)))
+    e = invert_block<T>(mats, nmat, ld, 0, n / kTile, M, w, flag, any_sign, sym, gs, s);
+  else if constexpr (std::is_same<T, float>::value)
+    e = invert_outer(mats, nmat, ld, n, M, w, flag, any_sign, sym, gs, s);
+  else
+    e = hipErrorInvalidValue;  // not reached: FP64 blocks are as wide as the matrix
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
 #define DDST_INST(T)                                                                      \
   template void launch_assemble<T>(const AsmJob *, int, const double *, int, int, int, int, \
                                    hipStream_t);                                           \
   template void launch_scale_cols<T>(const GemmJob *, int, int, double, hipStream_t);       \
-  template void launch_gemm<T>(const GemmJob *, int, int, int, double, double, hipStream_t); \
+  template void launch_gemm<T>(const GemmJob *, int, int, int, double, bool, hipStream_t);    \
+  template void launch_gemm_full<T>(const GemmJob *, int, int, bool, double, double,          \
+                                    hipStream_t);                                            \
   template void launch_gemm_rect<T>(const GemmJob *, int, int, int, int, int, int, double,     \
-                                    double, hipStream_t);                                      \
+                                    hipStream_t);                                              \
   template hipError_t gj_invert<T>(void *const *, int, int, int, void *, int *, int, int,   \
                                    GjStreams &, hipStream_t);
 DDST_INST(float)

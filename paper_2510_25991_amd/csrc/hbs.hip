@@ -991,12 +991,12 @@ void sample_chains(ddst_op *op, const double *Om, const double *Ps, int s, int s
   BMem tab(all.size() * sizeof(GemmJob));
   BCHK(hipMemcpyAsync(tab.p, all.data(), all.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st));
   const GemmJob *dj = tab.as<GemmJob>();
-  launch_gemm_rect<T>(dj + wfirst, nds, ld, sp, M, s, 1, 1.0, 0.0, st);
+  launch_gemm_rect<T>(dj + wfirst, nds, ld, sp, M, s, 1, 1.0, st);
   for (int i = 1; i <= m - 1; ++i) {
-    launch_gemm_rect<T>(dj + lyN[i].first, lyN[i].second, ld, sp, M, s, 0, -1.0, 0.0, st);
-    launch_gemm_rect<T>(dj + lyT[i].first, lyT[i].second, ld, sp, M, s, 1, -1.0, 0.0, st);
+    launch_gemm_rect<T>(dj + lyN[i].first, lyN[i].second, ld, sp, M, s, 0, -1.0, st);
+    launch_gemm_rect<T>(dj + lyT[i].first, lyT[i].second, ld, sp, M, s, 1, -1.0, st);
   }
-  launch_gemm_rect<T>(dj + yfirst, 2 * ns, ld, sp, M, s, 0, -1.0, 0.0, st);
+  launch_gemm_rect<T>(dj + yfirst, 2 * ns, ld, sp, M, s, 0, -1.0, st);
   // FP64 cluster-order samples; the Z chains end with a row scaling
   const size_t per = (size_t)M * s;
   for (int sl = 1; sl <= ns; ++sl)

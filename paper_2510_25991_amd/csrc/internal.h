@@ -47,13 +47,14 @@ struct AsmJob {
   int pad_;
 };
 
-// One batched GEMM job: C = alpha * A * diag(bscale) * B + beta * C
-// (all ld x ld; bscale may be null).
+// One batched GEMM job: C = alpha * diag(cscale) * A * diag(bscale) * B
+// (+ beta * C) with A, B, C ld x ld; each launch says which scalings it reads.
 struct GemmJob {
   const void *A;
   const void *B;
   void *C;
   const double *bscale;
+  const double *cscale;
 };
 
 // One batched GEMV job (vectors float64, matrix type T):
@@ -124,34 +125,44 @@ void launch_assemble(const AsmJob *jobs, int njobs, const double *coef, int n, i
                      int M, int ld, hipStream_t s);
 // M (the unpadded size) only enters the algorithmic work recorded by the
 // profiler: 2 M^3 flops per GEMM, 2 M^2 kNB per Gauss-Jordan update.
+// C = alpha diag(cscale) A diag(bscale) (cscale null: 1)
 template <typename T>
 void launch_scale_cols(const GemmJob *jobs, int njobs, int ld, double alpha, hipStream_t s);
+// C = alpha diag(cscale) A B, or A B^T (cscale null: 1)
 template <typename T>
-void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, double beta,
+void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, bool trans_b,
                  hipStream_t s);
-// C (ld x ldc) = alpha op(A) diag(bscale) B + beta C: A ld x ld (op = A, or
+// C = alpha A diag(bscale) B + beta C; bscale: whether the jobs have one
+template <typename T>
+void launch_gemm_full(const GemmJob *jobs, int njobs, int ld, bool bscale, double alpha,
+                      double beta, hipStream_t s);
+// C (ld x ldc) = alpha op(A) diag(bscale) B: A ld x ld (op = A, or
 // A^T when trans), B and C ld x ldc row-major, ldc a multiple of 128 (the
-// block products of the sampling chains).  M and ncols (the unpadded sizes)
-// only enter the profiler's work: 2 M^2 ncols flops per job.
+// block products of the sampling chains).  Of A only the first M rows and
+// columns are multiplied (the others are padding, whose products are zero);
+// ncols only enters the profiler's work: 2 M^2 ncols flops per job.
 template <typename T>
 void launch_gemm_rect(const GemmJob *jobs, int njobs, int ld, int ldc, int M, int ncols,
-                      int trans, double alpha, double beta, hipStream_t s);
-// Helper stream and events of the look-ahead Gauss-Jordan schedule, created
-// once and reused by every inversion of a build (destroyed with the object).
+                      int trans, double alpha, hipStream_t s);
+// Helper stream and events of the Gauss-Jordan schedule, created once and
+// reused by every inversion of a build (destroyed with the object).
 // Events are created without timing and with device-scope release only (a
 // system-scope release writes back the L2 caches, which after an update
-// launch holds megabytes of dirty lines); they are attached to the
-// dispatches they follow where possible.
+// launch holds megabytes of dirty lines).
 struct GjStreams {
-  hipStream_t h = nullptr;   // bulk of each update
-  hipStream_t x = nullptr;   // the next pivot's row and column blocks
-  hipEvent_t panel = nullptr;
-  hipEvent_t rest[2] = {nullptr, nullptr};
-  hipEvent_t cross[2] = {nullptr, nullptr};
+  hipStream_t h = nullptr;     // updates beside the next pivots
+  hipStream_t x = nullptr;     // those that the next panel waits for
+  hipStream_t o = nullptr;     // products of an outer block beside the next one's inversion
+  hipEvent_t panel = nullptr;  // on s: a step's panel is done
+  hipEvent_t arms = nullptr;   // on x: the next step's row and column blocks are updated
+  hipEvent_t upd = nullptr;    // on h: a step's bulk update is done
+  hipEvent_t left = nullptr;   // on s: the outer block's row panel is done
+  hipEvent_t next = nullptr;   // on s: the next diagonal block is updated
+  hipEvent_t rest = nullptr;   // on o: the outer block is done
   GjStreams() = default;
   GjStreams(const GjStreams &) = delete;
   GjStreams &operator=(const GjStreams &) = delete;
-  hipError_t create();
+  hipError_t create(int ld, int M, size_t esz);  // for gj_invert with these
   ~GjStreams();
 };
 // Device status words of the local eliminations (32 bytes, zeroed at set-up):
@@ -168,24 +179,19 @@ struct ElimStatus {
   unsigned long long pad2_;
 };
 static_assert(sizeof(ElimStatus) == 32, "ElimStatus is 32 bytes");
-// In-place Gauss-Jordan inversion (no pivoting) of `nmat` ld x ld matrices
-// with look-ahead: the pivot and panel kernels of step p + 1 apply step p's
-// update to their own row block (on s), while the update of every other
-// tile of step p runs on gs.h.  work: gj_workspace_bytes
-// bytes (two R and two column panels, the pivot inverses); flag: device
-// ElimStatus: bad set to 1 when a pivot is non-finite, or non-positive
-// unless any_sign is non-zero, inv_max raised to the largest |entry| of
-// the inverted pivot blocks; sym non-zero: the matrices are symmetric and
-// only their lower triangle is eliminated (the inverse is mirrored at the
-// end).  Everything is ordered before later work on s when the call
-// returns.
+// In-place Gauss-Jordan inversion (no pivoting) of `nmat` ld x ld matrices,
+// by outer blocks of 512 rows with look-ahead.  work: gj_workspace_bytes
+// bytes; flag: device ElimStatus: bad set to 1 when a pivot is non-finite, or
+// non-positive unless any_sign is non-zero, inv_max raised to the largest
+// |entry| of the inverted pivot blocks; sym non-zero: the matrices are
+// symmetric and only their lower triangle is eliminated (the inverse is
+// mirrored at the end).  Everything is ordered before later work on s when the
+// call returns.
 template <typename T>
 hipError_t gj_invert(void *const *mats, int nmat, int ld, int M, void *work, int *flag,
                      int any_sign, int sym, GjStreams &gs, hipStream_t s);
 // Bytes of Gauss-Jordan workspace for nmat matrices.
-inline size_t gj_workspace_bytes(int nmat, int ld, size_t esz) {
-  return (size_t)nmat * kNB * ld * esz * 4 + (size_t)nmat * kNB * kNB * esz;
-}
+size_t gj_workspace_bytes(int nmat, int ld, size_t esz, int sym);
 
 // ---- vector kernels (vec.hip) --------------------------------------------
 void launch_setup_coef(const double *kappa, const double *c, const double *bvec3,

@@ -1,0 +1,73 @@
+"""The batched dense kernels past one outer block and one tile size.
+
+Bounds: products as in test_gpu_kernels.py (2e-5 for up to 384 terms, growing
+with their number); inverses 8e-5 for ld <= 640 there, growing with ld; FP32
+transfer blocks against FP64 ones by tol.fp32_block_tol.
+"""
+import pytest
+import torch
+
+from tol import fp32_block_tol
+
+pytestmark = pytest.mark.gpu
+
+
+def ddst():
+    from paper_2510_25991_amd import ddst as mod
+    return mod
+
+
+def relerr(a, b):
+    return float((a - b).abs().max() / b.abs().max())
+
+
+@pytest.mark.parametrize("batch,ld", [(900, 128), (230, 384), (228, 512), (60, 896)])
+def test_many_tile_products(batch, ld):
+    """FP32 batches large enough for the 256 x 256 tiles, whole and partial."""
+    print(f"\n[gpu] products {batch} x {ld}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(ld)
+    A = torch.randn(batch, ld, ld, generator=g, device="cuda")
+    B = torch.randn(batch, ld, ld, generator=g, device="cuda")
+    C = torch.empty_like(A)
+    ddst().kernel_gemm(A, B, C, alpha=-1.0)
+    for b in (0, batch // 2, batch - 1):
+        ref = -(A[b].double() @ B[b].double())
+        assert relerr(C[b].double(), ref) <= 2e-5 * max(1.0, ld / 384)
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("ld,M", [(1152, 1025), (1152, 1152), (1280, 1225), (1664, 1536)])
+def test_outer_block_inverse(ld, M, symmetric):
+    """More rows than one outer block takes: a last block of one, two and
+    three steps, and one of padding alone."""
+    print(f"\n[gpu] kernel invert ld={ld} M={M} symmetric={symmetric}", flush=True)
+    g = torch.Generator().manual_seed(M)
+    batch = 2
+    A = torch.eye(ld, dtype=torch.float64).repeat(batch, 1, 1)
+    X = torch.randn(batch, M, M, generator=g, dtype=torch.float64)
+    if symmetric:
+        X = (X + X.transpose(1, 2)) / 2 ** 0.5
+    A[:, :M, :M] = 3.0 * torch.eye(M, dtype=torch.float64) + X / M ** 0.5
+    A = A.float()
+    Ad = A.cuda()
+    ddst().kernel_invert(Ad, symmetric=symmetric)
+    ref = torch.linalg.inv(A.double())
+    assert relerr(Ad.cpu().double(), ref) <= 8e-5 * ld / 640
+
+
+@pytest.mark.parametrize("b", [0.0, 10.0])
+@pytest.mark.parametrize("n,slabs", [(35, 6), (11, 4), (19, 5), (27, 7)])
+def test_transfer_blocks_of_ragged_planes(n, slabs, b):
+    """3D planes of 1225 (outer blocks), 121, 361 and 729 rows, padded to tiles;
+    symmetric (transposed chains) and not."""
+    print(f"\n[gpu] transfer blocks n={n} slabs={slabs} b={b}", flush=True)
+    ops = [ddst().Operator(3, n, slabs, bvec=(b, 0.0, 0.0), precision=p)
+           for p in ("fp32", "fp64")]
+    worst = scale = 0.0
+    for j in range(1, slabs):
+        for x, y in zip(ops[0].transfer(j), ops[1].transfer(j)):
+            worst = max(worst, float((x.double() - y.double()).abs().max()))
+            scale = max(scale, float(y.abs().max()))
+    for op in ops:
+        op.close()
+    assert worst <= fp32_block_tol((n + 1) // slabs, n * n) * scale
