@@ -6,6 +6,7 @@
 // coefficient is the mean of the 2^(dim-1) cells sharing the edge,
 // convection uses centred differences, and boundary neighbours carry g.
 #include <stdexcept>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -496,108 +497,187 @@ __global__ void k_fill(double *__restrict__ y, double v, size_t len) {
   if (e < len) y[e] = v;
 }
 
-// Dot products of w with nvec vectors (stride apart), two passes:
-// part[chunk][i] = sum over a 256-element chunk (one wavefront per vector,
-// the chunk of w staged in LDS), then out[i] = sum over chunks (fixed order,
-// deterministic).  A null V means w itself (squared norm).
-constexpr int kDotChunk = 256;
-constexpr int kDotVecs = 8;  // basis vectors per wavefront and round
+// ---- passes over a Krylov basis ---------------------------------------------
+// V: vectors of len entries, `stride` apart, 10 to 1000 of them, len 10^3 to
+// 10^6.  What bounds them is the loads in flight: a work-group takes a chunk of
+// 64 T entries (T per lane) and its 16 wavefronts share the vectors, eight at
+// a time with their loads issued together, so that a short basis of many
+// vectors still fills the chip (chunks of 256 entries with one thread each
+// for all vectors, and of 2048 with 32 vectors per work-group: 1.1 TB/s).
+// T = 1, 2, 4, the largest that leaves a chunk per CU (kDotChunks).
+// Sums are FP64, in a fixed order.
+constexpr int kDotWaves = 16;  // wavefronts per work-group
+constexpr int kDotVecs = 8;    // basis vectors per wavefront and round
+constexpr int kDotRound = kDotWaves * kDotVecs;
 
-// Partial dot products of one kDotChunk chunk (in LDS, zero past the end)
-// with V_0..V_{nvec-1} (V null: the chunk with itself), one wavefront per
-// vector: part[chunk * nvec + i].
-// Each wavefront takes kDotVecs vectors at a time with independent sums,
-// their loads issued together (entries past the chunk re-read its last element
-// and meet a zero of ws).
-template <typename B>
-__device__ __forceinline__ void chunk_dots(const B *__restrict__ V, size_t stride,
-                                           int nvec, const double *ws, size_t base, int cn,
-                                           double *__restrict__ part) {
-  constexpr int E = kDotChunk / 64;  // entries per lane
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double wv[E];
+// T entries of v from e0 (FULL: all inside the chunk; else those past its cn
+// entries repeat the last one, and the caller drops or zeroes what they give).
+template <int T, bool FULL, typename B>
+__device__ __forceinline__ void ld_entries(const B *v, int e0, int cn, double (&x)[T]) {
+  if constexpr (FULL && T > 1) {
+    // stride is any number: only the alignment of an entry
+    typedef B vec __attribute__((ext_vector_type(T), aligned(sizeof(B))));
+    const vec q = *reinterpret_cast<const vec *>(v + e0);
 #pragma unroll
-  for (int t = 0; t < E; ++t) wv[t] = ws[lane + 64 * t];
-  if (!V) {  // squared norm of the chunk (nvec == 1): the first wavefront
-    if (wave == 0) {
+    for (int t = 0; t < T; ++t) x[t] = (double)q[t];
+  } else {
+#pragma unroll
+    for (int t = 0; t < T; ++t) x[t] = (double)v[FULL ? e0 + t : min(e0 + t, cn - 1)];
+  }
+}
+
+// Sums over the wavefront of N values per lane (N a power of two), halved at
+// each exchange: lane l returns the sum of value l / (64 / N).
+template <int N, int OFF = 32> __device__ __forceinline__ double wave_sums(const double (&v)[N]) {
+  if constexpr (N > 1) {
+    const bool up = threadIdx.x & OFF;
+    double r[N / 2];
+#pragma unroll
+    for (int u = 0; u < N / 2; ++u)
+      r[u] = (up ? v[u + N / 2] : v[u]) + __shfl_xor(up ? v[u] : v[u + N / 2], OFF);
+    return wave_sums<N / 2, OFF / 2>(r);
+  } else {
+    double r = v[0];
+#pragma unroll
+    for (int off = OFF; off > 0; off >>= 1) r += __shfl_xor(r, off);
+    return r;
+  }
+}
+
+// sum[c][t] += coef_c[i] V_i (NC sets of coefficients) over the wavefront's
+// share of the nvec vectors, at its lanes' entries of the chunk.
+template <int NC, int T, bool FULL, typename B>
+__device__ __forceinline__ void chunk_combine(const B *V, size_t stride, int nvec,
+                                              const double *const (&coef)[NC], int cn,
+                                              double (&sum)[NC][T]) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int t = 0; t < T; ++t) sum[c][t] = 0.0;
+  for (int i0 = wave * kDotVecs; i0 < nvec; i0 += kDotRound) {
+    double x[kDotVecs][T];
+#pragma unroll
+    for (int u = 0; u < kDotVecs; ++u)
+      ld_entries<T, FULL>(V + (size_t)min(i0 + u, nvec - 1) * stride, lane * T, cn, x[u]);
+#pragma unroll
+    for (int u = 0; u < kDotVecs; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const double h = i0 + u < nvec ? coef[c][min(i0 + u, nvec - 1)] : 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) sum[c][t] += x[u][t] * h;
+      }
+  }
+}
+
+// The wavefronts' sums added up: the first 64 T threads get entry threadIdx.x
+// of every set.  red: NC kDotWaves 64 T doubles.
+template <int NC, int T>
+__device__ __forceinline__ void chunk_gather(const double (&sum)[NC][T], double *red,
+                                             double (&out)[NC]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      red[(c * kDotWaves + wave) * 64 * T + lane * T + t] = sum[c][t];
+  __syncthreads();
+  if (threadIdx.x < 64 * T)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
       double s = 0.0;
 #pragma unroll
-      for (int t = 0; t < E; ++t) s += wv[t] * wv[t];
-      s = wave_sum(s);
-      if (lane == 0) part[blockIdx.x] = s;
+      for (int w = 0; w < kDotWaves; ++w) s += red[(c * kDotWaves + w) * 64 * T + threadIdx.x];
+      out[c] = s;
     }
+}
+
+// Sum of x over the first 64 T threads of the work-group, in thread 0.
+template <int T> __device__ __forceinline__ double chunk_sum(double x, double *sh) {
+  if (threadIdx.x < 64 * T) {
+    x = wave_sum(x);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
+  }
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x == 0)
+    for (int w = 0; w < T; ++w) s += sh[w];
+  return s;
+}
+
+// Per chunk: w += sign V h (nvec vectors; 0: none), then, of the updated
+// chunk, the partial dot products with the same basis (ndot vectors),
+// part[chunk * ndot + i], or its partial squared norm part[chunk] (ndot 0), or
+// nothing (ndot < 0).
+template <typename B, int T>
+__global__ __launch_bounds__(64 * kDotWaves) void k_mgs_update_dots(
+    double *__restrict__ w, const B *__restrict__ V, size_t stride, int nvec,
+    const double *__restrict__ h, double sign, size_t len, int ndot, double *__restrict__ part) {
+  __shared__ double red[kDotWaves * 64 * T], ws[64 * T], sh[T];
+  const size_t base = (size_t)blockIdx.x * 64 * T;
+  const int cn = (int)min((size_t)(64 * T), len - base);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const B *v = V + base;
+  double we = tid < cn ? w[base + tid] : 0.0;
+  if (nvec > 0) {
+    double sum[1][T], r[1] = {0.0};
+    const double *const coef[1] = {h};
+    if (cn == 64 * T)
+      chunk_combine<1, T, true>(v, stride, nvec, coef, cn, sum);
+    else
+      chunk_combine<1, T, false>(v, stride, nvec, coef, cn, sum);
+    chunk_gather<1, T>(sum, red, r);
+    if (tid < cn) {
+      we += sign * r[0];
+      w[base + tid] = we;
+    }
+  }
+  if (ndot < 0) return;
+  if (ndot == 0) {
+    const double s = chunk_sum<T>(tid < cn ? we * we : 0.0, sh);
+    if (tid == 0) part[blockIdx.x] = s;
     return;
   }
-  for (int i0 = wave; i0 < nvec; i0 += 4 * kDotVecs) {
-    double s[kDotVecs];
+  if (tid < 64 * T) ws[tid] = we;
+  __syncthreads();
+  double wv[T];
 #pragma unroll
-    for (int u = 0; u < kDotVecs; ++u) s[u] = 0.0;
+  for (int t = 0; t < T; ++t) wv[t] = ws[lane * T + t];
+  auto dots = [&](auto full) {
+    for (int i0 = wave * kDotVecs; i0 < ndot; i0 += kDotRound) {
+      double x[kDotVecs][T], s[kDotVecs];
 #pragma unroll
-    for (int u = 0; u < kDotVecs; ++u) {
-      const int i = i0 + 4 * u;
-      if (i < nvec) {
-        const B *v = V + (size_t)i * stride + base;
+      for (int u = 0; u < kDotVecs; ++u)
+        ld_entries<T, decltype(full)::value>(v + (size_t)min(i0 + u, ndot - 1) * stride, lane * T,
+                                             cn, x[u]);
 #pragma unroll
-        for (int t = 0; t < E; ++t) {
-          const int e = lane + 64 * t;
-          s[u] += (double)v[e < cn ? e : cn - 1] * wv[t];
-        }
+      for (int u = 0; u < kDotVecs; ++u) {
+        s[u] = 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) s[u] += x[u][t] * wv[t];
       }
+      const double r = wave_sums<kDotVecs>(s);
+      const int i = i0 + lane / (64 / kDotVecs);
+      if (lane % (64 / kDotVecs) == 0 && i < ndot) part[(size_t)blockIdx.x * ndot + i] = r;
     }
-#pragma unroll
-    for (int u = 0; u < kDotVecs; ++u) {
-      const int i = i0 + 4 * u;
-      const double r = wave_sum(s[u]);
-      if (lane == 0 && i < nvec) part[(size_t)blockIdx.x * nvec + i] = r;
-    }
-  }
+  };
+  if (cn == 64 * T)
+    dots(std::true_type{});
+  else
+    dots(std::false_type{});
 }
 
-template <typename B>
-__global__ __launch_bounds__(256) void k_multidot_part(const B *__restrict__ V, size_t stride,
-                                                       int nvec, const double *__restrict__ w,
-                                                       size_t len, double *__restrict__ part) {
-  __shared__ double ws[kDotChunk];
-  const size_t base = (size_t)blockIdx.x * kDotChunk;
-  const int cn = (int)min((size_t)kDotChunk, len - base);
-  for (int e = threadIdx.x; e < kDotChunk; e += 256) ws[e] = (e < cn) ? w[base + e] : 0.0;
-  __syncthreads();
-  chunk_dots(V, stride, nvec, ws, base, cn, part);
-}
-
-// One Gram-Schmidt update of a chunk, w += sign * V h, followed by the
-// partial dot products of the updated chunk for the next pass (V2 = V,
-// nvec2 = nvec) or its partial squared norm (V2 null, nvec2 = 1): the two
-// kernels of the classical scheme that touch the same chunk, fused.
-template <typename B>
-__global__ __launch_bounds__(256) void k_mgs_update_dots(double *__restrict__ w,
-                                                         const B *__restrict__ V,
-                                                         size_t stride, int nvec,
-                                                         const double *__restrict__ h,
-                                                         double sign, size_t len,
-                                                         const B *__restrict__ V2,
-                                                         int nvec2, double *__restrict__ part) {
-  __shared__ double ws[kDotChunk];
-  const size_t base = (size_t)blockIdx.x * kDotChunk;
-  const int cn = (int)min((size_t)kDotChunk, len - base);
-  const int e = threadIdx.x;  // kDotChunk == blockDim.x
-  double we = 0.0;
-  if (e < cn) {
-    // eight independent partial sums: eight basis-vector loads in flight
-    const B *v = V + base + e;
-    double t[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int i = 0;
-    for (; i + 8 <= nvec; i += 8)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] += (double)v[(size_t)(i + u) * stride] * h[i + u];
-    for (; i < nvec; ++i) t[0] += (double)v[(size_t)i * stride] * h[i];
-    const double sum = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-    we = w[base + e] + sign * sum;
-    w[base + e] = we;
-  }
-  ws[e] = we;
-  __syncthreads();
-  chunk_dots(V2, stride, nvec2, ws, base, cn, part);
+// Partial squared norms per chunk of 256 entries.
+__global__ __launch_bounds__(256) void k_norm_part(const double *__restrict__ w, size_t len,
+                                                   double *__restrict__ part) {
+  __shared__ double sh[4];
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const double x = e < len ? w[e] : 0.0;
+  const double s = block_sum(x * x, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 // Column j of H, staged in LDS cl[0..j+1] (cl[j+1] = hn, the subdiagonal
@@ -763,19 +843,16 @@ __global__ __launch_bounds__(256) void k_norm_scale_givens(const double *__restr
                                                            double *__restrict__ dst,
                                                            float *__restrict__ slot, size_t len,
                                                            GmresDev gd, int k, double beta) {
-  __shared__ double sh[1];
-  if (threadIdx.x < 64) {
-    double s = 0.0;
-    for (int c = threadIdx.x; c < nchunk; c += 64) s += part[c];
-    s = wave_sum(s);
-    if (threadIdx.x == 0) {
-      const double d = sqrt(s);
-      sh[0] = d;
-      if (blockIdx.x == 0) hd[2 * (k + 1)] = d;
-    }
+  __shared__ double sh[4], snorm;
+  double s = 0.0;
+  for (int c = threadIdx.x; c < nchunk; c += 256) s += part[c];
+  s = block_sum(s, sh);
+  if (threadIdx.x == 0) {
+    snorm = sqrt(s);
+    if (blockIdx.x == 0) hd[2 * (k + 1)] = snorm;
   }
   __syncthreads();
-  const double d = sh[0];
+  const double d = snorm;
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < len) {
     const double v = (d > 0.0) ? src[e] / d : 0.0;
@@ -789,79 +866,70 @@ __global__ __launch_bounds__(256) void k_norm_scale_givens(const double *__restr
 
 // Pass A: partial dot products of the m - 1 basis vectors Q (V, stride) and
 // of the candidate u with u and with w (null: only those with u), per
-// kLagChunk-element chunk: part[chunk][i] = V_i . u, part[chunk][m + i] =
+// kLagChunk-entry chunk: part[chunk][i] = V_i . u, part[chunk][m + i] =
 // V_i . w (i < m - 1), part[chunk][m - 1] = u . u, part[chunk][2 m - 1] =
-// u . w.  Work-group (chunk, g) takes the chunk of u and w (in LDS) and the
-// kLagGroup basis vectors g kLagGroup ..: each wavefront 8 of them, four at
-// a time with their loads issued together, 32 entries per lane and vector
-// before one reduction per product; group 0 also forms the products of u.
-constexpr int kLagChunk = 2048, kLagGroup = 32;
+// u . w.  Work-group (chunk, g): vectors g kDotRound .., eight per wavefront;
+// group 0 also forms the products of u.  500 FP64 vectors of 15345: 54 us
+// with chunks of 2048 and 32 vectors per work-group (128 of them).
+constexpr int kLagChunk = 256;
 template <typename B>
-__global__ __launch_bounds__(256) void k_lag_dots(const B *__restrict__ V, size_t stride, int m,
-                                                  const double *__restrict__ u,
-                                                  const double *__restrict__ w, size_t len,
-                                                  double *__restrict__ part) {
-  constexpr int E = kLagChunk / 64;  // entries per lane and vector
-  __shared__ double us[kLagChunk], zs[kLagChunk];
+__global__ __launch_bounds__(64 * kDotWaves) void k_lag_dots(const B *__restrict__ V, size_t stride,
+                                                             int m, const double *__restrict__ u,
+                                                             const double *__restrict__ w,
+                                                             size_t len,
+                                                             double *__restrict__ part) {
+  constexpr int T = kLagChunk / 64;
   const size_t base = (size_t)blockIdx.x * kLagChunk;
   const int cn = (int)min((size_t)kLagChunk, len - base);
-  for (int e = threadIdx.x; e < kLagChunk; e += 256) {
-    us[e] = e < cn ? u[base + e] : 0.0;
-    zs[e] = (w && e < cn) ? w[base + e] : 0.0;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double *pc = part + (size_t)blockIdx.x * 2 * m;
-  if (blockIdx.y == 0 && wave == 0) {
-    double su = 0.0, sz = 0.0;
-    for (int t = 0; t < E; ++t) {
-      const double x = us[lane + 64 * t];
-      su += x * x;
-      sz += x * zs[lane + 64 * t];
-    }
-    su = wave_sum(su);
-    sz = wave_sum(sz);
-    if (lane == 0) {
-      pc[m - 1] = su;
-      pc[2 * m - 1] = sz;
-    }
-  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nq = m - 1;
-  const int i0 = blockIdx.y * kLagGroup + wave;
-#pragma unroll 1
-  for (int h = 0; h < kLagGroup / 4; h += 4) {
-    // vectors i0 + 4 (h + q), q < 4
-    double su[4] = {0.0, 0.0, 0.0, 0.0}, sz[4] = {0.0, 0.0, 0.0, 0.0};
-    const B *v[4];
+  const int i0 = blockIdx.y * kDotRound + wave * kDotVecs;
+  const bool own = blockIdx.y == 0 && wave == kDotWaves - 1;
+  if (i0 >= nq && !own) return;
+  double *pc = part + (size_t)blockIdx.x * 2 * m;
+  double a[T], c[T];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = min(i0 + 4 * (h + q), max(nq - 1, 0));
-      v[q] = V + (size_t)i * stride + base;
-    }
-    if (i0 + 4 * h < nq) {
-#pragma unroll 4
-      for (int t = 0; t < E; ++t) {
-        const int e = lane + 64 * t;
-        const int el = e < cn ? e : cn - 1;
-        const double a = us[e], c = zs[e];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const double x = (double)v[q][el];
-          su[q] += x * a;
-          sz[q] += x * c;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = i0 + 4 * (h + q);
-      const double ru = wave_sum(su[q]), rz = wave_sum(sz[q]);
-      if (lane == 0 && i < nq) {
-        pc[i] = ru;
-        pc[m + i] = rz;
-      }
-    }
+  for (int t = 0; t < T; ++t) {
+    const int e = lane * T + t;
+    a[t] = e < cn ? u[base + e] : 0.0;
+    c[t] = (w && e < cn) ? w[base + e] : 0.0;
   }
+  if (own) {
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      s[0] += a[t] * a[t];
+      s[1] += a[t] * c[t];
+    }
+    const double r = wave_sums<2>(s);
+    if (lane % 32 == 0) pc[lane == 0 ? m - 1 : 2 * m - 1] = r;
+  }
+  if (i0 >= nq) return;
+  double s[2 * kDotVecs];
+  auto dots = [&](auto full) {
+    double x[kDotVecs][T];
+#pragma unroll
+    for (int q = 0; q < kDotVecs; ++q)
+      ld_entries<T, decltype(full)::value>(V + (size_t)min(i0 + q, nq - 1) * stride + base,
+                                           lane * T, cn, x[q]);
+#pragma unroll
+    for (int q = 0; q < kDotVecs; ++q) {
+      s[q] = s[kDotVecs + q] = 0.0;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        s[q] += x[q][t] * a[t];
+        s[kDotVecs + q] += x[q][t] * c[t];
+      }
+    }
+  };
+  if (cn == kLagChunk)
+    dots(std::true_type{});
+  else
+    dots(std::false_type{});
+  const double r = wave_sums<2 * kDotVecs>(s);
+  const int q = lane / (32 / kDotVecs), i = i0 + q % kDotVecs;
+  if (lane % (32 / kDotVecs) == 0 && i < nq) pc[(q < kDotVecs ? 0 : m) + i] = r;
 }
 
 // nu = |u - Q a| = sqrt(|u|^2 - |a|^2) from the pass-A products (every
@@ -932,44 +1000,39 @@ __global__ __launch_bounds__(256) void k_lag_coef(GmresDev d, int k) {
   }
 }
 
-// Pass B, per 256-element chunk: q_k = (u - Q a) / nu into slot k of V, w =
+// Pass B, per chunk of 64 T entries: q_k = (u - Q a) / nu into slot k of V, w =
 // w / nu - Q f - g u, and the chunk's partial squared norm of the new w.
-// u may be slot k itself (an FP64 basis): each element is read before it is
-// overwritten, by the same thread.
-template <typename B>
-__global__ __launch_bounds__(256) void k_lag_update(B *V, size_t stride, int k, const double *u,
-                                                    double *__restrict__ w, size_t len,
-                                                    GmresDev d, double *__restrict__ part) {
-  __shared__ double sh[4];
-  const size_t e = (size_t)blockIdx.x * kDotChunk + threadIdx.x;
+// u may be slot k itself (an FP64 basis): each entry is read before it is
+// overwritten, by the same thread.  500 FP64 vectors of 15345: 50 us with one
+// thread an entry for all vectors.
+template <typename B, int T>
+__global__ __launch_bounds__(64 * kDotWaves) void k_lag_update(B *V, size_t stride, int k,
+                                                               const double *u,
+                                                               double *__restrict__ w, size_t len,
+                                                               GmresDev d,
+                                                               double *__restrict__ part) {
+  __shared__ double red[2 * kDotWaves * 64 * T], sh[T];
+  const size_t base = (size_t)blockIdx.x * 64 * T;
+  const int cn = (int)min((size_t)(64 * T), len - base);
+  const int tid = threadIdx.x;
+  double sum[2][T], r[2] = {0.0, 0.0};
+  const double *const coef[2] = {d.dA, d.cf};
+  if (cn == 64 * T)
+    chunk_combine<2, T, true>(V + base, stride, k, coef, cn, sum);
+  else
+    chunk_combine<2, T, false>(V + base, stride, k, coef, cn, sum);
+  chunk_gather<2, T>(sum, red, r);
   double zn = 0.0;
-  if (e < len) {
-    const double *a = d.dA, *f = d.cf;
-    const B *v = V + e;
-    double ta[8] = {0, 0, 0, 0, 0, 0, 0, 0}, tf[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int i = 0;
-    for (; i + 8 <= k; i += 8)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double x = (double)v[(size_t)(i + q) * stride];
-        ta[q] += x * a[i + q];
-        tf[q] += x * f[i + q];
-      }
-    for (; i < k; ++i) {
-      const double x = (double)v[(size_t)i * stride];
-      ta[0] += x * a[i];
-      tf[0] += x * f[i];
-    }
-    const double sa = ((ta[0] + ta[1]) + (ta[2] + ta[3])) + ((ta[4] + ta[5]) + (ta[6] + ta[7]));
-    const double sf = ((tf[0] + tf[1]) + (tf[2] + tf[3])) + ((tf[4] + tf[5]) + (tf[6] + tf[7]));
+  if (tid < cn) {
+    const size_t e = base + tid;
     const double inv = d.sc[0], g = d.sc[1];
     const double ue = u[e];
-    V[(size_t)k * stride + e] = (B)((ue - sa) * inv);
-    zn = w[e] * inv - sf - g * ue;
+    V[(size_t)k * stride + e] = (B)((ue - r[0]) * inv);
+    zn = w[e] * inv - r[1] - g * ue;
     w[e] = zn;
   }
-  const double s = block_sum(zn * zn, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+  const double s = chunk_sum<T>(zn * zn, sh);
+  if (tid == 0) part[blockIdx.x] = s;
 }
 
 // rho = |w| (every work-group sums the partials in the same order; the
@@ -979,19 +1042,16 @@ __global__ __launch_bounds__(256) void k_lag_norm_scale(const double *__restrict
                                                         const double *__restrict__ w,
                                                         double *__restrict__ vnext, size_t len,
                                                         GmresDev d, int givens_col, double beta) {
-  __shared__ double sh[1];
-  if (threadIdx.x < 64) {
-    double s = 0.0;
-    for (int c = threadIdx.x; c < nchunk; c += 64) s += part[c];
-    s = wave_sum(s);
-    if (threadIdx.x == 0) {
-      const double r = sqrt(s);
-      sh[0] = r;
-      if (blockIdx.x == 0 && len > 0) d.sc[2] = r;
-    }
+  __shared__ double sh[4], snorm;
+  double s = 0.0;
+  for (int c = threadIdx.x; c < nchunk; c += 256) s += part[c];
+  s = block_sum(s, sh);
+  if (threadIdx.x == 0) {
+    snorm = sqrt(s);
+    if (blockIdx.x == 0 && len > 0) d.sc[2] = snorm;
   }
   __syncthreads();
-  const double r = sh[0];
+  const double r = snorm;
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < len) vnext[e] = (r > 0.0) ? w[e] / r : 0.0;
   if (blockIdx.x == 0 && givens_col >= 0) gmres_givens_raw(d, givens_col, beta);
@@ -1008,16 +1068,6 @@ __global__ __launch_bounds__(256) void k_multidot_reduce(const double *__restric
   for (int c = threadIdx.x; c < nchunk; c += 256) s += part[(size_t)c * nvec + i];
   s = block_sum(s, sh);
   if (threadIdx.x == 0) out[i] = take_sqrt ? sqrt(s) : s;
-}
-
-template <typename B>
-__global__ void k_mgs_update(double *__restrict__ w, const B *__restrict__ V, size_t stride,
-                             int nvec, const double *__restrict__ h, double sign, size_t len) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= len) return;
-  double s = 0.0;
-  for (int i = 0; i < nvec; ++i) s += (double)V[(size_t)i * stride + e] * h[i];
-  w[e] += sign * s;
 }
 
 __global__ void k_to_float(float *__restrict__ dst, const double *__restrict__ src, size_t len) {
@@ -1208,11 +1258,31 @@ void launch_fill(double *y, double v, size_t len, hipStream_t s) {
   hipLaunchKernelGGL(k_fill, dim3(nblk(len)), dim3(256), 0, s, y, v, len);
 }
 
+namespace {
+// f(std::integral_constant<int, T>) for vectors of len entries
+template <typename F> void with_dot_width(size_t len, F f) {
+  switch (dot_width(len)) {
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    default: return f(std::integral_constant<int, 4>{});
+  }
+}
+template <typename B>
+void update_dots(double *w, const B *V, size_t stride, int nvec, const double *h, double sign,
+                 size_t len, int ndot, double *part, hipStream_t s) {
+  with_dot_width(len, [&](auto t) {
+    constexpr int T = decltype(t)::value;
+    hipLaunchKernelGGL((k_mgs_update_dots<B, T>), dim3(nblk(len, 64 * T)), dim3(64 * kDotWaves), 0,
+                       s, w, V, stride, nvec, h, sign, len, ndot, part);
+  });
+}
+}  // namespace
+
 template <typename B>
 void launch_mgs_update(double *w, const B *V, size_t stride, int nvec, const double *h,
                        double sign, size_t len, hipStream_t s) {
-  hipLaunchKernelGGL(k_mgs_update<B>, dim3(nblk(len)), dim3(256), 0, s, w, V, stride, nvec, h,
-                     sign, len);
+  if (len == 0 || nvec <= 0) return;
+  update_dots<B>(w, V, stride, nvec, h, sign, len, -1, nullptr, s);
 }
 template void launch_mgs_update<double>(double *, const double *, size_t, int, const double *,
                                         double, size_t, hipStream_t);
@@ -1228,21 +1298,19 @@ void launch_arnoldi_step(const B *V, size_t stride, int k, double *w, size_t len
                          double *vnext, float *vslot, double *part, GmresDev gd, double beta,
                          hipStream_t s) {
   const int nvec = k + 1;
-  const int nchunk = (int)((len + kDotChunk - 1) / kDotChunk);
-  static_assert(kDotChunk == 256, "one element per thread in the fused update");
+  const int nchunk = (int)dot_chunks(len);
+  auto reduce = [&](double *out) {
+    hipLaunchKernelGGL(k_multidot_reduce, dim3(nvec), dim3(256), 0, s, (const double *)part,
+                       nchunk, nvec, out, 0);
+  };
   // pass 1: h1 = V^T w
-  hipLaunchKernelGGL(k_multidot_part<B>, dim3(nchunk), dim3(256), 0, s, V, stride, nvec,
-                     (const double *)w, len, part);
-  hipLaunchKernelGGL(k_multidot_reduce, dim3(nvec), dim3(256), 0, s, (const double *)part,
-                     nchunk, nvec, hd, 0);
+  update_dots<B>(w, V, stride, 0, nullptr, 0.0, len, nvec, part, s);
+  reduce(hd);
   // w -= V h1, then pass 2 partials
-  hipLaunchKernelGGL(k_mgs_update_dots<B>, dim3(nchunk), dim3(256), 0, s, w, V, stride, nvec,
-                     (const double *)hd, -1.0, len, V, nvec, part);
-  hipLaunchKernelGGL(k_multidot_reduce, dim3(nvec), dim3(256), 0, s, (const double *)part,
-                     nchunk, nvec, hd + nvec, 0);
+  update_dots<B>(w, V, stride, nvec, hd, -1.0, len, nvec, part, s);
+  reduce(hd + nvec);
   // w -= V h2, then partial squared norms; v_next = w / |w| and the rotations
-  hipLaunchKernelGGL(k_mgs_update_dots<B>, dim3(nchunk), dim3(256), 0, s, w, V, stride, nvec,
-                     (const double *)(hd + nvec), -1.0, len, (const B *)nullptr, 1, part);
+  update_dots<B>(w, V, stride, nvec, hd + nvec, -1.0, len, 0, part, s);
   hipLaunchKernelGGL(k_norm_scale_givens, dim3(nblk(len)), dim3(256), 0, s,
                      (const double *)part, nchunk, hd, (const double *)w, vnext, vslot, len, gd,
                      k, beta);
@@ -1259,12 +1327,11 @@ void launch_arnoldi_lagged(B *V, size_t stride, int k, const double *u, double *
                            double *unext, size_t len, double *part, GmresDev gd, double beta,
                            int col_final, int finalize_only, hipStream_t s) {
   const int m = k + 1;
-  const int nchunk = (int)((len + kDotChunk - 1) / kDotChunk);
-  static_assert(kDotChunk == 256, "one element per thread in pass B");
-  const int nlchunk = (int)((len + kLagChunk - 1) / kLagChunk);
-  const int ngroup = std::max((m - 1 + kLagGroup - 1) / kLagGroup, 1);
-  hipLaunchKernelGGL(k_lag_dots<B>, dim3(nlchunk, ngroup), dim3(256), 0, s, (const B *)V, stride,
-                     m, u, finalize_only ? (const double *)nullptr : (const double *)w, len, part);
+  const int nlchunk = (int)nblk(len, kLagChunk);
+  const int ngroup = std::max((m - 1 + kDotRound - 1) / kDotRound, 1);
+  hipLaunchKernelGGL(k_lag_dots<B>, dim3(nlchunk, ngroup), dim3(64 * kDotWaves), 0, s,
+                     (const B *)V, stride, m, u,
+                     finalize_only ? (const double *)nullptr : (const double *)w, len, part);
   hipLaunchKernelGGL(k_multidot_reduce, dim3(2 * m), dim3(256), 0, s, (const double *)part,
                      nlchunk, 2 * m, gd.dA, 0);
   hipLaunchKernelGGL(k_lag_hmul, dim3((m + 3) / 4), dim3(256), 0, s, gd, k, col_final);
@@ -1275,10 +1342,13 @@ void launch_arnoldi_lagged(B *V, size_t stride, int k, const double *u, double *
     return;
   }
   hipLaunchKernelGGL(k_lag_coef, dim3(1), dim3(256), 0, s, gd, k);
-  hipLaunchKernelGGL(k_lag_update<B>, dim3(nchunk), dim3(256), 0, s, V, stride, k, u, w, len, gd,
-                     part);
+  with_dot_width(len, [&](auto t) {
+    constexpr int T = decltype(t)::value;
+    hipLaunchKernelGGL((k_lag_update<B, T>), dim3(nblk(len, 64 * T)), dim3(64 * kDotWaves), 0, s, V,
+                       stride, k, u, w, len, gd, part);
+  });
   hipLaunchKernelGGL(k_lag_norm_scale, dim3(nblk(len)), dim3(256), 0, s, (const double *)part,
-                     nchunk, (const double *)w, unext, len, gd, gcol, beta);
+                     (int)dot_chunks(len), (const double *)w, unext, len, gd, gcol, beta);
 }
 template void launch_arnoldi_lagged<double>(double *, size_t, int, const double *, double *,
                                             double *, size_t, double *, GmresDev, double, int,
@@ -1288,9 +1358,8 @@ template void launch_arnoldi_lagged<float>(float *, size_t, int, const double *,
                                            int, hipStream_t);
 
 void launch_norm(const double *w, size_t len, double *out, double *part, hipStream_t s) {
-  const int nchunk = (int)((len + kDotChunk - 1) / kDotChunk);
-  hipLaunchKernelGGL(k_multidot_part<double>, dim3(nchunk), dim3(256), 0, s,
-                     (const double *)nullptr, (size_t)0, 1, w, len, part);
+  const int nchunk = (int)nblk(len);
+  hipLaunchKernelGGL(k_norm_part, dim3(nchunk), dim3(256), 0, s, w, len, part);
   hipLaunchKernelGGL(k_multidot_reduce, dim3(1), dim3(256), 0, s, part, nchunk, 1, out, 1);
 }
 

@@ -71,3 +71,20 @@ def test_transfer_blocks_of_ragged_planes(n, slabs, b):
     for op in ops:
         op.close()
     assert worst <= fp32_block_tol((n + 1) // slabs, n * n) * scale
+
+
+@pytest.mark.parametrize("n,slabs", [(15, 4), (127, 64), (255, 128), (511, 128), (511, 256)])
+def test_krylov_passes_at_each_width(n, slabs):
+    """GMRES over bases of 45 entries (less than one chunk) to 130305: one, two
+    and four entries per lane, with ragged last chunks.  The estimate of the
+    rotations holds for the true residual as long as the basis is orthonormal."""
+    print(f"\n[gpu] Krylov passes n={n} slabs={slabs}", flush=True)
+    mod = ddst()
+    op = mod.Operator(2, n, slabs, bvec=(4.0, 1.0, 0.0), precision="fp64")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    v = torch.randn(op.n_ds * op.M, generator=g, device="cuda", dtype=torch.float64)
+    x, iters, relres = op.gmres(v, tol=1e-10, max_iter=2000)
+    r = v - op.apply(x).reshape(-1)
+    assert iters < 2000
+    assert float(r.norm() / v.norm()) <= 1e-9
+    op.close()
