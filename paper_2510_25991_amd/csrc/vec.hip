@@ -501,10 +501,12 @@ __global__ void k_fill(double *__restrict__ y, double v, size_t len) {
 // V: vectors of len entries, `stride` apart, 10 to 1000 of them, len 10^3 to
 // 10^6.  What bounds them is the loads in flight: a work-group takes a chunk of
 // 64 T entries (T per lane) and its 16 wavefronts share the vectors, eight at
-// a time with their loads issued together, so that a short basis of many
-// vectors still fills the chip (chunks of 256 entries with one thread each
-// for all vectors, and of 2048 with 32 vectors per work-group: 1.1 TB/s).
-// T = 1, 2, 4, the largest that leaves a chunk per CU (kDotChunks).
+// a time with their loads issued together, so that short vectors still fill
+// the chip.  A classical step's passes over FP32 bases of 15841 entries and
+// about 240 vectors take 4.6 us each; with 256 entries per work-group and
+// every vector in turn, by one thread an entry (updates) or by four
+// wavefronts (products), they took 15 and 19.  T = 1, 2, 4, the largest that
+// leaves a chunk per CU (kDotChunks).
 // Sums are FP64, in a fixed order.
 constexpr int kDotWaves = 16;  // wavefronts per work-group
 constexpr int kDotVecs = 8;    // basis vectors per wavefront and round
@@ -869,8 +871,9 @@ __global__ __launch_bounds__(256) void k_norm_scale_givens(const double *__restr
 // kLagChunk-entry chunk: part[chunk][i] = V_i . u, part[chunk][m + i] =
 // V_i . w (i < m - 1), part[chunk][m - 1] = u . u, part[chunk][2 m - 1] =
 // u . w.  Work-group (chunk, g): vectors g kDotRound .., eight per wavefront;
-// group 0 also forms the products of u.  500 FP64 vectors of 15345: 54 us
-// with chunks of 2048 and 32 vectors per work-group (128 of them).
+// group 0 also forms the products of u.  FP64 bases of 64449 entries, 500
+// vectors on average: 47 us, 5.4 TB/s (54 with chunks of 2048 and 32 vectors
+// per work-group).
 constexpr int kLagChunk = 256;
 template <typename B>
 __global__ __launch_bounds__(64 * kDotWaves) void k_lag_dots(const B *__restrict__ V, size_t stride,
@@ -1003,8 +1006,8 @@ __global__ __launch_bounds__(256) void k_lag_coef(GmresDev d, int k) {
 // Pass B, per chunk of 64 T entries: q_k = (u - Q a) / nu into slot k of V, w =
 // w / nu - Q f - g u, and the chunk's partial squared norm of the new w.
 // u may be slot k itself (an FP64 basis): each entry is read before it is
-// overwritten, by the same thread.  500 FP64 vectors of 15345: 50 us with one
-// thread an entry for all vectors.
+// overwritten, by the same thread.  As above: 44 us, 5.8 TB/s (50 with one
+// thread an entry for all vectors).
 template <typename B, int T>
 __global__ __launch_bounds__(64 * kDotWaves) void k_lag_update(B *V, size_t stride, int k,
                                                                const double *u,
