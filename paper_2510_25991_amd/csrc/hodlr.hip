@@ -61,7 +61,7 @@ struct Hodlr {
   size_t off_leaf[2] = {0, 0};
   int n_leaf[2] = {0, 0};
   size_t off_con = 0;        // byte offset of the Contrib table in `jobs`
-  // fused product (k_hodlr_apply_fused): one job per (interface, leaf
+  // fused product (k_hodlr_apply, _t): one job per (interface, leaf
   // cluster) holding every contribution to its rows, per direction
   void *fjobs = nullptr;
   size_t foff_con = 0;       // byte offset of the FContrib table in `fjobs`
@@ -731,40 +731,133 @@ __global__ void k_pack_leaf(const LeafJob *__restrict__ jobs, const int *__restr
 }
 
 // ------------------------------------------------------------------- apply
-// Eight consecutive factors (16-byte aligned) as accumulation values.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename F, typename Acc>
-__device__ __forceinline__ void load8f(const F *p, Acc (&v)[8]) {
-  if constexpr (sizeof(F) == 2) {
-    const u32x4 q = *reinterpret_cast<const __attribute__((address_space(1))) u32x4 *>(gp(p));
-    const unsigned w[4] = {q[0], q[1], q[2], q[3]};
+// Dot product of n consecutive factors from p (any alignment of F) with the
+// entries get(c), over the LANES lanes of a group, l this lane's number in it:
+// the lane's part of the sum, eight factors at a time.
+template <int LANES, typename Acc, typename F, typename G>
+__device__ __forceinline__ Acc row_part(const F *p, int n, int l, G get) {
+  typedef F vec __attribute__((ext_vector_type(8), aligned(sizeof(F))));
+  Acc acc = 0;
+  for (int c = 8 * l; c < n; c += 8 * LANES) {
+    if (c + 8 <= n) {
+      const vec v = *reinterpret_cast<const __attribute__((address_space(1))) vec *>(gp(p + c));
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[2 * e] = (Acc)__uint_as_float(w[e] << 16);
-      v[2 * e + 1] = (Acc)__uint_as_float(w[e] & 0xffff0000u);
+      for (int e = 0; e < 8; ++e) acc += (Acc)FactorIO<F>::get(v[e]) * get(c + e);
+    } else {
+      for (int e = c; e < n; ++e) acc += (Acc)FactorIO<F>::get(gp(p)[e]) * get(e);
     }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (Acc)FactorIO<F>::get(p[e]);
   }
+  return acc;
 }
 
-// y = x - S x (or x - S^T x) over the rows of one leaf cluster of one
-// interface per work-group, in one launch: the identity part, the dense
-// leaves of both neighbouring transfer blocks, and at every tree level the
-// low-rank blocks whose row cluster contains these rows (their t = V^T x
-// formed by each leaf work-group again: a few thousand entries).  Rows of a
-// work-group are disjoint from every other's, so there are no write races;
-// the last cluster of an interface also copies the padding (rows >= M).
+// y = x - S x over the rows of one leaf cluster of one interface per
+// work-group, in one launch: the identity part, the dense leaves of both
+// neighbouring transfer blocks, and at every tree level the low-rank blocks
+// whose row cluster contains these rows (their t = V^T x formed by each leaf
+// work-group again: a few thousand entries).  Rows of a work-group are
+// disjoint from every other's, so there are no write races; the last cluster
+// of an interface also copies the padding (rows >= M).
+//
+// What bounds it is latency: some ten blocks of a few tens of columns each,
+// read in one go they are 80 MB at 63 interfaces of 1023.  So the t of as many
+// blocks as fit are formed side by side (16 lanes an entry, the entries of
+// all blocks dealt to the 16 wavefronts), then, after one barrier, the rows (8
+// lanes each) take every block's share.  Block after block with two barriers
+// each, four wavefronts and one thread per row took 40.3 us there, this 23.7.
+// XLDS: the x of the two neighbouring interfaces is kept in LDS (M <=
+// kApplyX).
+constexpr int kApplyX = 2048, kApplyT = 1024, kApplyWaves = 16;
+template <typename F, bool XLDS>
+__global__ __launch_bounds__(64 * kApplyWaves) void k_hodlr_apply(
+    const LrJob *__restrict__ jobs, const FContrib *__restrict__ con, const F *__restrict__ store,
+    const double *__restrict__ x, double *__restrict__ y, int ld, int M, int n_ifc) {
+  using Acc = typename std::conditional<std::is_same<F, double>::value, double, float>::type;
+  __shared__ Acc t[kApplyT];
+  __shared__ Acc xs[XLDS ? 2 * kApplyX : 1];
+  const LrJob J = jobs[blockIdx.x];
+  const int rows = J.r1 - J.r0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double *xo = x + (size_t)J.out_iface * ld;
+  double *yo = y + (size_t)J.out_iface * ld;
+  if (J.r1 == M)
+    for (int r = M + tid; r < ld; r += 64 * kApplyWaves) yo[r] = xo[r];
+  if constexpr (XLDS) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      const int in = J.out_iface - 1 + 2 * side;
+      if (in >= 0 && in < n_ifc)
+        for (int c = tid; c < M; c += 64 * kApplyWaves)
+          xs[side * kApplyX + c] = (Acc)x[(size_t)in * ld + c];
+    }
+    __syncthreads();
+  }
+  // entry c of the block's input
+  auto input = [&](const FContrib &C) {
+    if constexpr (XLDS) {
+      const Acc *p = xs + (C.in_iface > J.out_iface ? kApplyX : 0) + C.c0;
+      return [p](int c) { return p[c]; };
+    } else {
+      const double *p = x + (size_t)C.in_iface * ld + C.c0;
+      return [p](int c) { return (Acc)p[c]; };
+    }
+  };
+  int b0 = 0;
+  do {
+    // blocks [b0, b1): as many as t holds (ranks are at most 128)
+    int b1 = b0, nt = 0, dealt = 0;
+    for (; b1 < J.count; ++b1) {
+      const FContrib C = con[J.first + b1];
+      if (C.rank < 0) continue;
+      if (nt + C.rank > kApplyT) break;
+      const F *v = store + C.off_v;
+      const int ncol = C.c1 - C.c0, ng = (C.rank + 3) / 4;
+      const auto xin = input(C);
+      for (int g = (wave - dealt) & (kApplyWaves - 1); g < ng; g += kApplyWaves) {
+        const int k = 4 * g + (lane >> 4);
+        Acc acc = 0;
+        if (k < C.rank) acc = row_part<16, Acc>(v + (size_t)k * ncol, ncol, lane & 15, xin);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) acc += __shfl_down(acc, off, 16);
+        if ((lane & 15) == 0 && k < C.rank) t[nt + k] = acc;
+      }
+      nt += C.rank;
+      dealt += ng;
+    }
+    __syncthreads();
+    for (int r = tid >> 3; r < rows; r += 8 * kApplyWaves) {
+      double sum = 0.0;
+      int at = 0;
+      for (int ci = b0; ci < b1; ++ci) {
+        const FContrib C = con[J.first + ci];
+        if (C.rank < 0) {  // dense square leaf, row stride lds
+          sum += (double)row_part<8, Acc>(store + C.off_u + (size_t)r * C.lds, C.c1 - C.c0,
+                                          lane & 7, input(C));
+        } else {
+          const Acc *tc = t + at;
+          sum += (double)row_part<8, Acc>(store + C.off_u + (size_t)(C.roff + r) * C.rank, C.rank,
+                                          lane & 7, [tc](int c) { return tc[c]; });
+          at += C.rank;
+        }
+      }
+#pragma unroll
+      for (int off = 4; off > 0; off >>= 1) sum += __shfl_down(sum, off, 8);
+      if ((lane & 7) == 0) yo[J.r0 + r] = (b0 == 0 ? xo[J.r0 + r] : yo[J.r0 + r]) - sum;
+    }
+    b0 = b1;
+    if (b0 < J.count) __syncthreads();  // t is written again
+  } while (b0 < J.count);
+}
+
+// The transposed product y = x - S^T x, block after block.
 template <typename F>
-__global__ __launch_bounds__(256) void k_hodlr_apply_fused(const LrJob *__restrict__ jobs,
+__global__ __launch_bounds__(256) void k_hodlr_apply_t(const LrJob *__restrict__ jobs,
                                                            const FContrib *__restrict__ con,
                                                            const F *__restrict__ store,
                                                            const double *__restrict__ x,
                                                            double *__restrict__ y, int ld, int M) {
   using Acc = typename std::conditional<std::is_same<F, double>::value, double, float>::type;
   __shared__ Acc t[128];
-  __shared__ Acc xs[128];
   const LrJob J = jobs[blockIdx.x];
   const int rows = J.r1 - J.r0;
   const double *xo = x + (size_t)J.out_iface * ld;
@@ -778,55 +871,25 @@ __global__ __launch_bounds__(256) void k_hodlr_apply_fused(const LrJob *__restri
     const FContrib C = con[J.first + ci];
     const double *xin = x + (size_t)C.in_iface * ld + C.c0;
     const int ncol = C.c1 - C.c0;
-    if (C.rank < 0) {  // dense square leaf, row stride lds (padding zero)
+    if (C.rank < 0) {  // dense square leaf, row stride lds
       const F *Lf = store + C.off_u;
-      if (!C.trans) {
-        // 16 lanes per row with 8 columns each (one 16-byte load of BF16),
-        // four rows per wavefront at a time; x staged per 128 columns
-        const int sub = lane >> 4, l16 = lane & 15;
-        for (int cb = 0; cb < ncol; cb += 128) {
-          const int cw = min(128, ncol - cb);
-          __syncthreads();
-          for (int c = threadIdx.x; c < 128; c += 256) xs[c] = c < cw ? (Acc)xin[cb + c] : Acc(0);
-          __syncthreads();
-          for (int r0 = 4 * wave; r0 < rows; r0 += 16) {
-            const int r = r0 + sub;
-            Acc acc = 0;
-            if (r < rows && 8 * l16 < cw) {
-              Acc v[8];
-              load8f<F, Acc>(Lf + (size_t)r * C.lds + cb + 8 * l16, v);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) acc += v[e] * xs[8 * l16 + e];
-            }
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) acc += __shfl_down(acc, off, 16);
-            if (l16 == 0 && r < rows) yo[r] -= (double)acc;
-          }
-        }
-      } else {
-        // one thread per row: column c of the leaf is contiguous over rows
-        for (int r = threadIdx.x; r < rows; r += 256) {
-          Acc acc = 0;
-          for (int c = 0; c < ncol; ++c)
-            acc += (Acc)FactorIO<F>::get(Lf[(size_t)c * C.lds + r]) * (Acc)xin[c];
-          yo[r] -= (double)acc;
-        }
+      // one thread per row: column c of the leaf is contiguous over rows
+      for (int r = threadIdx.x; r < rows; r += 256) {
+        Acc acc = 0;
+        for (int c = 0; c < ncol; ++c)
+          acc += (Acc)FactorIO<F>::get(Lf[(size_t)c * C.lds + r]) * (Acc)xin[c];
+        yo[r] -= (double)acc;
       }
       __syncthreads();
       continue;
     }
     const int rk = C.rank;
-    // t = V^T x (or U^T x for the transpose): one wavefront per entry of t
+    // t = U^T x: one wavefront per entry of t
     for (int k = wave; k < rk; k += 4) {
       Acc acc = 0;
-      if (!C.trans) {
-        const F *v = store + C.off_v + (size_t)k * ncol;
-        for (int c = lane; c < ncol; c += 64) acc += (Acc)FactorIO<F>::get(v[c]) * (Acc)xin[c];
-      } else {
-        const F *u = store + C.off_u;
-        for (int c = lane; c < ncol; c += 64)
-          acc += (Acc)FactorIO<F>::get(u[(size_t)c * rk + k]) * (Acc)xin[c];
-      }
+      const F *u = store + C.off_u;
+      for (int c = lane; c < ncol; c += 64)
+        acc += (Acc)FactorIO<F>::get(u[(size_t)c * rk + k]) * (Acc)xin[c];
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
       if (lane == 0) t[k] = acc;
@@ -836,14 +899,9 @@ __global__ __launch_bounds__(256) void k_hodlr_apply_fused(const LrJob *__restri
     for (int r = threadIdx.x; r < rows; r += 256) {
       Acc acc = 0;
       const int rr = C.roff + r;
-      if (!C.trans) {
-        const F *u = store + C.off_u + (size_t)rr * rk;
-        for (int k = 0; k < rk; ++k) acc += (Acc)FactorIO<F>::get(u[k]) * t[k];
-      } else {
-        const F *v = store + C.off_v;
-        for (int k = 0; k < rk; ++k)
-          acc += (Acc)FactorIO<F>::get(v[(size_t)k * C.rfull + rr]) * t[k];
-      }
+      const F *v = store + C.off_v;
+      for (int k = 0; k < rk; ++k)
+        acc += (Acc)FactorIO<F>::get(v[(size_t)k * C.rfull + rr]) * t[k];
       yo[r] -= (double)acc;
     }
     __syncthreads();
@@ -1517,19 +1575,20 @@ int hodlr_apply_jobs(const ddst_op *op, const double *x, double *y, int transpos
     const LrJob *fj = static_cast<const LrJob *>(H->fjobs) + H->foff[dir];
     const FContrib *fc = reinterpret_cast<const FContrib *>(
         static_cast<const unsigned char *>(H->fjobs) + H->foff_con);
+    auto product = [&](auto *factors) {
+      using F = std::remove_const_t<std::remove_pointer_t<decltype(factors)>>;
+      if (transpose)
+        hipLaunchKernelGGL(k_hodlr_apply_t<F>, dim3(nj), dim3(256), 0, s, fj, fc, factors, xi, yp,
+                           op->ld, op->M);
+      else
+        hipLaunchKernelGGL((op->M <= kApplyX ? k_hodlr_apply<F, true> : k_hodlr_apply<F, false>),
+                           dim3(nj), dim3(64 * kApplyWaves), 0, s, fj, fc, factors, xi, yp, op->ld,
+                           op->M, op->n_ds);
+    };
     switch (H->dtype) {
-      case DDST_FACTOR_BF16:
-        hipLaunchKernelGGL(k_hodlr_apply_fused<unsigned short>, dim3(nj), dim3(256), 0, s, fj, fc,
-                           static_cast<const unsigned short *>(H->factors), xi, yp, op->ld,
-                           op->M);
-        break;
-      case DDST_FACTOR_FP32:
-        hipLaunchKernelGGL(k_hodlr_apply_fused<float>, dim3(nj), dim3(256), 0, s, fj, fc,
-                           static_cast<const float *>(H->factors), xi, yp, op->ld, op->M);
-        break;
-      default:
-        hipLaunchKernelGGL(k_hodlr_apply_fused<double>, dim3(nj), dim3(256), 0, s, fj, fc,
-                           static_cast<const double *>(H->factors), xi, yp, op->ld, op->M);
+      case DDST_FACTOR_BF16: product(static_cast<const unsigned short *>(H->factors)); break;
+      case DDST_FACTOR_FP32: product(static_cast<const float *>(H->factors)); break;
+      default: product(static_cast<const double *>(H->factors));
     }
   }
   prof_end(KK_GEMV, s, (double)H->bytes);

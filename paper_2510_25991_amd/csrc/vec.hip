@@ -1039,12 +1039,16 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_lag_update(B *V, size_t stri
 }
 
 // rho = |w| (every work-group sums the partials in the same order; the
-// first stores it), vnext = w / rho, and work-group 0 rotates column
-// givens_col of H (< 0: none) from Hraw, beside the others' scaling.
+// first stores it), vnext = w / rho; beside them the last work-group rotates
+// column givens_col of H (< 0: none) from Hraw.
 __global__ __launch_bounds__(256) void k_lag_norm_scale(const double *__restrict__ part, int nchunk,
                                                         const double *__restrict__ w,
                                                         double *__restrict__ vnext, size_t len,
                                                         GmresDev d, int givens_col, double beta) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (givens_col >= 0) gmres_givens_raw(d, givens_col, beta);
+    return;
+  }
   __shared__ double sh[4], snorm;
   double s = 0.0;
   for (int c = threadIdx.x; c < nchunk; c += 256) s += part[c];
@@ -1057,7 +1061,6 @@ __global__ __launch_bounds__(256) void k_lag_norm_scale(const double *__restrict
   const double r = snorm;
   const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < len) vnext[e] = (r > 0.0) ? w[e] / r : 0.0;
-  if (blockIdx.x == 0 && givens_col >= 0) gmres_givens_raw(d, givens_col, beta);
 }
 
 // One work-group per vector sums its partials (strided, then a tree).
@@ -1350,7 +1353,7 @@ void launch_arnoldi_lagged(B *V, size_t stride, int k, const double *u, double *
     hipLaunchKernelGGL((k_lag_update<B, T>), dim3(nblk(len, 64 * T)), dim3(64 * kDotWaves), 0, s, V,
                        stride, k, u, w, len, gd, part);
   });
-  hipLaunchKernelGGL(k_lag_norm_scale, dim3(nblk(len)), dim3(256), 0, s, (const double *)part,
+  hipLaunchKernelGGL(k_lag_norm_scale, dim3(nblk(len) + 1), dim3(256), 0, s, (const double *)part,
                      (int)dot_chunks(len), (const double *)w, unext, len, gd, gcol, beta);
 }
 template void launch_arnoldi_lagged<double>(double *, size_t, int, const double *, double *,

@@ -88,3 +88,23 @@ def test_krylov_passes_at_each_width(n, slabs):
     assert iters < 2000
     assert float(r.norm() / v.norm()) <= 1e-9
     op.close()
+
+
+@pytest.mark.parametrize("n,slabs,leaf,levels", [(299, 10, 32, 4), (511, 128, 128, 2),
+                                                 (2303, 8, 128, 5)])
+@pytest.mark.parametrize("factors", ["fp64", "fp32"])
+def test_compressed_product(n, slabs, leaf, levels, factors):
+    """y = S x through the compressed blocks, rows that begin at any alignment
+    and planes that do and do not fit LDS; the bound of the compressed operator
+    (4 levels tol), FP32 factors adding their rounding."""
+    print(f"\n[gpu] compressed product n={n} leaf={leaf} {factors}", flush=True)
+    tol = 1e-8 if factors == "fp64" else 1e-6
+    op = ddst().Operator(2, n, slabs, bvec=(3.0, 1.0, 0.0), precision="fp64")
+    op.compress(tol=tol, leaf=leaf, oversample=10, max_rank=100, factor_dtype=factors)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(op.n_ds * op.M, generator=g, device="cuda", dtype=torch.float64)
+    for transpose in (False, True):
+        y = op.apply(x, which="hodlr", transpose=transpose).reshape(-1)
+        ref = op.apply(x, transpose=transpose).reshape(-1)
+        assert float((y - ref).norm() / x.norm()) <= 4 * levels * tol
+    op.close()
