@@ -27,7 +27,7 @@ struct Hodlr;
 constexpr int kTile = 128;   // GEMM / update output tile (rows and cols)
 constexpr int kNB = 128;     // Gauss-Jordan block width (= kTile)
 constexpr int kMaxGmresIter = 20000;  // unrestarted GMRES: basis kept in HBM
-constexpr int kGemvChunk = 32;  // rows per partial sum in the transposed GEMV
+constexpr int kGemvChunk = 32;  // workspace of the transposed GEMV: one sum per so many rows
 
 // Stencil coefficient slots: coef[slot * N + node], node = interior C-order.
 // slot 0: diagonal; slot 1+2a: neighbour p - e_a; slot 2+2a: neighbour p + e_a.

@@ -176,11 +176,6 @@ __global__ void k_unpad(const double *__restrict__ src, double *__restrict__ dst
   dst[e] = src[row * ld + c];
 }
 
-// rows per wavefront of the GEMV (8 FP32 rows would take all 256 registers:
-// the conversions to FP64 are scheduled early)
-template <typename T> constexpr int gemv_rpw() { return 4; }
-constexpr int kGemvCh = 1024;
-
 // four consecutive matrix entries as doubles (global-memory vector loads)
 template <typename T>
 __device__ __forceinline__ void ld4(const T *p, double *o) {
@@ -193,22 +188,26 @@ __device__ __forceinline__ void ld4(const T *p, double *o) {
   }
 }
 
-// out[r] = w[r] + alpha * (G[r,:] (x1 - e.*x2) + G2[r,:] x3); 4 R rows per block.
-// HBM-bound: each wavefront owns R rows and, per chunk of
-// kGemvCh columns, issues all its 16-byte loads of a matrix before using
-// any (4 R per matrix and chunk in flight per wavefront; no branches between
-// them: columns past the chunk re-read an in-bounds address and meet x = 0);
-// the first matrix's loads are issued before x is staged in LDS, which they
-// do not depend on.
-template <typename T, int R>
-__device__ __forceinline__ void gemv_rows_load(const T *M, size_t row0_off, int ld, int c0,
-                                               int cn, int lane, T (&g)[R][kGemvCh / 256][4]) {
+// out[r] = w[r] + alpha * (G[r,:] (x1 - e.*x2) + G2[r,:] x3); kGemvRows rows per
+// work-group.  HBM-bound: each wavefront owns kGemvR rows and takes kGemvCh
+// columns of a matrix at a time, all its 16-byte loads before using any (no
+// branches between them: columns past the chunk re-read an in-bounds address
+// and meet x = 0); the first loads are issued before x, staged in LDS kGemvX
+// columns at a time, which they do not depend on.  Rows and columns that are padding are not read.
+// Two rows and 512 columns: little per wavefront, but six and more wavefronts
+// per SIMD, whose number evens out the last round of work-groups.  Planes of a
+// sweep over 1023^2 on 32 slabs, 134 MB: 33 us with four rows and 1024
+// columns, 28 with these (with one row 32, with eight 34); FP64 79 and 63.
+constexpr int kGemvR = 2, kGemvRows = 4 * kGemvR, kGemvCh = 512, kGemvX = 1024;
+template <typename T>
+__device__ __forceinline__ void gemv_rows_load(const T *M, int ld, int cn, int lane,
+                                               T (&g)[kGemvR][kGemvCh / 256][4]) {
 #pragma unroll
-  for (int q = 0; q < R; ++q)
+  for (int q = 0; q < kGemvR; ++q)
 #pragma unroll
     for (int i = 0; i < kGemvCh / 256; ++i) {
       const int c = lane * 4 + 256 * i;
-      const T *src = M + row0_off + (size_t)q * ld + c0 + (c < cn ? c : 0);
+      const T *src = M + (size_t)q * ld + (c < cn ? c : 0);
       constexpr int V = 16 / sizeof(T);
 #pragma unroll
       for (int h = 0; h < 4 / V; ++h) {
@@ -219,73 +218,80 @@ __device__ __forceinline__ void gemv_rows_load(const T *M, size_t row0_off, int 
     }
 }
 // x: kGemvCh doubles in LDS, zero past the chunk
-template <typename T, int R>
-__device__ __forceinline__ void gemv_rows_fma(const T (&g)[R][kGemvCh / 256][4],
-                                              const double *x, int lane, double (&acc)[R]) {
+template <typename T>
+__device__ __forceinline__ void gemv_rows_fma(const T (&g)[kGemvR][kGemvCh / 256][4],
+                                              const double *x, int lane, double (&acc)[kGemvR]) {
 #pragma unroll
   for (int i = 0; i < kGemvCh / 256; ++i) {
     const int c = lane * 4 + 256 * i;
     const double x0 = x[c], x1 = x[c + 1], x2 = x[c + 2], x3 = x[c + 3];
 #pragma unroll
-    for (int q = 0; q < R; ++q)
+    for (int q = 0; q < kGemvR; ++q)
       acc[q] += (double)g[q][i][0] * x0 + (double)g[q][i][1] * x1 +
                 (double)g[q][i][2] * x2 + (double)g[q][i][3] * x3;
   }
 }
 
 template <typename T>
-__device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, int ld,
+__device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, int ld, int M,
                                             double alpha) {
-  constexpr int R = gemv_rpw<T>();
-  __shared__ double xs[kGemvCh];
-  __shared__ double x3s[kGemvCh];
+  __shared__ double xs[2][kGemvX];
   const GemvJob J = jobs[blockIdx.y];
   const T *G = static_cast<const T *>(J.G);
   const T *G2 = static_cast<const T *>(J.G2);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row0 = blockIdx.x * (4 * R) + wave * R;
+  const int row0 = blockIdx.x * kGemvRows + wave * kGemvR;
   const size_t ro = (size_t)row0 * ld;
-  if (!G && !G2) {  // no matrix term (an end of a sweep): out = w
-    if (lane < R) {
+  if ((!G && !G2) || (int)blockIdx.x * kGemvRows >= M) {
+    // no matrix term (an end of a sweep, or padding): out = w
+    if (lane < kGemvR) {
       const int r = row0 + lane;
       gp(J.out)[r] = J.w ? gp(J.w)[r] : 0.0;
     }
     return;
   }
-  double acc[R];
+  double acc[kGemvR];
 #pragma unroll
-  for (int q = 0; q < R; ++q) acc[q] = 0.0;
-  T g[R][kGemvCh / 256][4];
-  for (int c0 = 0; c0 < ld; c0 += kGemvCh) {
-    const int cn = min(kGemvCh, ld - c0);
-    gemv_rows_load<T, R>(G ? G : G2, ro, ld, c0, cn, lane, g);
-    if (c0 > 0) __syncthreads();  // the previous chunk's x is no longer read
-    for (int c = threadIdx.x; c < kGemvCh; c += 256) {
+  for (int q = 0; q < kGemvR; ++q) acc[q] = 0.0;
+  // step t: chunk t of the first matrix, or, with two, chunk t / 2 of either
+  const int two = G && G2 ? 1 : 0;
+  const T *first = G ? G : G2;
+  const int mc = min(ld, (M + 3) & ~3);  // whole 16-byte loads
+  const int x0 = G ? 0 : 1;              // the first matrix's entries
+  T g[kGemvR][kGemvCh / 256][4];
+  for (int c0 = 0; c0 < mc; c0 += kGemvX) {
+    const int xn = min(kGemvX, mc - c0);
+    const int steps = (xn + kGemvCh - 1) / kGemvCh << two;
+    auto load = [&](int t) {
+      const int c = (t >> two) * kGemvCh;
+      gemv_rows_load<T>((t & two ? G2 : first) + ro + c0 + c, ld, xn - c, lane, g);
+    };
+    auto use = [&](int t) {
+      gemv_rows_fma<T>(g, xs[t & two ? 1 : x0] + (t >> two) * kGemvCh, lane, acc);
+    };
+    load(0);
+    if (c0 > 0) __syncthreads();  // the previous columns' x is no longer read
+    for (int c = threadIdx.x; c < kGemvX; c += 256) {
       double v = 0.0, v3 = 0.0;
-      if (c < cn) {
+      if (c < xn) {
         v = J.x1 ? gp(J.x1)[c0 + c] : 0.0;
         if (J.e) v -= gp(J.e)[c0 + c] * gp(J.x2)[c0 + c];
         v3 = (G2 && J.x3) ? gp(J.x3)[c0 + c] : 0.0;
       }
-      xs[c] = v;
-      x3s[c] = v3;
+      xs[0][c] = v;
+      xs[1][c] = v3;
     }
     __syncthreads();
-    if (G) {
-      gemv_rows_fma<T, R>(g, xs, lane, acc);
-      if (G2) {
-        // keep the second matrix's loads after the first one's products
-        // (hoisting them doubles the live registers)
-        asm volatile("" ::: "memory");
-        gemv_rows_load<T, R>(G2, ro, ld, c0, cn, lane, g);
-        gemv_rows_fma<T, R>(g, x3s, lane, acc);
-      }
-    } else {
-      gemv_rows_fma<T, R>(g, x3s, lane, acc);
+    use(0);
+    for (int t = 1; t < steps; ++t) {
+      // not earlier: more registers, fewer wavefronts
+      asm volatile("" ::: "memory");
+      load(t);
+      use(t);
     }
   }
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
+  for (int q = 0; q < kGemvR; ++q) {
     const double s = wave_sum(acc[q]);
     if (lane == 0) {
       const int r = row0 + q;
@@ -294,16 +300,13 @@ __device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, in
   }
 }
 
-// FP32 matrices: capped at 3 wavefronts' registers per SIMD (138 VGPRs, no
-// spills) for more loads in flight per CU; FP64 keeps the compiler's choice
-// (a cap spills).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gemv_n_f32(
-    const GemvJob *__restrict__ jobs, int ld, double alpha) {
-  gemv_n_body<float>(jobs, ld, alpha);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_gemv_n_f32(
+    const GemvJob *__restrict__ jobs, int ld, int M, double alpha) {
+  gemv_n_body<float>(jobs, ld, M, alpha);
 }
 __global__ __launch_bounds__(256) void k_gemv_n_f64(const GemvJob *__restrict__ jobs, int ld,
-                                                    double alpha) {
-  gemv_n_body<double>(jobs, ld, alpha);
+                                                    int M, double alpha) {
+  gemv_n_body<double>(jobs, ld, M, alpha);
 }
 
 // Several right-hand sides per launch, on the matrix cores: vector v of a job
@@ -317,13 +320,13 @@ __global__ __launch_bounds__(256) void k_gemv_n_f64(const GemvJob *__restrict__ 
 // the A operand of four MFMAs, the i-th taking columns {4 q + i}; the B
 // operand is the matching entries of the 16 vectors, staged column-major in
 // LDS per chunk of columns (zero for vectors past nv); the next chunk's
-// matrix entries are loaded while a chunk is used.  The FP64 output holds
+// matrix entries and vectors are loaded while a chunk is used.  The FP64 output holds
 // vector l % 16 of rows 4 r + l / 16 in register r.
 typedef double f64x4v __attribute__((ext_vector_type(4)));
 constexpr int kMvLd = 17;  // LDS row stride (doubles) of the staged block
 // columns staged per chunk: a divisor of every leading dimension (a multiple
 // of 128)
-constexpr int kMvCh = 128;
+constexpr int kMvCh = 64;
 
 template <typename T, int NS>
 __device__ __forceinline__ void mv_load(const T *Mt, size_t row_off, int c0, int kq,
@@ -341,23 +344,30 @@ __device__ __forceinline__ void mv_load(const T *Mt, size_t row_off, int c0, int
   }
 }
 
-// W wavefronts (16-row strips) per work-group: 8 share each staged block of
-// x over 128 rows (fewer staging loads per row, better from 8 vectors on),
-// 4 give twice the work-groups (better for 2 to 4 vectors).
-template <typename T, int W>
-__global__ __launch_bounds__(64 * W) void k_gemv_mfma(const GemvJob *__restrict__ jobs, int ld,
-                                                      double alpha, int nv, size_t vs) {
-  constexpr int CH = kMvCh, NS = CH / 16, RB = 16 * W;
-  __shared__ double xt[CH * kMvLd];
+// W strips of 16 rows per work-group: 8 share each staged block of x over 128
+// rows (fewer staging loads per row, better from 8 vectors on), 4 give twice
+// the work-groups (better for 2 to 4 vectors).  The chunks are dealt to H = 2
+// sets of W wavefronts, whose sums are added at the end: a sweep over 32 FP32
+// planes of 1024 rows would be 8 wavefronts per CU with one set, too few
+// loads in flight.  That sweep and the interface products, on average: 44 us
+// with 8 vectors, 40 with 3 (one set, chunks of 128 with x loaded between two
+// barriers: 54 and 48).
+template <typename T, int W, int H>
+__global__ __launch_bounds__(64 * W * H) void k_gemv_mfma(const GemvJob *__restrict__ jobs, int ld,
+                                                          double alpha, int nv, size_t vs) {
+  constexpr int CH = kMvCh, NS = CH / 16, RB = 16 * W, NX = 16 * CH / (64 * W);
+  __shared__ double xt[2][H][CH * kMvLd];
+  static_assert((H - 1) * W * 64 * 4 <= 2 * H * CH * kMvLd, "the sums of the other sets fit");
   const GemvJob J = jobs[blockIdx.y];
   const T *G = static_cast<const T *>(J.G);
   const T *G2 = static_cast<const T *>(J.G2);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int strip = wave % W, set = wave / W, tid = threadIdx.x - set * 64 * W;
   const int m = lane & 15, kq = lane >> 4;
   const int rowb = blockIdx.x * RB;  // first row of the work-group
-  const int roww = rowb + wave * 16;  // first row of this wavefront's strip
+  const int roww = rowb + strip * 16;  // first row of this wavefront's strip
   if (!G && !G2) {  // no matrix term: out = w
-    for (int e = threadIdx.x; e < RB * nv; e += 64 * W) {
+    for (int e = threadIdx.x; e < RB * nv; e += 64 * W * H) {
       const size_t o = (size_t)(e / RB) * vs + rowb + e % RB;
       gp(J.out)[o] = J.w ? gp(J.w)[o] : 0.0;
     }
@@ -365,40 +375,70 @@ __global__ __launch_bounds__(64 * W) void k_gemv_mfma(const GemvJob *__restrict_
   }
   f64x4v acc = {0.0, 0.0, 0.0, 0.0};
   const size_t row_off = (size_t)(roww + m) * ld;
-#pragma unroll 1
-  for (int pass = 0; pass < 2; ++pass) {
-    const T *Mt = pass == 0 ? G : G2;
-    if (!Mt) continue;
-    const double *xa = pass == 0 ? J.x1 : J.x3;
-    const double *xe = pass == 0 ? J.e : nullptr;
-    T a[NS][4], an[NS][4];
-    mv_load<T, NS>(Mt, row_off, 0, kq, a);
-    for (int c0 = 0; c0 < ld; c0 += CH) {
-      // the next chunk's matrix entries go out before this chunk is used
-      if (c0 + CH < ld) mv_load<T, NS>(Mt, row_off, c0 + CH, kq, an);
-      __syncthreads();  // the previous block of x is no longer read
-      for (int idx = threadIdx.x; idx < 16 * CH; idx += 64 * W) {
-        const int v = idx / CH, c = idx % CH;
-        double x = 0.0;
-        if (v < nv) {
-          const size_t o = (size_t)v * vs + c0 + c;
-          x = xa ? gp(xa)[o] : 0.0;
-          if (xe) x -= gp(xe)[c0 + c] * gp(J.x2)[o];
-        }
-        xt[c * kMvLd + v] = x;
+  // chunks of the first matrix, then of the second; set h takes every H-th
+  const int nc = ld / CH, total = nc << (G && G2 ? 1 : 0), steps = (total + H - 1) / H;
+  T a[NS][4], an[NS][4];
+  double xr[NX];
+  auto load = [&](int t, T (&q)[NS][4]) {
+    const int ch = t * H + set;
+    if (ch >= total) return;
+    const bool one = G && ch < nc;
+    const int c0 = (ch < nc ? ch : ch - nc) * CH;
+    mv_load<T, NS>(one ? G : G2, row_off, c0, kq, q);
+    const double *xa = one ? J.x1 : J.x3, *xe = one ? J.e : nullptr;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int idx = tid + 64 * W * i, v = idx / CH, k = c0 + idx % CH;
+      double x = 0.0;
+      if (v < nv) {
+        const size_t o = (size_t)v * vs + k;
+        x = xa ? gp(xa)[o] : 0.0;
+        if (xe) x -= gp(xe)[k] * gp(J.x2)[o];
       }
-      __syncthreads();
+      xr[i] = x;
+    }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int idx = tid + 64 * W * i;
+      xt[buf][set][idx % CH * kMvLd + idx / CH] = xr[i];
+    }
+  };
+  load(0, a);
+  store(0);
+  __syncthreads();
+#pragma unroll 1
+  for (int t = 0; t < steps; ++t) {
+    if (t + 1 < steps) load(t + 1, an);
+    const double *xb = xt[t & 1][set];
+    if (t * H + set < total)
 #pragma unroll
       for (int st = 0; st < NS; ++st)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
-              (double)a[st][i], xt[(16 * st + 4 * kq + i) * kMvLd + m], acc, 0, 0, 0);
+              (double)a[st][i], xb[(16 * st + 4 * kq + i) * kMvLd + m], acc, 0, 0, 0);
+    if (t + 1 < steps) {
+      store((t + 1) & 1);
 #pragma unroll
       for (int st = 0; st < NS; ++st)
 #pragma unroll
         for (int i = 0; i < 4; ++i) a[st][i] = an[st][i];
     }
+    __syncthreads();
+  }
+  if constexpr (H > 1) {
+    double *red = &xt[0][0][0];
+    if (set > 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[(((set - 1) * W + strip) * 4 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    if (set > 0) return;
+#pragma unroll
+    for (int h = 0; h < H - 1; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += red[((h * W + strip) * 4 + r) * 64 + lane];
   }
   if (m < nv) {
 #pragma unroll
@@ -411,44 +451,61 @@ __global__ __launch_bounds__(64 * W) void k_gemv_mfma(const GemvJob *__restrict_
 
 // Transposed product, partial sums over row chunks:
 // part[(job*nchunk + chunk)*ld + c] = sum_{r in chunk} G[r,c] xe[r] + G2[r,c] x3[r]
+// Work-group (chunk, job, z): 256 columns, a quarter of the chunk's rows per
+// wavefront, eight rows' loads in flight; rows and columns of padding are not
+// read.  24 planes of 768 rows in FP32: 23 us and 8 for the reduction with
+// chunks of 32 rows and one row at a time over all columns.
 template <typename T>
 __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__ jobs, int ld,
-                                                     int rows_per_chunk,
+                                                     int M, int rows_per_chunk,
                                                      double *__restrict__ part) {
+  constexpr int U = 8;
+  __shared__ double red[4][256];
   extern __shared__ double sh[];
-  double *xs = sh;
-  double *x3s = sh + rows_per_chunk;
   const int chunk = blockIdx.x, job = blockIdx.y, nchunk = gridDim.x;
   const GemvJob J = jobs[job];
-  const T *G = static_cast<const T *>(J.G);
-  const T *G2 = static_cast<const T *>(J.G2);
-  const int r0 = chunk * rows_per_chunk;
-  for (int r = threadIdx.x; r < rows_per_chunk; r += 256) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = chunk * rows_per_chunk, rn = max(0, min(rows_per_chunk, M - r0));
+  const int c = blockIdx.z * 256 + lane * 4;
+  double *xs[2] = {sh, sh + rows_per_chunk};
+  for (int r = threadIdx.x; r < rn; r += 256) {
     double v = J.x1 ? gp(J.x1)[r0 + r] : 0.0;
     if (J.e) v -= gp(J.e)[r0 + r] * gp(J.x2)[r0 + r];
-    xs[r] = v;
-    x3s[r] = (G2 && J.x3) ? gp(J.x3)[r0 + r] : 0.0;
+    xs[0][r] = v;
+    xs[1][r] = (J.G2 && J.x3) ? gp(J.x3)[r0 + r] : 0.0;
   }
   __syncthreads();
-  for (int c = threadIdx.x * 4; c < ld; c += 1024) {
-    double s[4] = {0, 0, 0, 0};
-    for (int r = 0; r < rows_per_chunk; ++r) {
-      double gv[4];
-      const size_t o = (size_t)(r0 + r) * ld + c;
-      if (G) {
-        ld4<T>(G + o, gv);
-        const double xv = xs[r];
-        s[0] += gv[0] * xv; s[1] += gv[1] * xv; s[2] += gv[2] * xv; s[3] += gv[3] * xv;
+  double s[4] = {0, 0, 0, 0};
+  if (c < M)
+    for (int k = 0; k < 2; ++k) {
+      const T *G = static_cast<const T *>(k == 0 ? J.G : J.G2);
+      if (!G) continue;
+      G += (size_t)r0 * ld + c;
+      const double *x = xs[k];
+      int r = wave * U;
+      for (; r + U <= rn; r += 4 * U) {
+        double g[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) ld4<T>(G + (size_t)(r + u) * ld, g[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] += g[u][e] * x[r + u];
       }
-      if (G2) {
-        ld4<T>(G2 + o, gv);
-        const double xv = x3s[r];
-        s[0] += gv[0] * xv; s[1] += gv[1] * xv; s[2] += gv[2] * xv; s[3] += gv[3] * xv;
+      for (; r < rn; ++r) {  // the ragged last rows (of one wavefront)
+        double g[4];
+        ld4<T>(G + (size_t)r * ld, g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += g[e] * x[r];
       }
     }
-    double *po = part + ((size_t)job * nchunk + chunk) * ld + c;
-    po[0] = s[0]; po[1] = s[1]; po[2] = s[2]; po[3] = s[3];
-  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wave][lane * 4 + e] = s[e];
+  __syncthreads();
+  const int cc = blockIdx.z * 256 + threadIdx.x;
+  if (cc < ld)
+    part[((size_t)job * nchunk + chunk) * ld + cc] =
+        (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
 __global__ void k_gemv_t_reduce(const GemvJob *__restrict__ jobs, int ld, int nchunk,
@@ -1193,18 +1250,19 @@ void launch_unpad(const double *src, double *dst, int rows, int M, int ld, hipSt
 template <typename T>
 void launch_gemv(const GemvJob *jobs, int njobs, int ld, int M, int transpose, double alpha,
                  double *partial, hipStream_t s) {
-  (void)M;
   if (njobs <= 0) return;
   const ProfSpan ps = prof_open(KK_GEMV);
   if (!transpose) {
     auto kern = sizeof(T) == 4 ? k_gemv_n_f32 : k_gemv_n_f64;
-    hipExtLaunchKernelGGL(kern, dim3(ld / (4 * gemv_rpw<T>()), njobs), dim3(256), 0, s, ps.a,
-                          ps.b, 0, jobs, ld, alpha);
+    hipExtLaunchKernelGGL(kern, dim3(ld / kGemvRows, njobs), dim3(256), 0, s, ps.a, ps.b, 0, jobs,
+                          ld, M, alpha);
   } else {
-    const int nchunk = (ld / kGemvChunk <= 64) ? ld / kGemvChunk : 64;
+    const int nchunk = std::min(ld / 64, 64);  // 64 rows and more
     const int rpc = ld / nchunk;
-    hipExtLaunchKernelGGL(k_gemv_t_part<T>, dim3(nchunk, njobs), dim3(256),
-                          2 * rpc * sizeof(double), s, ps.a, nullptr, 0, jobs, ld, rpc, partial);
+    static_assert(kGemvChunk <= 64, "the partial sums fit the workspace");
+    hipExtLaunchKernelGGL(k_gemv_t_part<T>, dim3(nchunk, njobs, (ld + 255) / 256), dim3(256),
+                          2 * rpc * sizeof(double), s, ps.a, nullptr, 0, jobs, ld, M, rpc,
+                          partial);
     hipExtLaunchKernelGGL(k_gemv_t_reduce, dim3(nblk(ld), njobs), dim3(256), 0, s, nullptr, ps.b,
                           0, jobs, ld, nchunk, partial, alpha);
   }
@@ -1223,12 +1281,13 @@ void launch_gemv_many(const GemvJob *jobs, int njobs, int ld, int M, double alph
   if (nv > 16) throw std::invalid_argument("launch_gemv_many: more than 16 vectors");
   const ProfSpan ps = prof_open(KK_GEMV_MANY);
   // 64 or 128 rows per work-group (ld % 128 == 0: whole work-groups and chunks)
+  constexpr int H = 2;
   if (nv <= 4)
-    hipExtLaunchKernelGGL(k_gemv_mfma<T, 4>, dim3(ld / 64, njobs), dim3(256), 0, s, ps.a, ps.b,
-                          0, jobs, ld, alpha, nv, vs);
+    hipExtLaunchKernelGGL((k_gemv_mfma<T, 4, H>), dim3(ld / 64, njobs), dim3(256 * H), 0, s, ps.a,
+                          ps.b, 0, jobs, ld, alpha, nv, vs);
   else
-    hipExtLaunchKernelGGL(k_gemv_mfma<T, 8>, dim3(ld / 128, njobs), dim3(512), 0, s, ps.a, ps.b,
-                          0, jobs, ld, alpha, nv, vs);
+    hipExtLaunchKernelGGL((k_gemv_mfma<T, 8, H>), dim3(ld / 128, njobs), dim3(512 * H), 0, s, ps.a,
+                          ps.b, 0, jobs, ld, alpha, nv, vs);
   // one M x M matrix per job (interface jobs read two: a lower bound)
   prof_close(ps, KK_GEMV_MANY, (double)njobs * M * M * sizeof(T));
 }

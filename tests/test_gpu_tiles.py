@@ -108,3 +108,38 @@ def test_compressed_product(n, slabs, leaf, levels, factors):
         ref = op.apply(x, transpose=transpose).reshape(-1)
         assert float((y - ref).norm() / x.norm()) <= 4 * levels * tol
     op.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("dim,n,slabs", [(2, 5, 3), (2, 127, 8), (2, 331, 4), (2, 899, 10),
+                                         (2, 1151, 8), (3, 35, 6)])
+def test_block_products(dim, n, slabs, precision):
+    """y = S x, its transpose and 5 and 9 vectors at once, against the blocks
+    themselves: planes with and without padding, one chunk of columns and
+    several.  FP64 sums: 1e-12; with FP32 blocks too, their entries being the
+    same on both sides."""
+    print(f"\n[gpu] block products {dim}D n={n} {precision}", flush=True)
+    op = ddst().Operator(dim, n, slabs, bvec=(5.0, 1.0, 0.0), precision=precision)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    J, M = op.n_ds, op.M
+    x = torch.randn(J, M, generator=g, device="cuda", dtype=torch.float64)
+    S = [tuple(b.double() for b in op.transfer(j)) for j in range(1, J + 1)]
+    y, yt = x.clone(), x.clone()
+    for j in range(J):
+        if j > 0:
+            y[j] -= (S[j][0] * x[j - 1]).sum(1)
+            yt[j] -= (S[j - 1][1] * x[j - 1][:, None]).sum(0)
+        if j < J - 1:
+            y[j] -= (S[j][1] * x[j + 1]).sum(1)
+            yt[j] -= (S[j + 1][0] * x[j + 1][:, None]).sum(0)
+    for ref, transpose in ((y, False), (yt, True)):
+        out = op.apply(x.reshape(-1), transpose=transpose).reshape(J, M)
+        assert relerr(out, ref) <= 1e-12
+    for nrhs in (3, 9):
+        F = torch.randn((nrhs,) + (n,) * dim, generator=g, device="cuda", dtype=torch.float64)
+        opts = ddst().SolveOptions(tol=1e-10, max_iter=400)
+        U, _ = op.solve_many(F, opts=opts)
+        for v in (0, nrhs - 1):
+            u = op.solve(F[v], opts=opts)[0]
+            assert relerr(U[v].reshape(-1), u.reshape(-1)) <= 1e-8
+    op.close()
