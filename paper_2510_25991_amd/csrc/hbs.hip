@@ -538,29 +538,53 @@ __device__ __forceinline__ int pow2_ge(int n) {
   return p;
 }
 
+// Rows i0, i0 + G, i0 + 2 G, i0 + 3 G of A's 8-column chunk ch, loaded together
+// (rows past the last repeat it).
+template <typename F>
+__device__ __forceinline__ void load_rows4(const F *A, int lda, int rows, int i0, int G, int ch,
+                                           double (&a)[4][8]) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    load8(A + (size_t)min(i0 + u * G, rows - 1) * lda + 8 * ch, a[u]);
+}
+
+// t[u] += A[i0 + u G][...] v by the group of lp lanes, lane l of it with chunk l,
+// reduced across the group.
+template <typename F>
+__device__ __forceinline__ void dot_rows4(const F *A, int lda, int rows, int cols, int i0, int G,
+                                          int l, int lp, const double (&x)[8], double (&t)[4]) {
+  double a[4][8];
+  load_rows4(A, lda, rows, i0, G, min(l, ((cols + 7) >> 3) - 1), a);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    t[u] = 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (8 * l + e < cols) t[u] += a[u][e] * x[e];
+  }
+  for (int off = lp >> 1; off > 0; off >>= 1)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] += __shfl_xor(t[u], off);
+}
+
 // out[i] += sum_c A[i][c] v[c] (i < rows, c < cols; rows of A padded to lda,
-// a multiple of 8): a group of lp lanes per row, eight entries per lane and
-// load, the row's partial sums reduced across the group.  Called by all
-// threads with the same arguments.
+// a multiple of 8): a group of lp lanes per row, eight entries per lane, four
+// rows' loads in flight.  Called by all threads with the same arguments.
 template <typename F>
 __device__ __forceinline__ void mv_rows(const F *A, int lda, int rows, int cols, const double *v,
                                         double *out) {
-  const int nch = (cols + 7) >> 3;
-  const int lp = pow2_ge(nch);
+  const int lp = pow2_ge((cols + 7) >> 3);
   const int g = threadIdx.x / lp, l = threadIdx.x % lp, G = WG / lp;
-  for (int i0 = 0; i0 < rows; i0 += G) {
-    const int i = i0 + g;
-    double t = 0.0;
-    if (i < rows)
-      for (int ch = l; ch < nch; ch += lp) {
-        double a[8];
-        load8(A + (size_t)i * lda + 8 * ch, a);
+  double x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (8 * ch + e < cols) t += a[e] * v[8 * ch + e];
-      }
-    for (int off = lp >> 1; off > 0; off >>= 1) t += __shfl_xor(t, off);
-    if (i < rows && l == 0) out[i] += t;
+  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? v[8 * l + e] : 0.0;
+  for (int i0 = 0; i0 < rows; i0 += 4 * G) {
+    double t[4];
+    dot_rows4(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
+    if (l == 0)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i0 + u * G + g < rows) out[i0 + u * G + g] += t[u];
   }
 }
 
@@ -579,12 +603,14 @@ __device__ __forceinline__ void mv_cols(const F *B, int ldb, int rows, int cols,
 #pragma unroll
   for (int e = 0; e < 8; ++e) t[e] = 0.0;
   if (l < nch)
-    for (int i = g; i < rows; i += G) {
-      double a[8];
-      load8(B + (size_t)i * ldb + 8 * l, a);
-      const double vi = v[i];
+    for (int i = g; i < rows; i += 4 * G) {
+      double a[4][8];
+      load_rows4(B, ldb, rows, i, G, l, a);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] += a[e] * vi;
+      for (int u = 0; u < 4; ++u)
+        if (i + u * G < rows)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t[e] += a[u][e] * v[i + u * G];
     }
   for (int off = lp; off < 64; off <<= 1)
 #pragma unroll
@@ -600,8 +626,8 @@ __device__ __forceinline__ void mv_cols(const F *B, int ldb, int rows, int cols,
 }
 
 // out[c] = sum_i B[i][c] v[i] (i < rows, c < cols) by one wavefront: lane
-// l of a group of lp takes the 8-column chunk l of the rows g, g + G, ...;
-// the groups' partial sums are reduced by shuffles.
+// l of a group of lp takes the 8-column chunk l of the rows g, g + G, ..., four
+// rows' loads in flight; the groups' partial sums are reduced by shuffles.
 template <typename F>
 __device__ __forceinline__ void wave_mv_cols(const F *B, int ldb, int rows, int cols,
                                              const double *v, double *out) {
@@ -613,12 +639,14 @@ __device__ __forceinline__ void wave_mv_cols(const F *B, int ldb, int rows, int 
 #pragma unroll
   for (int e = 0; e < 8; ++e) t[e] = 0.0;
   if (l < nch)
-    for (int i = g; i < rows; i += G) {
-      double a[8];
-      load8(B + (size_t)i * ldb + 8 * l, a);
-      const double vi = v[i];
+    for (int i = g; i < rows; i += 4 * G) {
+      double a[4][8];
+      load_rows4(B, ldb, rows, i, G, l, a);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] += a[e] * vi;
+      for (int u = 0; u < 4; ++u)
+        if (i + u * G < rows)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t[e] += a[u][e] * v[i + u * G];
     }
   for (int off = lp; off < 64; off <<= 1)
 #pragma unroll
@@ -727,28 +755,25 @@ __global__ __launch_bounds__(WG) void k_hbs_down(const HbsNodeDev *__restrict__ 
 }
 
 // out[i] = sum_c A[i][c] v[c] (i < rows, c < cols) by one wavefront: a
-// group of lp lanes per row, eight entries per lane and load, the row's
-// partial sums reduced by shuffles.
+// group of lp lanes per row, eight entries per lane, four rows' loads in flight,
+// a row's partial sums reduced by shuffles.
 template <typename F>
 __device__ __forceinline__ void wave_mv_rows(const F *A, int lda, int rows, int cols,
                                              const double *v, double *out) {
   const int lane = threadIdx.x & 63;
-  const int nch = (cols + 7) >> 3;
+  const int nch = (cols + 7) >> 3;  // at most lp: one chunk per lane
   const int lp = pow2_ge(nch);
   const int g = lane / lp, l = lane % lp, G = 64 / lp;
-  for (int i0 = 0; i0 < rows; i0 += G) {
-    const int i = i0 + g;
-    double t = 0.0;
-    if (i < rows)
-      for (int ch = l; ch < nch; ch += lp) {
-        double a[8];
-        load8(A + (size_t)i * lda + 8 * ch, a);
+  double x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (8 * ch + e < cols) t += a[e] * v[8 * ch + e];
-      }
-    for (int off = lp >> 1; off > 0; off >>= 1) t += __shfl_xor(t, off);
-    if (i < rows && l == 0) out[i] = t;
+  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? v[8 * l + e] : 0.0;
+  for (int i0 = 0; i0 < rows; i0 += 4 * G) {
+    double t[4];
+    dot_rows4(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
+    if (l == 0)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i0 + u * G + g < rows) out[i0 + u * G + g] = t[u];
   }
 }
 

@@ -143,3 +143,21 @@ def test_block_products(dim, n, slabs, precision):
             u = op.solve(F[v], opts=opts)[0]
             assert relerr(U[v].reshape(-1), u.reshape(-1)) <= 1e-8
     op.close()
+
+
+@pytest.mark.parametrize("n,slabs,leaf", [(59, 6, 64), (99, 10, 64), (199, 10, 64), (399, 10, 64),
+                                          (511, 16, 32), (1023, 16, 32)])
+def test_sampled_product(n, slabs, leaf):
+    """y = S x through the sampled form with trees of 1 to 32 leaves, whose upper
+    levels one work-group takes.  Blocks of this operator decay fast (rank 30
+    holds them far below 1e-6); a lost or misplaced node is of order 1."""
+    print(f"\n[gpu] sampled product n={n} leaf={leaf}", flush=True)
+    op = ddst().Operator(2, n, slabs, bvec=(3.0, 1.0, 0.0), precision="fp64")
+    op.compress_hbs(rank=30, oversample=10, leaf=leaf, factor_dtype="fp64")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(op.n_ds * op.M, generator=g, device="cuda", dtype=torch.float64)
+    for transpose in (False, True):
+        y = op.apply(x, which="hbs", transpose=transpose).reshape(-1)
+        ref = op.apply(x, transpose=transpose).reshape(-1)
+        assert float((y - ref).norm() / ref.norm()) <= 1e-5
+    op.close()
