@@ -460,7 +460,8 @@ def large_leg(dd, torch, name):
         sym = bool(op.build_stats()["symmetric"])
         inv = n_inv * (1.0 if sym else 2.0) * M3
         if route == "dense_hodlr":
-            flops[route] = inv + chain
+            # symmetric: the chains of one direction serve both
+            flops[route] = inv + chain - ((p.n_slabs - 2) * steps * 2.0 * M3 if sym else 0.0)
             info = op.compress(tol=1e-8 if p.dim == 2 else 1e-7, leaf=128, oversample=10,
                                max_rank=118, factor_dtype=fdt)
             o = dataclasses_replace(opts, use_hodlr=True)
