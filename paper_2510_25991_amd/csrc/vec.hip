@@ -1012,21 +1012,24 @@ __device__ __forceinline__ double lag_nu(const GmresDev &d, int k) {
 // Hraw already): prov + rho a above the diagonal, rho nu below it; work-group
 // 0 stores that column in Hraw.
 __global__ __launch_bounds__(256) void k_lag_hmul(GmresDev d, int k, int col_final) {
-  const double nu = lag_nu(d, k);
   const double *a = d.dA;
-  const double rho = d.sc[2];
   const bool fin = k >= 1 && !col_final;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.x * 4 + wave;
+  const int jend = fin ? k - 1 : k;  // stored columns [j0, jend)
+  double acc = 0.0;
+  if (r <= k) {  // needs no norm: its loads are under way beside it
+    const int j0 = r > 0 ? r - 1 : 0;
+    const double *row = d.Hraw + gmres_roff(r, d.maxit) - j0;
+#pragma unroll 4
+    for (int j = j0 + lane; j < jend; j += 64) acc += row[j] * a[j];
+  }
+  const double nu = lag_nu(d, k);
+  const double rho = d.sc[2];
   auto lastcol = [&](int i) { return i < k ? d.prov[i] + rho * a[i] : rho * nu; };
   if (blockIdx.x == 0 && fin)
     for (int i = threadIdx.x; i <= k; i += 256) d.Hraw[gmres_rix(i, k - 1, d.maxit)] = lastcol(i);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = blockIdx.x * 4 + wave;
   if (r > k) return;
-  const int j0 = r > 0 ? r - 1 : 0;
-  const int jend = fin ? k - 1 : k;  // stored columns [j0, jend)
-  const double *row = d.Hraw + gmres_roff(r, d.maxit) - j0;
-  double acc = 0.0;
-  for (int j = j0 + lane; j < jend; j += 64) acc += row[j] * a[j];
   acc = wave_sum(acc);
   if (lane == 0) d.dv[r] = acc + (fin ? lastcol(r) * a[k - 1] : 0.0);
 }
@@ -1036,15 +1039,31 @@ __global__ __launch_bounds__(256) void k_lag_hmul(GmresDev d, int k, int col_fin
 // ((gamma - a.b) / nu - d_k) / nu; e = d / nu + h; pass B forms
 // z = w / nu - Q f - g u with f = e[0:k] - e_k a / nu, g = e_k / nu.
 __global__ __launch_bounds__(256) void k_lag_coef(GmresDev d, int k) {
-  __shared__ double sh[4], sek;
-  const double nu = lag_nu(d, k);
+  __shared__ double sh[2][4], sek, sinv;
   const int m = k + 1;
   const double *a = d.dA, *b = d.dA + m;
-  double t = 0.0;
-  for (int i = threadIdx.x; i < k; i += 256) t += a[i] * b[i];
-  t = block_sum(t, sh);
-  const double inv = nu > 0.0 ? 1.0 / nu : 0.0;
+  double aa = 0.0, t = 0.0;
+  for (int i = threadIdx.x; i < k; i += 256) {
+    const double x = a[i];
+    aa += x * x;
+    t += x * b[i];
+  }
+  aa = wave_sum(aa);
+  t = wave_sum(t);
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = aa;
+    sh[1][threadIdx.x >> 6] = t;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
+    aa = t = 0.0;
+    for (int w = 0; w < 4; ++w) {
+      aa += sh[0][w];
+      t += sh[1][w];
+    }
+    const double nu2 = d.dA[k] - aa;  // as lag_nu
+    const double inv = nu2 > 0.0 ? 1.0 / sqrt(nu2) : 0.0;
+    sinv = inv;
     const double hk = ((b[k] - t) * inv - d.dv[k]) * inv;
     d.prov[k] = hk;
     sek = d.dv[k] * inv + hk;
@@ -1052,7 +1071,7 @@ __global__ __launch_bounds__(256) void k_lag_coef(GmresDev d, int k) {
     d.sc[1] = sek * inv;
   }
   __syncthreads();
-  const double ek = sek;
+  const double ek = sek, inv = sinv;
   for (int i = threadIdx.x; i < k; i += 256) {
     const double h = (b[i] - d.dv[i]) * inv;
     d.prov[i] = h;
@@ -1429,17 +1448,40 @@ void launch_norm(const double *w, size_t len, double *out, double *part, hipStre
 }
 
 namespace {
-// Back substitution R y = g, column by column: y_j is fixed, then every
-// thread removes its contribution from rows i < j.
+// Back substitution R y = g, 64 columns at a time from the last: the first
+// wavefront solves their triangle, row j in lane j, with no barrier between the
+// unknowns, then every thread removes the 64 from its rows above (one column
+// and two barriers at a time: 1.56 ms at 1017 columns).
 __global__ __launch_bounds__(256) void k_gmres_backsub(GmresDev d, int k) {
+  constexpr int NB = 64;
+  __shared__ double ys[NB];
   for (int i = threadIdx.x; i < k; i += blockDim.x) d.y[i] = d.g[i];
   __syncthreads();
-  for (int j = k - 1; j >= 0; --j) {
-    const double *col = d.H + gmres_hoff(j);
-    const double yj = col[j] != 0.0 ? d.y[j] / col[j] : 0.0;
+  for (int j0 = (k - 1) / NB * NB; j0 >= 0; j0 -= NB) {
+    const int nb = min(NB, k - j0);
+    if (threadIdx.x < NB) {
+      const int l = threadIdx.x, i = j0 + l;
+      double y = l < nb ? d.y[i] : 0.0, R[NB];  // R[c]: entry (i, j0 + c)
+#pragma unroll
+      for (int c = 0; c < NB; ++c)
+        R[c] = c < nb && l <= c ? d.H[gmres_hoff(j0 + c) + i] : 0.0;
+#pragma unroll
+      for (int c = NB - 1; c >= 0; --c)
+        if (c < nb) {
+          const double piv = __shfl(R[c], c), yc = __shfl(y, c);
+          const double v = piv != 0.0 ? yc / piv : 0.0;
+          y = l == c ? v : y - R[c] * v;
+        }
+      ys[l] = y;
+      if (l < nb) d.y[i] = y;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) d.y[j] = yj;
-    for (int i = threadIdx.x; i < j; i += blockDim.x) d.y[i] -= col[i] * yj;
+    for (int i = threadIdx.x; i < j0; i += blockDim.x) {
+      double s = 0.0;
+#pragma unroll 8
+      for (int c = 0; c < nb; ++c) s += d.H[gmres_hoff(j0 + c) + i] * ys[c];
+      d.y[i] -= s;
+    }
     __syncthreads();
   }
 }

@@ -161,3 +161,18 @@ def test_sampled_product(n, slabs, leaf):
         ref = op.apply(x, transpose=transpose).reshape(-1)
         assert float((y - ref).norm() / ref.norm()) <= 1e-5
     op.close()
+
+
+@pytest.mark.parametrize("iters", [1, 63, 64, 65, 129, 300])
+def test_back_substitution_lengths(iters):
+    """x = V y of a run stopped at a given length (blocks of 64 unknowns, whole and
+    partial): its true residual is the one the rotations report."""
+    print(f"\n[gpu] back substitution {iters}", flush=True)
+    op = ddst().Operator(2, 255, 128, bvec=(4.0, 1.0, 0.0), precision="fp64")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    v = torch.randn(op.n_ds * op.M, generator=g, device="cuda", dtype=torch.float64)
+    x, used, relres = op.gmres(v, tol=1e-15, max_iter=iters, allow_notconv=True)
+    r = float((v - op.apply(x).reshape(-1)).norm() / v.norm())
+    assert used == iters
+    assert abs(r - relres) <= 1e-10 * max(1.0, relres) + 1e-6 * relres
+    op.close()
