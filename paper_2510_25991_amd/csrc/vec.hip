@@ -569,6 +569,13 @@ constexpr int kDotWaves = 16;  // wavefronts per work-group
 constexpr int kDotVecs = 8;    // basis vectors per wavefront and round
 constexpr int kDotRound = kDotWaves * kDotVecs;
 
+// Entries of the work-group's chunk of `chunk`.  In 32 bits: the compiler takes
+// a uniform 64-bit minimum's select from a condition that its comparison does
+// not set, and the last chunk then came out whole.
+__device__ __forceinline__ int chunk_len(int chunk, size_t len) {
+  return blockIdx.x + 1 < gridDim.x ? chunk : (int)(len - (size_t)blockIdx.x * chunk);
+}
+
 // T entries of v from e0 (FULL: all inside the chunk; else those past its cn
 // entries repeat the last one, and the caller drops or zeroes what they give).
 template <int T, bool FULL, typename B>
@@ -676,7 +683,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_mgs_update_dots(
     const double *__restrict__ h, double sign, size_t len, int ndot, double *__restrict__ part) {
   __shared__ double red[kDotWaves * 64 * T], ws[64 * T], sh[T];
   const size_t base = (size_t)blockIdx.x * 64 * T;
-  const int cn = (int)min((size_t)(64 * T), len - base);
+  const int cn = chunk_len(64 * T, len);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const B *v = V + base;
@@ -940,7 +947,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_lag_dots(const B *__restrict
                                                              double *__restrict__ part) {
   constexpr int T = kLagChunk / 64;
   const size_t base = (size_t)blockIdx.x * kLagChunk;
-  const int cn = (int)min((size_t)kLagChunk, len - base);
+  const int cn = chunk_len(kLagChunk, len);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nq = m - 1;
@@ -1092,7 +1099,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_lag_update(B *V, size_t stri
                                                                double *__restrict__ part) {
   __shared__ double red[2 * kDotWaves * 64 * T], sh[T];
   const size_t base = (size_t)blockIdx.x * 64 * T;
-  const int cn = (int)min((size_t)(64 * T), len - base);
+  const int cn = chunk_len(64 * T, len);
   const int tid = threadIdx.x;
   double sum[2][T], r[2] = {0.0, 0.0};
   const double *const coef[2] = {d.dA, d.cf};

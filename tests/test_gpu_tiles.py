@@ -73,7 +73,7 @@ def test_transfer_blocks_of_ragged_planes(n, slabs, b):
     assert worst <= fp32_block_tol((n + 1) // slabs, n * n) * scale
 
 
-@pytest.mark.parametrize("n,slabs", [(15, 4), (127, 64), (255, 128), (511, 128), (511, 256)])
+@pytest.mark.parametrize("n,slabs", [(15, 4), (127, 64), (255, 128), (383, 192), (511, 128), (511, 256)])
 def test_krylov_passes_at_each_width(n, slabs):
     """GMRES over bases of 45 entries (less than one chunk) to 130305: one, two
     and four entries per lane, with ragged last chunks.  The estimate of the
