@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../../include/ddst.h"
+#include "rules.h"
 
 struct ddst_op;
 
@@ -231,17 +232,6 @@ void launch_copy_planes(const double *src, int src_stride, int src_off, double *
 void launch_axpy(double *y, const double *x, double a, size_t len, hipStream_t s);
 void launch_fill(double *y, double v, size_t len, hipStream_t s);
 // part: at least dots_part_len(len, nvec) doubles of workspace
-// (the passes take chunks of 64 dot_width entries: 64, 128 or 256, the most
-// that leave one per CU)
-constexpr size_t kDotChunks = 256;
-inline int dot_width(size_t len) {
-  return len >= 64 * 4 * kDotChunks ? 4 : len >= 64 * 2 * kDotChunks ? 2 : 1;
-}
-inline size_t dot_chunks(size_t len) {
-  const size_t c = 64 * (size_t)dot_width(len);
-  return (len + c - 1) / c;
-}
-inline size_t dots_part_len(size_t len, int nvec) { return dot_chunks(len) * (size_t)nvec; }
 // w += sign V h over nvec basis vectors of stride `stride` (FP64 or FP32
 // storage, FP64 arithmetic)
 template <typename B>

@@ -1,0 +1,33 @@
+"""The host's rules (csrc/rules.h), compiled for the CPU and evaluated here."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2510_25991_amd", "csrc")
+
+
+def evaluate(tmp_path, body):
+    """Output lines of a C++ main() with this body."""
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <cstdio>\n#include "rules.h"\nusing namespace ddst;\n'
+                   "int main() {\n" + body + "\n  return 0;\n}\n")
+    subprocess.run([cxx, "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()
+
+
+def test_dot_workspace_holds_every_shorter_vector(tmp_path):
+    """A workspace sized for one length serves every shorter one (a solve of
+    several loads works on stacked vectors and on single ones)."""
+    bad = evaluate(tmp_path, """
+  size_t most = 0;
+  for (size_t len = 1; len <= 400000; ++len) {
+    most = std::max(most, dot_chunks(len));
+    if (dots_part_len(len, 3) < 3 * most) { std::printf("%zu\\n", len); break; }
+  }""")
+    assert bad == []
