@@ -247,7 +247,7 @@ void run_sweeps(ddst_op *op, const SweepPlan &plan, const SweepBuffers &buf, hip
   tab.upload(s);
   DeviceMem gjw(gj_workspace_bytes(nsw, ld, sizeof(T), op->sym));
   GjStreams gs;
-  HIPCHK(gs.create(ld, op->M, sizeof(T)));
+  HIPCHK(gs.create(nsw, ld, op->M, sizeof(T), op->sym));
   // The transfer chain of plane k needs only G_k: it runs on a second
   // stream, overlapping the inversion of plane k+1 with its
   // (matrix-core-bound) GEMM.  Before plane k+2 is assembled into the
@@ -438,7 +438,7 @@ int build_impl(ddst_op *op, int keep, int blocks, hipStream_t s) {
   launch_assemble<T>(tab.at<AsmJob>(oc), nds, op->coef, op->n, op->dim, op->M, op->ld, s);
   DeviceMem gjw(gj_workspace_bytes(nds, op->ld, sizeof(T), op->sym));
   GjStreams gs;
-  HIPCHK(gs.create(op->ld, op->M, sizeof(T)));
+  HIPCHK(gs.create(nds, op->ld, op->M, sizeof(T), op->sym));
   HIPCHK(gj_invert<T>(tab.at<void *>(om), nds, op->ld, op->M, gjw.p, op->flag, op->indefinite,
                       op->sym, gs, s));
   if (!sj.empty())
@@ -1961,7 +1961,7 @@ static int test_invert(int32_t precision, int32_t ld, int32_t batch, void *A, in
     HIPCHK(hipMemsetAsync(fl.p, 0, sizeof(ElimStatus), stream));
     DeviceMem w(gj_workspace_bytes(batch, ld, esize(precision), sym));
     GjStreams gs;
-    HIPCHK(gs.create(ld, ld, esize(precision)));
+    HIPCHK(gs.create(batch, ld, ld, esize(precision), sym));
     int *flag = static_cast<int *>(fl.p);
     if (precision == DDST_FP32)
       HIPCHK(gj_invert<float>(t.at<void *>(o), batch, ld, ld, w.p, flag, 0, sym, gs, stream));

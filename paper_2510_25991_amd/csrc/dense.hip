@@ -1111,9 +1111,9 @@ __global__ __launch_bounds__(256, 2) void k_gj_update(void *const *__restrict__ 
 }
 
 // ---- outer elimination: blocks of kOuter = 512 ------------------------------
-// Matrices of more than kOuter rows are eliminated in outer blocks P: D[P, P]
-// is inverted by the 128-wide steps above, and the rest of the matrix takes
-// one step of rank w <= 512 per outer block:
+// Where outer_blocks (rules.h) says so, matrices are eliminated in outer blocks
+// P: D[P, P] is inverted by the 128-wide steps above, and the rest of the
+// matrix takes one step of rank w <= 512 per outer block:
 //   left     D[P, j] = P^{-1} D[P, j]                       (over its operand)
 //   update   D[i, j] -= D[i, P] D[P, j]
 //   right    D[i, P] = -D[i, P] P^{-1}                      (over its operand)
@@ -1478,17 +1478,14 @@ GjStreams::~GjStreams() {
 // Steps from which the look-ahead schedule pays (below, its events and streams
 // cost more than the overlap gives: 361 rows, 3.2 ms against 2.25 in all).
 constexpr int kLookAhead = 4;
-// Matrices of more rows than this are eliminated in outer blocks (FP32 only: an
-// FP64 update of rank 128 takes as long on the matrix cores as in memory).
-// 1024 rows: the chains' GEMMs fill the chip beside the 128-wide steps, and
-// outer blocks put a second inversion in series: 1023^2 on 8 slabs 145 ms
-// against 104, on 64 57 against 65; above, 63^3 on 8 slabs 112 against 124 ms.
-constexpr int kSingle = 1024;
-static int block_width(int ld, size_t esz) { return esz == 4 && ld > kSingle ? kOuter : ld; }
+// Rows that the 128-wide steps invert at a time.
+static int block_width(int nmat, int ld, size_t esz, int sym) {
+  return outer_blocks(nmat, ld, esz, sym != 0) ? kOuter : ld;
+}
 
 // A stream costs more to make (and end) than the elimination of a small block
 // takes: only those that the schedule uses.
-hipError_t GjStreams::create(int ld, int M, size_t esz) {
+hipError_t GjStreams::create(int nmat, int ld, int M, size_t esz, int sym) {
   const int n = (M + kTile - 1) / kTile * kTile;
   hipError_t e = hipSuccess;
   auto stream = [&](hipStream_t &st) {
@@ -1504,7 +1501,7 @@ hipError_t GjStreams::create(int ld, int M, size_t esz) {
     stream(x);
     events({&panel, &arms, &upd});
   }
-  if (n > block_width(ld, esz)) {
+  if (n > block_width(nmat, ld, esz, sym)) {
     stream(o);
     events({&left, &next, &rest});
   }
@@ -1512,7 +1509,7 @@ hipError_t GjStreams::create(int ld, int M, size_t esz) {
 }
 
 size_t gj_workspace_bytes(int nmat, int ld, size_t esz, int sym) {
-  const size_t lw = block_width(ld, esz);
+  const size_t lw = block_width(nmat, ld, esz, sym);
   return (size_t)nmat * esz *
          (4 * (size_t)kNB * lw + (size_t)kNB * kNB +
           (sym && lw != (size_t)ld ? (size_t)kOuter * ld : 0));
@@ -1701,7 +1698,7 @@ hipError_t gj_invert(void *const *mats, int nmat, int ld, int M, void *work, int
   if (sym && n > 0)
     hipLaunchKernelGGL(k_sym_diag<T>, dim3(10, n / kTile, nmat), dim3(256), 0, s, mats, ld);
   hipError_t e;
-  if (n <= block_width(ld, sizeof(T)))
+  if (n <= block_width(nmat, ld, sizeof(T), sym))
     e = invert_block<T>(mats, nmat, ld, 0, n / kTile, M, w, flag, any_sign, sym, gs, s);
   else if constexpr (std::is_same<T, float>::value)
     e = invert_outer(mats, nmat, ld, n, M, w, flag, any_sign, sym, gs, s);

@@ -163,7 +163,7 @@ struct GjStreams {
   GjStreams() = default;
   GjStreams(const GjStreams &) = delete;
   GjStreams &operator=(const GjStreams &) = delete;
-  hipError_t create(int ld, int M, size_t esz);  // for gj_invert with these
+  hipError_t create(int nmat, int ld, int M, size_t esz, int sym);  // for gj_invert with these
   ~GjStreams();
 };
 // Device status words of the local eliminations (32 bytes, zeroed at set-up):
@@ -181,8 +181,9 @@ struct ElimStatus {
 };
 static_assert(sizeof(ElimStatus) == 32, "ElimStatus is 32 bytes");
 // In-place Gauss-Jordan inversion (no pivoting) of `nmat` ld x ld matrices,
-// by outer blocks of 512 rows with look-ahead.  work: gj_workspace_bytes
-// bytes; flag: device ElimStatus: bad set to 1 when a pivot is non-finite, or
+// in steps of 128 rows with look-ahead, or in outer blocks of 512 rows
+// (outer_blocks, rules.h).  work: gj_workspace_bytes of the same nmat, ld, type
+// and sym; gs: created for the same; flag: device ElimStatus: bad set to 1 when a pivot is non-finite, or
 // non-positive unless any_sign is non-zero, inv_max raised to the largest
 // |entry| of the inverted pivot blocks; sym non-zero: the matrices are
 // symmetric and only their lower triangle is eliminated (the inverse is
@@ -191,7 +192,7 @@ static_assert(sizeof(ElimStatus) == 32, "ElimStatus is 32 bytes");
 template <typename T>
 hipError_t gj_invert(void *const *mats, int nmat, int ld, int M, void *work, int *flag,
                      int any_sign, int sym, GjStreams &gs, hipStream_t s);
-// Bytes of Gauss-Jordan workspace for nmat matrices.
+// Bytes of Gauss-Jordan workspace.
 size_t gj_workspace_bytes(int nmat, int ld, size_t esz, int sym);
 
 // ---- vector kernels (vec.hip) --------------------------------------------

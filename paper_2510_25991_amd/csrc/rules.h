@@ -28,4 +28,37 @@ inline size_t dots_part_len(size_t len, int nvec) {
   return std::max(dot_chunks(len), most) * (size_t)nvec;
 }
 
+// ---- Gauss-Jordan inversion ---------------------------------------------------
+// Whether nmat matrices of ld rows (element size esz) are eliminated in outer
+// blocks of 512 rows.  An outer block's products take 256 x 256 tiles at the
+// matrix cores' rate, where a rank-128 update is bound by its traffic, but they
+// put a second elimination in series: they pay where the tiles fill the chip
+// several times over, so the rule counts the tiles of all matrices (half of
+// them where the symmetric elimination touches the lower triangle only).
+// Builds, ms:                           tiles   one level   outer blocks
+//   2D 1151, 4 slabs (7 matrices)         142       205          315
+//   2D 1535, 4 slabs                      252       383          601
+//   2D 1023, 16 slabs                     496        75.1         89.8
+//   2D 1023, 32 slabs, symmetric          503        53.4         57.7
+//   2D 1791, 8 slabs                      734       563          562
+//   3D 47, 12 slabs, symmetric            856        21.3         21.5
+//   2D 1407, 16 slabs                     936       237          222
+//   2D 2047, 8 slabs                      959       949          828
+//   2D 1023, 32 slabs                    1006        69.5         64.4
+//   2D 1023, 64 slabs, symmetric         1014        51.0         48.5
+//   2D 1535, 16 slabs                    1115       317          294
+//   2D 1151, 32 slabs                    1274       107          110
+//   3D 63, 8 slabs, symmetric            1803       117           95.0
+//   2D 1023, 64 slabs                    2028        64.7         58.5
+// Below 896 rows the second block is half a block or less: 767 on 64 slabs
+// (1140 tiles) 25.6 and 25.8 ms, 639 on 128 (1589) 14.6 and 14.5.
+// FP64: one level, whose update of rank 128 takes as long on the matrix cores
+// as in memory.
+constexpr int kOuterRows = 896;    // rows (with padding) from which
+constexpr int kOuterTiles = 900;   // 256 x 256 tiles from which
+inline bool outer_blocks(int nmat, int ld, size_t esz, bool sym) {
+  const double side = ld / 256.0;
+  return esz == 4 && ld >= kOuterRows && nmat * side * side >= (sym ? 2 : 1) * kOuterTiles;
+}
+
 }  // namespace ddst

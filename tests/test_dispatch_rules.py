@@ -31,3 +31,18 @@ def test_dot_workspace_holds_every_shorter_vector(tmp_path):
     if (dots_part_len(len, 3) < 3 * most) { std::printf("%zu\\n", len); break; }
   }""")
     assert bad == []
+
+
+@pytest.mark.parametrize("dim,n,slabs,sym,outer", [
+    (2, 1151, 2, 0, 0), (2, 1151, 4, 0, 0), (2, 1535, 4, 0, 0), (2, 2047, 4, 1, 0),
+    (3, 39, 4, 0, 0), (3, 47, 4, 1, 0), (2, 1023, 16, 0, 0), (2, 1023, 32, 1, 0),
+    (2, 1023, 32, 0, 1), (2, 1023, 64, 1, 1), (2, 1535, 16, 0, 1), (2, 2047, 16, 0, 1),
+    (3, 63, 8, 1, 1), (2, 767, 64, 0, 0)])
+def test_outer_blocks_take_the_faster_way(tmp_path, dim, n, slabs, sym, outer):
+    """Builds whose two ways were measured (the matrices of all sweeps at once)."""
+    ld = (n ** (dim - 1) + 127) // 128 * 128
+    got = evaluate(tmp_path, 'std::printf("%%d %%d", (int)outer_blocks(%d, %d, 4, %s), '
+                   "(int)outer_blocks(%d, %d, 8, %s));"
+                   % (2 * slabs - 1, ld, "true" if sym else "false",
+                      2 * slabs - 1, ld, "true" if sym else "false"))
+    assert got == [str(outer), "0"]

@@ -1,0 +1,70 @@
+"""Kernel variants that the host chooses by the shape of a call, each at shapes
+where its rule takes it."""
+import math
+
+import pytest
+import torch
+
+from tol import fp32_block_tol
+
+pytestmark = pytest.mark.gpu
+
+
+def ddst():
+    from paper_2510_25991_amd import ddst as mod
+    return mod
+
+
+def plane_schur(M, skew, dtype=torch.float64):
+    """The limit of the plane Schur complements of a 2D Laplacian, D = T - D^{-1}
+    with T = tridiag(-1, 4, -1), rows and columns scaled apart by up to
+    exp(skew) (skew 0: symmetric)."""
+    i = torch.arange(1, M + 1, device="cuda", dtype=dtype)
+    q = math.sqrt(2 / (M + 1)) * torch.sin(math.pi * i[:, None] * i[None, :] / (M + 1))
+    lam = 4 - 2 * torch.cos(math.pi * i / (M + 1))
+    D = (q * ((lam + torch.sqrt(lam * lam - 4)) / 2)) @ q
+    s = torch.exp(skew * i / M)
+    return (D + D.T) / 2 if skew == 0 else s[:, None] * D / s[None, :]
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("ld,M,tiles", [(896, 800, 74), (1152, 1025, 45), (1280, 1225, 36),
+                                        (1664, 1536, 22)])
+def test_outer_elimination_is_as_accurate(ld, M, tiles, symmetric):
+    """Many matrices are eliminated in outer blocks, two of them in one level:
+    the same sums in another order, so the same error, up to a factor of 2 in
+    the Frobenius norm and of 4 in the largest entry."""
+    batch = tiles * (2 if symmetric else 1)
+    print(f"\n[gpu] outer elimination ld={ld} M={M} batch={batch}", flush=True)
+    one = torch.eye(ld, device="cuda", dtype=torch.float32)
+    one[:M, :M] = plane_schur(M, 0.0 if symmetric else 1.0).float()
+    if symmetric:
+        one[:M, :M] = torch.tril(one[:M, :M]) + torch.tril(one[:M, :M], -1).T
+    ref = torch.linalg.inv(one.double())
+    few = one.repeat(2, 1, 1)
+    many = one.repeat(batch, 1, 1)
+    ddst().kernel_invert(few, symmetric=symmetric)
+    ddst().kernel_invert(many, symmetric=symmetric)
+    e1 = few[0].double() - ref
+    for b in (0, batch // 2, batch - 1):
+        e = many[b].double() - ref
+        assert float(e.norm()) <= 2 * float(e1.norm())
+        assert float(e.abs().max()) <= 4 * float(e1.abs().max())
+
+
+@pytest.mark.parametrize("dim,n,slabs,b", [(2, 895, 64, 10.0), (2, 1023, 64, 0.0),
+                                           (3, 47, 8, 10.0), (3, 47, 24, 0.0)])
+def test_builds_by_outer_blocks(dim, n, slabs, b):
+    """FP32 transfer blocks of builds that eliminate in outer blocks against FP64
+    ones (one level)."""
+    print(f"\n[gpu] outer build {dim}D n={n} slabs={slabs} b={b}", flush=True)
+    ops = [ddst().Operator(dim, n, slabs, bvec=(b, 0.0, 0.0), precision=p, keep_factors=False)
+           for p in ("fp32", "fp64")]
+    worst = scale = 0.0
+    for j in (1, 2, slabs // 2, slabs - 1):
+        for x, y in zip(ops[0].transfer(j), ops[1].transfer(j)):
+            worst = max(worst, float((x.double() - y.double()).abs().max()))
+            scale = max(scale, float(y.abs().max()))
+    for op in ops:
+        op.close()
+    assert worst <= fp32_block_tol((n + 1) // slabs, n ** (dim - 1)) * scale
