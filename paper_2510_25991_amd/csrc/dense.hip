@@ -155,7 +155,7 @@ template <> struct MmaLds<float> {
 // operands (a thread holds 16 values of one row of A and of one column of
 // B), splits them once and stores the three parts in fragment order, so the
 // product loop reads whole 8-element fragments (16 bytes) from LDS.
-template <bool NEG_A, bool TA, bool PART>
+template <bool NEG_A, bool TA, bool TB, bool PART>
 __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda,
                                             const float *__restrict__ B, int ldb,
                                             const double *__restrict__ bscale, int K,
@@ -177,8 +177,12 @@ __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda
     } else {
       ld16n<16>(A + (size_t)rr * lda + k0 + kh, ra);
     }
+    if (TB) {
+      ld16n<16>(B + (size_t)rr * ldb + k0 + kh, rb);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) rb[e] = gp(B)[(size_t)(k0 + kh + e) * ldb + rr];
+      for (int e = 0; e < 16; ++e) rb[e] = gp(B)[(size_t)(k0 + kh + e) * ldb + rr];
+    }
     if (bscale) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) rb[e] *= (float)gp(bscale)[k0 + kh + e];
@@ -234,7 +238,7 @@ __device__ __forceinline__ void mma_tile_x6(const float *__restrict__ A, int lda
 // B row-major with leading dim ldb (points at the tile's first column).
 // TA: the operand is the transpose of a row-major matrix G, A[i][k] =
 // G[k][i]; A then points at G's column of the tile's first row.
-// TB (FP64): the right operand is the transpose of a row-major matrix H,
+// TB: the right operand is the transpose of a row-major matrix H,
 // B[k][j] = H[j][k]; B then points at H's row of the tile's first column.
 // rows, cols: how many of the tile's rows and columns are wanted; 16 x 16
 // tiles past them are skipped and stay as they are (products over the padding
@@ -253,9 +257,8 @@ __device__ __forceinline__ void mma_part(const T *__restrict__ A, int lda,
   const int ni = __builtin_amdgcn_readfirstlane(min(4, max(0, (rows - wm + 15) / 16)));
   const int nj = __builtin_amdgcn_readfirstlane(min(4, max(0, (cols - wn + 15) / 16)));
   if constexpr (std::is_same<T, float>::value) {
-    static_assert(!TB, "FP32: see k_gemm_big");
     // As is the start of an MmaLds<float>::bytes buffer
-    mma_tile_x6<NEG_A, TA, PART>(A, lda, B, ldb, bscale, K,
+    mma_tile_x6<NEG_A, TA, TB, PART>(A, lda, B, ldb, bscale, K,
                                  reinterpret_cast<unsigned char *>(As), acc, ni, nj);
     return;
   }
@@ -1418,28 +1421,20 @@ void launch_scale_cols(const GemmJob *jobs, int njobs, int ld, double alpha, hip
   hipLaunchKernelGGL(k_scale_cols<T>, dim3(ld, njobs), dim3(256), 0, s, jobs, ld, (T)alpha);
 }
 
-// 256 x 256 tiles from which k_gemm_big is the faster one: the build of 1023^2
-// on 64 slabs (62 chains of 16 tiles) took 65.5 ms with it against 69.0, that
-// on 32 (30 chains) 57.8 ms with either; fewer tiles leave CUs idle.
-constexpr int kGemmMany = 900;
 template <typename T>
 void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, bool trans_b,
                  hipStream_t s) {
   if (njobs <= 0) return;
   const int nt = ld / kTile, nbig = (ld + WgTile<2>::TM - 1) / WgTile<2>::TM;
   const ProfSpan ps = prof_open(KK_GEMM);
-  if constexpr (std::is_same<T, float>::value) {
-    if (trans_b || njobs * nbig * nbig >= kGemmMany)
-      hipExtLaunchKernelGGL(trans_b ? k_gemm_big<true> : k_gemm_big<false>,
-                            dim3(nbig * nbig * njobs), dim3(512), 0, s, ps.a, ps.b, 0, jobs, ld, M,
-                            (float)alpha);
-    else
-      hipExtLaunchKernelGGL((k_gemm<float, false>), dim3(nt * nt * njobs), dim3(256), 0, s, ps.a,
-                            ps.b, 0, jobs, ld, M, (float)alpha, 0.f);
-  } else {
+  const bool big = std::is_same<T, float>::value && gemm_big_tiles(njobs, ld);
+  if (big)
+    hipExtLaunchKernelGGL((trans_b ? k_gemm_big<true> : k_gemm_big<false>),
+                          dim3(nbig * nbig * njobs), dim3(512), 0, s, ps.a, ps.b, 0, jobs, ld, M,
+                          (float)alpha);
+  else
     hipExtLaunchKernelGGL((trans_b ? k_gemm<T, true> : k_gemm<T, false>), dim3(nt * nt * njobs),
                           dim3(256), 0, s, ps.a, ps.b, 0, jobs, ld, M, (T)alpha, T(0));
-  }
   prof_close(ps, KK_GEMM, 2.0 * njobs * (double)M * M * M);
 }
 

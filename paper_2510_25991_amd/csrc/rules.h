@@ -28,6 +28,29 @@ inline size_t dots_part_len(size_t len, int nvec) {
   return std::max(dot_chunks(len), most) * (size_t)nvec;
 }
 
+// ---- FP32 batched products -----------------------------------------------------
+// Whether njobs products of ld x ld matrices take 256 x 256 tiles (one
+// work-group a CU) or 128 x 128 ones.  Both take the same rows and columns;
+// what decides is how many CUs have a tile, and the halves of the last tiles
+// that an odd multiple of 128 leaves empty.  us, 256 x 256 against 128 x 128:
+//   16 x 1024   (256 tiles)   162  178        33 x 1024  (528)    445  389
+//   60 x 1024   (960)         628  668        65 x 1024 (1040)    755  754
+//   188 x 1024 (3008)        1993 2143        14 x 896   (224)    139  152
+//   900 x 128   (900)          87   41        225 x 384  (900)    253  166
+//   100 x 640   (900)         350  320        94 x 896  (1504)    774  715
+//   36 x 1152   (900)         618  591        25 x 1408  (900)    789  742
+//   21 x 1664  (1029)        1024 1014        16 x 1920 (1024)   1130 1227
+//   1 x 1024     (16)         129   63        4 x 256      (4)     43   21
+// Between 256 and 900 tiles the last round of work-groups decides; in a build
+// other launches run beside it: symmetric 1023^2 on 32 slabs (30 chains, 480
+// tiles) 57.8 ms with either, on 64 (992) 65.5 against 69.0 with 128 x 128.
+constexpr int kGemmMany = 900;     // 256 x 256 tiles from which
+constexpr int kGemmOddRows = 1664; // rows from which an odd multiple of 128
+inline bool gemm_big_tiles(int njobs, int ld) {
+  const int nt = (ld + 255) / 256;
+  return (ld % 256 == 0 || ld >= kGemmOddRows) && (long long)njobs * nt * nt >= kGemmMany;
+}
+
 // ---- Gauss-Jordan inversion ---------------------------------------------------
 // Whether nmat matrices of ld rows (element size esz) are eliminated in outer
 // blocks of 512 rows.  An outer block's products take 256 x 256 tiles at the

@@ -15,9 +15,8 @@
 // of 12 x 4096^3: 177 TFLOP/s with 128 x 128 tiles, 218 with these (235 and
 // 291 on matrices of zeros: what bounds both is power, the clock falls to 1.6
 // GHz; the library's 8192^3 BF16 product reaches 1.14 PFLOP/s on the same
-// card, these 1.31 PFLOP/s of BF16 products).  With fewer tiles than a few
-// per CU the 128 x 128 tiles are the better ones: 60 x 768^3, two waves of
-// work-groups with the second nearly empty, 345 us against 379.
+// card, these 1.31 PFLOP/s of BF16 products).  Where the tiles are few or half
+// empty the 128 x 128 ones are the better (gemm_big_tiles, rules.h).
 #pragma once
 
 #include "internal.h"

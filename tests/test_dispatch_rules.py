@@ -46,3 +46,12 @@ def test_outer_blocks_take_the_faster_way(tmp_path, dim, n, slabs, sym, outer):
                    % (2 * slabs - 1, ld, "true" if sym else "false",
                       2 * slabs - 1, ld, "true" if sym else "false"))
     assert got == [str(outer), "0"]
+
+
+@pytest.mark.parametrize("njobs,ld,big", [
+    (900, 128, 0), (225, 384, 0), (100, 640, 0), (94, 896, 0), (36, 1152, 0), (25, 1408, 0),
+    (1, 1024, 0), (4, 256, 0), (33, 1024, 0), (60, 1024, 1), (188, 1024, 1), (225, 512, 1),
+    (16, 1920, 1), (4000, 2048, 1)])
+def test_products_take_the_faster_tiles(tmp_path, njobs, ld, big):
+    got = evaluate(tmp_path, f'std::printf("%d", (int)gemm_big_tiles({njobs}, {ld}));')
+    assert got == [str(big)]

@@ -68,3 +68,36 @@ def test_builds_by_outer_blocks(dim, n, slabs, b):
     for op in ops:
         op.close()
     assert worst <= fp32_block_tol((n + 1) // slabs, n ** (dim - 1)) * scale
+
+
+@pytest.mark.parametrize("batch,ld", [(225, 512), (224, 512), (21, 1664), (6, 1664), (60, 1024)])
+def test_products_at_the_tiles_rule(batch, ld):
+    """FP32 products on both sides of the rule: 128 x 128 tiles, 256 x 256 ones,
+    whole and with half tiles at the edges (sums of up to 1664 terms: 2e-5 per
+    384 of them, as the other product tests)."""
+    print(f"\n[gpu] products {batch} x {ld}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(ld + batch)
+    A = torch.randn(batch, ld, ld, generator=g, device="cuda")
+    B = torch.randn(batch, ld, ld, generator=g, device="cuda")
+    C = torch.empty_like(A)
+    ddst().kernel_gemm(A, B, C)
+    for b in (0, batch // 2, batch - 1):
+        ref = A[b].double() @ B[b].double()
+        assert float((C[b].double() - ref).abs().max() / ref.abs().max()) <= 2e-5 * ld / 384
+
+
+@pytest.mark.parametrize("dim,n,slabs", [(2, 31, 4), (2, 127, 4), (2, 299, 10), (2, 511, 256),
+                                         (3, 13, 7), (3, 31, 16)])
+def test_transposed_products_of_symmetric_builds(dim, n, slabs):
+    """The right blocks of a symmetric operator, products with a transposed right
+    operand, by both tile sizes: FP32 against FP64."""
+    print(f"\n[gpu] symmetric build {dim}D n={n} slabs={slabs}", flush=True)
+    ops = [ddst().Operator(dim, n, slabs, precision=p) for p in ("fp32", "fp64")]
+    worst = scale = 0.0
+    for j in range(1, slabs):
+        x, y = (op.transfer(j)[1] for op in ops)
+        worst = max(worst, float((x - y).abs().max()))
+        scale = max(scale, float(y.abs().max()))
+    for op in ops:
+        op.close()
+    assert worst <= fp32_block_tol((n + 1) // slabs, n ** (dim - 1)) * scale
