@@ -63,6 +63,7 @@ struct Hbs {
   int k = 0, s = 0, sp = 0, leaf = 0, depth = 0, dtype = 0, nblk = 0;
   std::vector<std::vector<HbsNodeDev>> lv;  // depth d = 0 .. depth (0: root)
   std::vector<int> nhat;                    // hat entries per level (sum of ranks)
+  std::vector<int> rows;                    // largest node (rows) per level
   std::vector<size_t> hoff;                 // per-level offset in one block's hat vector
   size_t hat_per_block = 0;
   size_t block_elems = 0, root_off = 0;     // FP64 compression output per block; root D offset
@@ -538,54 +539,96 @@ __device__ __forceinline__ int pow2_ge(int n) {
   return p;
 }
 
-// Rows i0, i0 + G, i0 + 2 G, i0 + 3 G of A's 8-column chunk ch, loaded together
+// Calls f with the number of rows a group of lanes takes at a time (a compile-
+// time constant, at most MAX: hbs_rows_in_flight), the rows of a product being
+// dealt to G groups: several while there are so many, so that their loads are
+// in flight together, and no more than there are, since rows past the last are
+// loaded too.
+template <int MAX, typename Fn>
+__device__ __forceinline__ void with_rows(int rows, int G, Fn f) {
+  if (rows <= G)
+    f(std::integral_constant<int, 1>{});
+  else if (MAX == 2 || rows <= 2 * G)
+    f(std::integral_constant<int, 2>{});
+  else
+    f(std::integral_constant<int, 4>{});
+}
+
+// Rows i0, i0 + G, .. (U of them) of A's 8-column chunk ch, loaded together
 // (rows past the last repeat it).
-template <typename F>
-__device__ __forceinline__ void load_rows4(const F *A, int lda, int rows, int i0, int G, int ch,
-                                           double (&a)[4][8]) {
+template <int U, typename F>
+__device__ __forceinline__ void load_rows(const F *A, int lda, int rows, int i0, int G, int ch,
+                                          double (&a)[U][8]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < U; ++u)
     load8(A + (size_t)min(i0 + u * G, rows - 1) * lda + 8 * ch, a[u]);
 }
 
-// t[u] += A[i0 + u G][...] v by the group of lp lanes, lane l of it with chunk l,
+// t[u] = A[i0 + u G][...] v by the group of lp lanes, lane l of it with chunk l,
 // reduced across the group.
-template <typename F>
-__device__ __forceinline__ void dot_rows4(const F *A, int lda, int rows, int cols, int i0, int G,
-                                          int l, int lp, const double (&x)[8], double (&t)[4]) {
-  double a[4][8];
-  load_rows4(A, lda, rows, i0, G, min(l, ((cols + 7) >> 3) - 1), a);
+template <int U, typename F>
+__device__ __forceinline__ void dot_rows(const F *A, int lda, int rows, int cols, int i0, int G,
+                                         int l, int lp, const double (&x)[8], double (&t)[U]) {
+  double a[U][8];
+  const int nch = (cols + 7) >> 3;
+  if (U > 1 || (i0 < rows && l < nch))  // one row: none past the last
+    load_rows<U>(A, lda, rows, i0, G, min(l, nch - 1), a);
+  else
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
+    for (int e = 0; e < 8; ++e) a[0][e] = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
     t[u] = 0.0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (8 * l + e < cols) t[u] += a[u][e] * x[e];
+    for (int e = 0; e < 8; ++e) t[u] += a[u][e] * x[e];
   }
   for (int off = lp >> 1; off > 0; off >>= 1)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] += __shfl_xor(t[u], off);
+    for (int u = 0; u < U; ++u) t[u] += __shfl_xor(t[u], off);
+}
+
+// t[e] += sum_i B[i][8 l + e] v[i] over the rows g, g + G, ..
+template <int MAX, typename F>
+__device__ __forceinline__ void sum_rows(const F *B, int ldb, int rows, int g, int G, int l,
+                                         const double *v, double (&t)[8]) {
+  with_rows<MAX>(rows, G, [&](auto n) {
+    constexpr int U = decltype(n)::value;
+    for (int i = g; i < rows; i += U * G) {
+      double a[U][8];
+      load_rows<U>(B, ldb, rows, i, G, l, a);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (U == 1 || i + u * G < rows)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) t[e] += a[u][e] * v[i + u * G];
+    }
+  });
 }
 
 // out[i] += sum_c A[i][c] v[c] (i < rows, c < cols; rows of A padded to lda,
-// a multiple of 8): a group of lp lanes per row, eight entries per lane, four
-// rows' loads in flight.  Called by all threads with the same arguments.
-template <typename F>
+// a multiple of 8): a group of lp lanes per row, eight entries per lane.
+// Called by all threads with the same arguments.
+template <int MAX, typename F>
 __device__ __forceinline__ void mv_rows(const F *A, int lda, int rows, int cols, const double *v,
                                         double *out) {
   const int lp = pow2_ge((cols + 7) >> 3);
   const int g = threadIdx.x / lp, l = threadIdx.x % lp, G = WG / lp;
   double x[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? v[8 * l + e] : 0.0;
-  for (int i0 = 0; i0 < rows; i0 += 4 * G) {
-    double t[4];
-    dot_rows4(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
-    if (l == 0)
+  for (int e = 0; e < 8; ++e) x[e] = v[8 * l + e];  // inside v: l < 32
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i0 + u * G + g < rows) out[i0 + u * G + g] += t[u];
-  }
+  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? x[e] : 0.0;
+  with_rows<MAX>(rows, G, [&](auto n) {
+    constexpr int U = decltype(n)::value;
+    for (int i0 = 0; i0 < rows; i0 += U * G) {
+      double t[U];
+      dot_rows<U>(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
+      if (l == 0)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * G + g < rows) out[i0 + u * G + g] += t[u];
+    }
+  });
 }
 
 // out[c] += sum_i B[i][c] v[i] (i < rows, c < cols): lane l of a group of lp
@@ -593,7 +636,7 @@ __device__ __forceinline__ void mv_rows(const F *A, int lda, int rows, int cols,
 // sums are reduced across the wavefront's groups by shuffles and across the
 // four wavefronts through red.  Called by all threads with the same
 // arguments; out is complete on return.
-template <typename F>
+template <int MAX, typename F>
 __device__ __forceinline__ void mv_cols(const F *B, int ldb, int rows, int cols, const double *v,
                                         double *out, double (*red)[kMaxN]) {
   const int nch = (cols + 7) >> 3;
@@ -602,16 +645,7 @@ __device__ __forceinline__ void mv_cols(const F *B, int ldb, int rows, int cols,
   double t[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) t[e] = 0.0;
-  if (l < nch)
-    for (int i = g; i < rows; i += 4 * G) {
-      double a[4][8];
-      load_rows4(B, ldb, rows, i, G, l, a);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i + u * G < rows)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t[e] += a[u][e] * v[i + u * G];
-    }
+  if (l < nch) sum_rows<MAX>(B, ldb, rows, g, G, l, v, t);
   for (int off = lp; off < 64; off <<= 1)
 #pragma unroll
     for (int e = 0; e < 8; ++e) t[e] += __shfl_xor(t[e], off);
@@ -626,9 +660,9 @@ __device__ __forceinline__ void mv_cols(const F *B, int ldb, int rows, int cols,
 }
 
 // out[c] = sum_i B[i][c] v[i] (i < rows, c < cols) by one wavefront: lane
-// l of a group of lp takes the 8-column chunk l of the rows g, g + G, ..., four
-// rows' loads in flight; the groups' partial sums are reduced by shuffles.
-template <typename F>
+// l of a group of lp takes the 8-column chunk l of the rows g, g + G, ...; the
+// groups' partial sums are reduced by shuffles.
+template <int MAX, typename F>
 __device__ __forceinline__ void wave_mv_cols(const F *B, int ldb, int rows, int cols,
                                              const double *v, double *out) {
   const int lane = threadIdx.x & 63;
@@ -638,16 +672,7 @@ __device__ __forceinline__ void wave_mv_cols(const F *B, int ldb, int rows, int 
   double t[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) t[e] = 0.0;
-  if (l < nch)
-    for (int i = g; i < rows; i += 4 * G) {
-      double a[4][8];
-      load_rows4(B, ldb, rows, i, G, l, a);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i + u * G < rows)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t[e] += a[u][e] * v[i + u * G];
-    }
+  if (l < nch) sum_rows<MAX>(B, ldb, rows, g, G, l, v, t);
   for (int off = lp; off < 64; off <<= 1)
 #pragma unroll
     for (int e = 0; e < 8; ++e) t[e] += __shfl_xor(t[e], off);
@@ -659,7 +684,7 @@ __device__ __forceinline__ void wave_mv_cols(const F *B, int ldb, int rows, int 
 
 // Up, leaf level, four leaves per work-group (one per wavefront):
 // xh[b][L][t] = B^T x_in[perm[lo..lo+n)] (B = V, or U if trans).
-template <typename F>
+template <typename F, int MAX>
 __global__ __launch_bounds__(WG) void k_hbs_up_leaf4(const HbsNodeDev *__restrict__ nodes, int nl,
                                                      const F *__restrict__ fac, size_t bstride,
                                                      const int *__restrict__ perm,
@@ -678,12 +703,12 @@ __global__ __launch_bounds__(WG) void k_hbs_up_leaf4(const HbsNodeDev *__restric
   }
   __syncthreads();
   if (has)
-    wave_mv_cols(fac + b * bstride + (trans ? N.pU : N.pV), N.ldr, N.n, N.r, v[w],
+    wave_mv_cols<MAX>(fac + b * bstride + (trans ? N.pU : N.pV), N.ldr, N.n, N.r, v[w],
                  hat + b * hstride + hoff + N.roff);
 }
 
 // Up, internal level: xh[b][d][t] = B^T xh[b][d+1][children].
-template <typename F>
+template <typename F, int MAX>
 __global__ __launch_bounds__(WG) void k_hbs_up(const HbsNodeDev *__restrict__ nodes,
                                                const F *__restrict__ fac, size_t bstride,
                                                double *__restrict__ hat, size_t hstride,
@@ -695,13 +720,13 @@ __global__ __launch_bounds__(WG) void k_hbs_up(const HbsNodeDev *__restrict__ no
   for (int i = threadIdx.x; i < N.n; i += WG) v[i] = in[i];
   for (int c = threadIdx.x; c < N.r; c += WG) out[c] = 0.0;
   __syncthreads();
-  mv_cols(fac + b * bstride + (trans ? N.pU : N.pV), N.ldr, N.n, N.r, v, out, red);
+  mv_cols<MAX>(fac + b * bstride + (trans ? N.pU : N.pV), N.ldr, N.n, N.r, v, out, red);
   double *h = hat + b * hstride + hoff + N.roff;
   for (int c = threadIdx.x; c < N.r; c += WG) h[c] = out[c];
 }
 
 // Root: yh[b][1] = D_root xh[b][1] (or D_root^T).
-template <typename F>
+template <typename F, int MAX>
 __global__ __launch_bounds__(WG) void k_hbs_root(const HbsNodeDev *__restrict__ root,
                                                  const F *__restrict__ fac, size_t bstride,
                                                  double *__restrict__ hat, size_t hstride,
@@ -717,9 +742,9 @@ __global__ __launch_bounds__(WG) void k_hbs_root(const HbsNodeDev *__restrict__ 
   __syncthreads();
   const F *D = fac + b * bstride + R.pD;
   if (trans)
-    mv_cols(D, R.ldn, R.n, R.n, v, out, red);
+    mv_cols<MAX>(D, R.ldn, R.n, R.n, v, out, red);
   else
-    mv_rows(D, R.ldn, R.n, R.n, v, out);
+    mv_rows<MAX>(D, R.ldn, R.n, R.n, v, out);
   __syncthreads();
   double *o = hat + b * hstride + hoff_y;
   for (int i = threadIdx.x; i < R.n; i += WG) o[i] = out[i];
@@ -727,7 +752,7 @@ __global__ __launch_bounds__(WG) void k_hbs_root(const HbsNodeDev *__restrict__ 
 
 // Down, internal level d: yh[b][d+1][children] = B' yh[b][d][t] + D xh[b][d+1][children]
 // (B' = U, or V if trans; D or D^T).
-template <typename F>
+template <typename F, int MAX>
 __global__ __launch_bounds__(WG) void k_hbs_down(const HbsNodeDev *__restrict__ nodes,
                                                  const F *__restrict__ fac, size_t bstride,
                                                  double *__restrict__ hat, size_t hstride,
@@ -744,20 +769,20 @@ __global__ __launch_bounds__(WG) void k_hbs_down(const HbsNodeDev *__restrict__ 
   }
   __syncthreads();
   const F *fb = fac + b * bstride;
-  mv_rows(fb + (trans ? N.pV : N.pU), N.ldr, N.n, N.r, vy, out);
+  mv_rows<MAX>(fb + (trans ? N.pV : N.pU), N.ldr, N.n, N.r, vy, out);
   __syncthreads();
   if (trans)
-    mv_cols(fb + N.pD, N.ldn, N.n, N.n, vx, out, red);
+    mv_cols<MAX>(fb + N.pD, N.ldn, N.n, N.n, vx, out, red);
   else
-    mv_rows(fb + N.pD, N.ldn, N.n, N.n, vx, out);
+    mv_rows<MAX>(fb + N.pD, N.ldn, N.n, N.n, vx, out);
   __syncthreads();
   for (int i = threadIdx.x; i < N.n; i += WG) hb[hoff_yc + N.coff + i] = out[i];
 }
 
 // out[i] = sum_c A[i][c] v[c] (i < rows, c < cols) by one wavefront: a
-// group of lp lanes per row, eight entries per lane, four rows' loads in flight,
-// a row's partial sums reduced by shuffles.
-template <typename F>
+// group of lp lanes per row, eight entries per lane, a row's partial sums
+// reduced by shuffles.
+template <int MAX, typename F>
 __device__ __forceinline__ void wave_mv_rows(const F *A, int lda, int rows, int cols,
                                              const double *v, double *out) {
   const int lane = threadIdx.x & 63;
@@ -766,15 +791,20 @@ __device__ __forceinline__ void wave_mv_rows(const F *A, int lda, int rows, int 
   const int g = lane / lp, l = lane % lp, G = 64 / lp;
   double x[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? v[8 * l + e] : 0.0;
-  for (int i0 = 0; i0 < rows; i0 += 4 * G) {
-    double t[4];
-    dot_rows4(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
-    if (l == 0)
+  for (int e = 0; e < 8; ++e) x[e] = v[8 * l + e];  // inside v: l < 32
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i0 + u * G + g < rows) out[i0 + u * G + g] = t[u];
-  }
+  for (int e = 0; e < 8; ++e) x[e] = 8 * l + e < cols ? x[e] : 0.0;
+  with_rows<MAX>(rows, G, [&](auto n) {
+    constexpr int U = decltype(n)::value;
+    for (int i0 = 0; i0 < rows; i0 += U * G) {
+      double t[U];
+      dot_rows<U>(A, lda, rows, cols, i0 + g, G, l, lp, x, t);
+      if (l == 0)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * G + g < rows) out[i0 + u * G + g] = t[u];
+    }
+  });
 }
 
 // Leaves: for output interface jo (blockIdx.y + 1) and leaf t,
@@ -784,7 +814,7 @@ __device__ __forceinline__ void wave_mv_rows(const F *A, int lda, int rows, int 
 // basis product (h = 0) or dense product (h = 1) into its own LDS slice;
 // the slices are summed after one barrier.  The first leaf's work-group also
 // copies the padding entries (M .. ld - 1) of y_jo from x_jo.
-template <typename F>
+template <typename F, int MAX>
 __global__ __launch_bounds__(WG) void k_hbs_leaf_out(
     const HbsNodeDev *__restrict__ nodes, const F *__restrict__ fac, size_t bstride,
     const int *__restrict__ perm, const double *__restrict__ x, double *__restrict__ y, int M,
@@ -822,11 +852,11 @@ __global__ __launch_bounds__(WG) void k_hbs_leaf_out(
   if (act) {
     const F *fb = fac + b * bstride;
     if (h == 0)
-      wave_mv_rows(fb + (trans ? N.pV : N.pU), N.ldr, N.n, N.r, vin[w], part[w]);
+      wave_mv_rows<MAX>(fb + (trans ? N.pV : N.pU), N.ldr, N.n, N.r, vin[w], part[w]);
     else if (trans)
-      wave_mv_cols(fb + N.pD, N.ldn, N.n, N.n, vin[w], part[w]);
+      wave_mv_cols<MAX>(fb + N.pD, N.ldn, N.n, N.n, vin[w], part[w]);
     else
-      wave_mv_rows(fb + N.pD, N.ldn, N.n, N.n, vin[w], part[w]);
+      wave_mv_rows<MAX>(fb + N.pD, N.ldn, N.n, N.n, vin[w], part[w]);
   }
   __syncthreads();
   const double *xo = x + (size_t)(jo - 1) * ld;
@@ -1106,6 +1136,7 @@ int hbs_compress(ddst_op *op, int k, int q, int leaf, int dtype, const double *o
     H->lv.assign(L + 1, {});
     size_t off = 0, poff = 0;
     H->nhat.assign(L + 1, 0);
+    for (const auto &v : nn) H->rows.push_back(*std::max_element(v.begin(), v.end()));
     for (int d = L; d >= 1; --d) {
       int roff = 0, coff = 0;
       for (size_t t = 0; t < nn[d].size(); ++t) {
@@ -1399,28 +1430,31 @@ void hbs_apply_t(const ddst_op *op, const double *x, double *y, int trans, hipSt
     BCHK(hipMemcpyAsync(y, x, (size_t)op->n_ds * ld * 8, hipMemcpyDeviceToDevice, st));
     return;
   }
+  auto many = [&](int d) { return hbs_rows_in_flight(H->rows[d]) > 2; };
   if (L >= 1) {
     const unsigned nl = (unsigned)H->lv[L].size();
-    hipLaunchKernelGGL(k_hbs_up_leaf4<F>, dim3((nl + WG / 64 - 1) / (WG / 64), nb), dim3(WG), 0,
-                       st, nodes(L), (int)nl, fac, bs, H->d_perm, x, ld, H->hat, hs,
-                       H->hoff[2 * L], trans);
+    hipLaunchKernelGGL((many(L) ? k_hbs_up_leaf4<F, 4> : k_hbs_up_leaf4<F, 2>),
+                       dim3((nl + WG / 64 - 1) / (WG / 64), nb), dim3(WG), 0, st, nodes(L),
+                       (int)nl, fac, bs, H->d_perm, x, ld, H->hat, hs, H->hoff[2 * L], trans);
     for (int d = L - 1; d >= 1; --d)
-      hipLaunchKernelGGL(k_hbs_up<F>, dim3((unsigned)H->lv[d].size(), nb), dim3(WG), 0, st,
-                         nodes(d), fac, bs, H->hat, hs, H->hoff[2 * d], H->hoff[2 * (d + 1)],
-                         trans);
-    hipLaunchKernelGGL(k_hbs_root<F>, dim3(nb), dim3(WG), 0, st, nodes(0), fac, bs, H->hat, hs,
-                       H->hoff[2], H->hoff[3], trans);
+      hipLaunchKernelGGL((many(d) ? k_hbs_up<F, 4> : k_hbs_up<F, 2>),
+                         dim3((unsigned)H->lv[d].size(), nb), dim3(WG), 0, st, nodes(d), fac, bs,
+                         H->hat, hs, H->hoff[2 * d], H->hoff[2 * (d + 1)], trans);
+    hipLaunchKernelGGL((many(0) ? k_hbs_root<F, 4> : k_hbs_root<F, 2>), dim3(nb), dim3(WG), 0, st,
+                       nodes(0), fac, bs, H->hat, hs, H->hoff[2], H->hoff[3], trans);
     for (int d = 1; d <= L - 1; ++d)
-      hipLaunchKernelGGL(k_hbs_down<F>, dim3((unsigned)H->lv[d].size(), nb), dim3(WG), 0, st,
-                         nodes(d), fac, bs, H->hat, hs, H->hoff[2 * (d + 1)], H->hoff[2 * d + 1],
+      hipLaunchKernelGGL((many(d) ? k_hbs_down<F, 4> : k_hbs_down<F, 2>),
+                         dim3((unsigned)H->lv[d].size(), nb), dim3(WG), 0, st, nodes(d), fac, bs,
+                         H->hat, hs, H->hoff[2 * (d + 1)], H->hoff[2 * d + 1],
                          H->hoff[2 * (d + 1) + 1], trans);
-    hipLaunchKernelGGL(k_hbs_leaf_out<F>, dim3(nl, op->n_ds), dim3(WG), 0, st, nodes(L), fac, bs,
-                       H->d_perm, x, y, op->M, ld, op->n_ds, H->hat, hs, H->hoff[2 * L + 1], 1,
-                       trans);
+    hipLaunchKernelGGL((many(L) ? k_hbs_leaf_out<F, 4> : k_hbs_leaf_out<F, 2>),
+                       dim3(nl, op->n_ds), dim3(WG), 0, st, nodes(L), fac, bs, H->d_perm, x, y,
+                       op->M, ld, op->n_ds, H->hat, hs, H->hoff[2 * L + 1], 1, trans);
   } else {
     // a single cluster: the root block is the whole transfer block
-    hipLaunchKernelGGL(k_hbs_leaf_out<F>, dim3(1, op->n_ds), dim3(WG), 0, st, nodes(0), fac, bs,
-                       H->d_perm, x, y, op->M, ld, op->n_ds, H->hat, hs, (size_t)0, 0, trans);
+    hipLaunchKernelGGL((many(0) ? k_hbs_leaf_out<F, 4> : k_hbs_leaf_out<F, 2>),
+                       dim3(1, op->n_ds), dim3(WG), 0, st, nodes(0), fac, bs, H->d_perm, x, y,
+                       op->M, ld, op->n_ds, H->hat, hs, (size_t)0, 0, trans);
   }
 }
 

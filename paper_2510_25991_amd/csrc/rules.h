@@ -84,4 +84,16 @@ inline bool outer_blocks(int nmat, int ld, size_t esz, bool sym) {
   return esz == 4 && ld >= kOuterRows && nmat * side * side >= (sym ? 2 : 1) * kOuterTiles;
 }
 
+// ---- sampled (HBS) product ------------------------------------------------------
+// Most rows that a group of lanes of the product's kernels takes at a time, for
+// nodes of up to `rows` rows.  Four rows' loads pay for their registers (more
+// than the 64 that leave eight wavefronts on a SIMD) where a group has that many
+// rows.  us, up to four against up to two: leaves of 128 (3D 31, rank 64) BF16
+// 45.0 and 50.3, FP32 46.6 and 55.6, FP64 62.4 and 62.8, transposed 56.8 and
+// 61.7; leaves of 64 (2D 511 on 32 slabs, rank 32) 32.6 and 33.0, 34.3 and 35.0,
+// 39.6 and 38.4; of 32 (2D 1023 on 64, rank 16) 66.4 and 63.5, 67.1 and 64.2,
+// 73.2 and 69.7.  (Four rows always, also where a group has one: 75.9, 74.8 and
+// 89.4; one row at a time: 63.4, 64.0 and 70.5, leaves of 128 80.5 to 99.4.)
+inline int hbs_rows_in_flight(int rows) { return rows > 64 ? 4 : 2; }
+
 }  // namespace ddst

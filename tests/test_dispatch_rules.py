@@ -55,3 +55,9 @@ def test_outer_blocks_take_the_faster_way(tmp_path, dim, n, slabs, sym, outer):
 def test_products_take_the_faster_tiles(tmp_path, njobs, ld, big):
     got = evaluate(tmp_path, f'std::printf("%d", (int)gemm_big_tiles({njobs}, {ld}));')
     assert got == [str(big)]
+
+
+@pytest.mark.parametrize("rows,most", [(1, 2), (32, 2), (64, 2), (65, 4), (128, 4)])
+def test_rows_in_flight_of_the_sampled_product(tmp_path, rows, most):
+    got = evaluate(tmp_path, f'std::printf("%d", hbs_rows_in_flight({rows}));')
+    assert got == [str(most)]

@@ -101,3 +101,30 @@ def test_transposed_products_of_symmetric_builds(dim, n, slabs):
     for op in ops:
         op.close()
     assert worst <= fp32_block_tol((n + 1) // slabs, n ** (dim - 1)) * scale
+
+
+@pytest.mark.parametrize("factors", ["bf16", "fp32", "fp64"])
+@pytest.mark.parametrize("dim,n,slabs,rank,leaf", [(2, 127, 4, 1, 1), (2, 255, 8, 8, 16),
+                                                   (2, 299, 10, 16, 37), (2, 639, 8, 48, 128),
+                                                   (3, 23, 6, 64, 128)])
+def test_sampled_product_by_node_size(dim, n, slabs, rank, leaf, factors):
+    """y = S x through trees whose nodes hold one to four rows per group of lanes
+    (clusters of one point to 128): the transposed product is the transpose of
+    the plain one, entry by entry (FP64 sums of the same factors: 1e-12)."""
+    print(f"\n[gpu] sampled product {dim}D n={n} rank={rank} leaf={leaf} {factors}", flush=True)
+    op = ddst().Operator(dim, n, slabs, precision="fp32")
+    op.compress_hbs(rank=rank, oversample=10, leaf=leaf, factor_dtype=factors, seed=3)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(2, op.n_ds * op.M, generator=g, device="cuda", dtype=torch.float64)
+    y = op.apply(x[0], which="hbs").reshape(-1)
+    z = op.apply(x[1], which="hbs", transpose=True).reshape(-1)
+    assert abs(float(y @ x[1] - z @ x[0])) <= 1e-12 * float(x[0].norm() * x[1].norm())
+    # column by column against the whole product, at both ends and between
+    cols = [0, 1, op.M // 2, op.M - 1, op.M, op.n_ds * op.M - 1]
+    e = torch.zeros_like(x[0])
+    for c in cols:
+        e.zero_()
+        e[c] = 1.0
+        col = op.apply(e, which="hbs").reshape(-1)
+        assert abs(float(col @ x[1]) - float(z[c])) <= 1e-12 * float(x[1].norm())
+    op.close()
