@@ -451,10 +451,14 @@ __global__ __launch_bounds__(64 * W * H) void k_gemv_mfma(const GemvJob *__restr
 
 // Transposed product, partial sums over row chunks:
 // part[(job*nchunk + chunk)*ld + c] = sum_{r in chunk} G[r,c] xe[r] + G2[r,c] x3[r]
-// Work-group (chunk, job, z): 256 columns, a quarter of the chunk's rows per
+// Work-group (z, chunk, job): 256 columns, a quarter of the chunk's rows per
 // wavefront, eight rows' loads in flight; rows and columns of padding are not
-// read.  24 planes of 768 rows in FP32: 23 us and 8 for the reduction with
-// chunks of 32 rows and one row at a time over all columns.
+// read.  The work-groups of a chunk's columns follow one another, so that whole
+// rows are read at a time: with all chunks of all jobs for the first 256
+// columns, then for the next, large launches took longer than one row at a
+// time over all columns and chunks of 32 rows (both passes, FP64 planes of 1023
+// rows on 64 slabs: 208 us, so 173, one row at a time 192; 24 planes of 767 rows
+// in FP32 20, 20 and 31).
 template <typename T>
 __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__ jobs, int ld,
                                                      int M, int rows_per_chunk,
@@ -462,11 +466,11 @@ __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__
   constexpr int U = 8;
   __shared__ double red[4][256];
   extern __shared__ double sh[];
-  const int chunk = blockIdx.x, job = blockIdx.y, nchunk = gridDim.x;
+  const int chunk = blockIdx.y, job = blockIdx.z, nchunk = gridDim.y;
   const GemvJob J = jobs[job];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = chunk * rows_per_chunk, rn = max(0, min(rows_per_chunk, M - r0));
-  const int c = blockIdx.z * 256 + lane * 4;
+  const int c = blockIdx.x * 256 + lane * 4;
   double *xs[2] = {sh, sh + rows_per_chunk};
   for (int r = threadIdx.x; r < rn; r += 256) {
     double v = J.x1 ? gp(J.x1)[r0 + r] : 0.0;
@@ -502,7 +506,7 @@ __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__
 #pragma unroll
   for (int e = 0; e < 4; ++e) red[wave][lane * 4 + e] = s[e];
   __syncthreads();
-  const int cc = blockIdx.z * 256 + threadIdx.x;
+  const int cc = blockIdx.x * 256 + threadIdx.x;
   if (cc < ld)
     part[((size_t)job * nchunk + chunk) * ld + cc] =
         (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
@@ -1286,7 +1290,7 @@ void launch_gemv(const GemvJob *jobs, int njobs, int ld, int M, int transpose, d
     const int nchunk = std::min(ld / 64, 64);  // 64 rows and more
     const int rpc = ld / nchunk;
     static_assert(kGemvChunk <= 64, "the partial sums fit the workspace");
-    hipExtLaunchKernelGGL(k_gemv_t_part<T>, dim3(nchunk, njobs, (ld + 255) / 256), dim3(256),
+    hipExtLaunchKernelGGL(k_gemv_t_part<T>, dim3((ld + 255) / 256, nchunk, njobs), dim3(256),
                           2 * rpc * sizeof(double), s, ps.a, nullptr, 0, jobs, ld, M, rpc,
                           partial);
     hipExtLaunchKernelGGL(k_gemv_t_reduce, dim3(nblk(ld), njobs), dim3(256), 0, s, nullptr, ps.b,
