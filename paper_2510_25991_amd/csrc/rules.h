@@ -96,4 +96,20 @@ inline bool outer_blocks(int nmat, int ld, size_t esz, bool sym) {
 // 89.4; one row at a time: 63.4, 64.0 and 70.5, leaves of 128 80.5 to 99.4.)
 inline int hbs_rows_in_flight(int rows) { return rows > 64 ? 4 : 2; }
 
+// ---- matrix-vector products ----------------------------------------------------
+// Whether an FP32 launch over njobs matrices takes 1024 columns of its two rows
+// at a time instead of 512.  Where a launch is long, its last round of
+// work-groups counts for less than the loads in flight of each wavefront.  us
+// with 512 and 1024 columns, by bytes of the matrices (planes of a sweep):
+//   2D 511 on 64 slabs    67 MB   19.7 20.2    3D 47 on 6    127 MB   25.2 26.4
+//   2D 1023 on 32 slabs  134 MB   29.2 28.8    3D 63 on 4    252 MB   48.6 48.1
+//   2D 1023 on 64 slabs  268 MB   75.8 69.3    2D 2047 on 16 268 MB   50.3 47.0
+//   2D 1023 on 128 slabs 537 MB    164  160
+// FP64, twice the loads per column: 152 and 149 at 537 MB, 95.5 and 96.5 at 2047
+// on 16 slabs, so 512.
+constexpr double kGemvWideBytes = 192e6;
+inline bool gemv_wide(int njobs, int ld) {
+  return 4.0 * njobs * ld * ld >= kGemvWideBytes;
+}
+
 }  // namespace ddst

@@ -189,23 +189,24 @@ __device__ __forceinline__ void ld4(const T *p, double *o) {
 }
 
 // out[r] = w[r] + alpha * (G[r,:] (x1 - e.*x2) + G2[r,:] x3); kGemvRows rows per
-// work-group.  HBM-bound: each wavefront owns kGemvR rows and takes kGemvCh
-// columns of a matrix at a time, all its 16-byte loads before using any (no
-// branches between them: columns past the chunk re-read an in-bounds address
-// and meet x = 0); the first loads are issued before x, staged in LDS kGemvX
-// columns at a time, which they do not depend on.  Rows and columns that are padding are not read.
-// Two rows and 512 columns: little per wavefront, but six and more wavefronts
-// per SIMD, whose number evens out the last round of work-groups.  Planes of a
-// sweep over 1023^2 on 32 slabs, 134 MB: 33 us with four rows and 1024
-// columns, 28 with these (with one row 32, with eight 34); FP64 79 and 63.
-constexpr int kGemvR = 2, kGemvRows = 4 * kGemvR, kGemvCh = 512, kGemvX = 1024;
-template <typename T>
+// work-group.  HBM-bound: each wavefront owns kGemvR rows and takes CH columns
+// of a matrix at a time, all its 16-byte loads before using any (no branches
+// between them: columns past the chunk re-read an in-bounds address and meet
+// x = 0); the first loads are issued before x, staged in LDS kGemvX columns at a
+// time, which they do not depend on.  Rows and columns that are padding are not
+// read.  Two rows and 512 columns: little per wavefront, but six and more
+// wavefronts per SIMD, whose number evens out the last round of work-groups; in
+// large FP32 launches 1024 (gemv_wide, rules.h).  Planes of a sweep over 1023^2
+// on 32 slabs, 134 MB: 33 us with four rows and 1024 columns, 28 with these (with
+// one row 32, with eight 34); FP64 79 and 63.
+constexpr int kGemvR = 2, kGemvRows = 4 * kGemvR, kGemvX = 1024;
+template <int CH, typename T>
 __device__ __forceinline__ void gemv_rows_load(const T *M, int ld, int cn, int lane,
-                                               T (&g)[kGemvR][kGemvCh / 256][4]) {
+                                               T (&g)[kGemvR][CH / 256][4]) {
 #pragma unroll
   for (int q = 0; q < kGemvR; ++q)
 #pragma unroll
-    for (int i = 0; i < kGemvCh / 256; ++i) {
+    for (int i = 0; i < CH / 256; ++i) {
       const int c = lane * 4 + 256 * i;
       const T *src = M + (size_t)q * ld + (c < cn ? c : 0);
       constexpr int V = 16 / sizeof(T);
@@ -217,12 +218,12 @@ __device__ __forceinline__ void gemv_rows_load(const T *M, int ld, int cn, int l
       }
     }
 }
-// x: kGemvCh doubles in LDS, zero past the chunk
-template <typename T>
-__device__ __forceinline__ void gemv_rows_fma(const T (&g)[kGemvR][kGemvCh / 256][4],
+// x: CH doubles in LDS, zero past the chunk
+template <int CH, typename T>
+__device__ __forceinline__ void gemv_rows_fma(const T (&g)[kGemvR][CH / 256][4],
                                               const double *x, int lane, double (&acc)[kGemvR]) {
 #pragma unroll
-  for (int i = 0; i < kGemvCh / 256; ++i) {
+  for (int i = 0; i < CH / 256; ++i) {
     const int c = lane * 4 + 256 * i;
     const double x0 = x[c], x1 = x[c + 1], x2 = x[c + 2], x3 = x[c + 3];
 #pragma unroll
@@ -232,7 +233,7 @@ __device__ __forceinline__ void gemv_rows_fma(const T (&g)[kGemvR][kGemvCh / 256
   }
 }
 
-template <typename T>
+template <int CH, typename T>
 __device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, int ld, int M,
                                             double alpha) {
   __shared__ double xs[2][kGemvX];
@@ -258,16 +259,16 @@ __device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, in
   const T *first = G ? G : G2;
   const int mc = min(ld, (M + 3) & ~3);  // whole 16-byte loads
   const int x0 = G ? 0 : 1;              // the first matrix's entries
-  T g[kGemvR][kGemvCh / 256][4];
+  T g[kGemvR][CH / 256][4];
   for (int c0 = 0; c0 < mc; c0 += kGemvX) {
     const int xn = min(kGemvX, mc - c0);
-    const int steps = (xn + kGemvCh - 1) / kGemvCh << two;
+    const int steps = (xn + CH - 1) / CH << two;
     auto load = [&](int t) {
-      const int c = (t >> two) * kGemvCh;
-      gemv_rows_load<T>((t & two ? G2 : first) + ro + c0 + c, ld, xn - c, lane, g);
+      const int c = (t >> two) * CH;
+      gemv_rows_load<CH, T>((t & two ? G2 : first) + ro + c0 + c, ld, xn - c, lane, g);
     };
     auto use = [&](int t) {
-      gemv_rows_fma<T>(g, xs[t & two ? 1 : x0] + (t >> two) * kGemvCh, lane, acc);
+      gemv_rows_fma<CH, T>(g, xs[t & two ? 1 : x0] + (t >> two) * CH, lane, acc);
     };
     load(0);
     if (c0 > 0) __syncthreads();  // the previous columns' x is no longer read
@@ -300,13 +301,14 @@ __device__ __forceinline__ void gemv_n_body(const GemvJob *__restrict__ jobs, in
   }
 }
 
+template <int CH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_gemv_n_f32(
     const GemvJob *__restrict__ jobs, int ld, int M, double alpha) {
-  gemv_n_body<float>(jobs, ld, M, alpha);
+  gemv_n_body<CH, float>(jobs, ld, M, alpha);
 }
 __global__ __launch_bounds__(256) void k_gemv_n_f64(const GemvJob *__restrict__ jobs, int ld,
                                                     int M, double alpha) {
-  gemv_n_body<double>(jobs, ld, M, alpha);
+  gemv_n_body<512, double>(jobs, ld, M, alpha);
 }
 
 // Several right-hand sides per launch, on the matrix cores: vector v of a job
@@ -1283,7 +1285,9 @@ void launch_gemv(const GemvJob *jobs, int njobs, int ld, int M, int transpose, d
   if (njobs <= 0) return;
   const ProfSpan ps = prof_open(KK_GEMV);
   if (!transpose) {
-    auto kern = sizeof(T) == 4 ? k_gemv_n_f32 : k_gemv_n_f64;
+    auto kern = sizeof(T) == 8           ? k_gemv_n_f64
+                : gemv_wide(njobs, ld) ? k_gemv_n_f32<1024>
+                                       : k_gemv_n_f32<512>;
     hipExtLaunchKernelGGL(kern, dim3(ld / kGemvRows, njobs), dim3(256), 0, s, ps.a, ps.b, 0, jobs,
                           ld, M, alpha);
   } else {

@@ -61,3 +61,11 @@ def test_products_take_the_faster_tiles(tmp_path, njobs, ld, big):
 def test_rows_in_flight_of_the_sampled_product(tmp_path, rows, most):
     got = evaluate(tmp_path, f'std::printf("%d", hbs_rows_in_flight({rows}));')
     assert got == [str(most)]
+
+
+@pytest.mark.parametrize("njobs,ld,wide", [(1, 128, 0), (64, 512, 0), (32, 1024, 0), (6, 2304, 0),
+                                           (64, 1024, 1), (128, 1024, 1), (16, 2048, 1),
+                                           (40000, 16256, 1)])
+def test_columns_of_the_matrix_vector_product(tmp_path, njobs, ld, wide):
+    got = evaluate(tmp_path, f'std::printf("%d", (int)gemv_wide({njobs}, {ld}));')
+    assert got == [str(wide)]

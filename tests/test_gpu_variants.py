@@ -128,3 +128,24 @@ def test_sampled_product_by_node_size(dim, n, slabs, rank, leaf, factors):
         col = op.apply(e, which="hbs").reshape(-1)
         assert abs(float(col @ x[1]) - float(z[c])) <= 1e-12 * float(x[1].norm())
     op.close()
+
+
+@pytest.mark.parametrize("n,slabs", [(1023, 64), (1151, 48), (899, 60), (2047, 16)])
+def test_wide_matrix_vector_products(n, slabs):
+    """FP32 products of launches with 1024 columns at a time (the last of 1023, 127,
+    899 and 1023 columns), against the blocks themselves: FP64 sums, 1e-12."""
+    print(f"\n[gpu] wide products n={n} slabs={slabs}", flush=True)
+    op = ddst().Operator(2, n, slabs, bvec=(5.0, 1.0, 0.0), precision="fp32", keep_factors=False)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    J, M = op.n_ds, op.M
+    x = torch.randn(J, M, generator=g, device="cuda", dtype=torch.float64)
+    out = op.apply(x.reshape(-1)).reshape(J, M)
+    for j in (0, 1, J // 2, J - 1):
+        a, b = op.transfer(j + 1)
+        y = x[j].clone()
+        if j > 0:
+            y -= (a * x[j - 1]).sum(1)
+        if j < J - 1:
+            y -= (b * x[j + 1]).sum(1)
+        assert float((out[j] - y).abs().max()) <= 1e-12 * float(y.abs().max())
+    op.close()
