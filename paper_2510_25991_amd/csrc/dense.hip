@@ -506,13 +506,18 @@ __device__ __forceinline__ bool leaf_invert16(double (&v)[4]) {
 // with three wavefronts of tiles and the leaf on a SIMD of its own, 38).
 // With Rprev and Cprev (the previous step's panels), that step's update of
 // the block is applied first.
+// WPE: wavefronts per SIMD to fit.  Its 181 registers (FP32) leave room for one
+// work-group on a CU; with WPE 3 (168, one of them spilled) and exactly half of
+// the LDS two fit, for launches of more matrices than CUs: a build of 319
+// matrices of 639 rows without transfer blocks takes 10.2 ms with one on a CU
+// (246 us a pivot launch, in two rounds), 9.7 with two.
 constexpr int kLeaf = 16;
 constexpr int kCqS = 20;        // LDS row stride of the column block (doubles)
 constexpr int kRqS = kNB + 16;  // LDS row stride of the row block (doubles)
 static_assert(kNB == 128, "the register layout below assumes 128-wide pivots");
 
-template <typename T, bool ANY_SIGN>
-__global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ mats,
+template <typename T, bool ANY_SIGN, int WPE>
+__global__ __launch_bounds__(320, WPE) void k_gj_pivot(void *const *__restrict__ mats,
                                                      T *__restrict__ Pinv,
                                                      const T *__restrict__ Rprev,
                                                      const T *__restrict__ Cprev, int ld, int o,
@@ -523,7 +528,7 @@ __global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ m
   __shared__ __align__(16) double lds[kCqN + kRqN];
   double (*Cq)[kNB][kCqS] = reinterpret_cast<double (*)[kNB][kCqS]>(lds);
   double (*Rq)[kLeaf][kRqS] = reinterpret_cast<double (*)[kLeaf][kRqS]>(lds + kCqN);
-  __shared__ double Lt[kLeaf][kLeaf + 1];  // the next leaf
+  __shared__ double Lt[kLeaf][kLeaf];  // the next leaf, entry (i, j) at [i][i ^ j]
   __shared__ double Lv[4][64];             // the inverted leaf, in leaf_invert16's layout
   const int b = blockIdx.x, l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int lr = l >> 4, lc = l & 15;
@@ -536,7 +541,7 @@ __global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ m
       __syncthreads();  // the leaf q is in Lt
       double v[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) v[c] = Lt[lc][lr + 4 * c];
+      for (int c = 0; c < 4; ++c) v[c] = Lt[lc][lc ^ (lr + 4 * c)];
       ok = leaf_invert16<ANY_SIGN>(v) && ok;
 #pragma unroll
       for (int c = 0; c < 4; ++c) Lv[c][l] = v[c];
@@ -567,6 +572,7 @@ __global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ m
     // second set of FP64 accumulators would not fit next to it).  Operands
     // are staged through LDS in KS-deep slices.
     static_assert(2 * KS * LW * sizeof(T) <= sizeof(lds), "operand slices fit the LDS");
+    static_assert(sizeof(lds) + sizeof(Lt) + sizeof(Lv) <= 80 * 1024, "two work-groups a CU");
     T (*As)[LW] = reinterpret_cast<T (*)[LW]>(lds);
     T (*Bs)[LW] = reinterpret_cast<T (*)[LW]>(reinterpret_cast<T *>(lds) + KS * LW);
     const T *A = Cprev + ((size_t)b * lw + p * kNB) * kNB;  // rows p, kNB wide
@@ -630,7 +636,7 @@ __global__ __launch_bounds__(320, 2) void k_gj_pivot(void *const *__restrict__ m
   }
   auto put_leaf = [&](const f64x4 &x) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) Lt[4 * r + lr][lc] = x[r];
+    for (int r = 0; r < 4; ++r) Lt[4 * r + lr][(4 * r + lr) ^ lc] = x[r];
   };
   // row block q and column block q (its owner holds it as jj = q & 1) to LDS
   auto put_blocks = [&](int q) {
@@ -1562,6 +1568,11 @@ static hipError_t invert_block(void *const *mats, int nmat, int ld, int o, int n
     if ((e = (call)) != hipSuccess) return e; \
   } while (0)
   const bool look = nt >= kLookAhead;
+  constexpr int DENSE = sizeof(T) == 4 ? 3 : 2;  // FP64 takes 248 registers
+  auto *pivot = pivots_share_cus(nmat) ? (any_sign ? k_gj_pivot<T, true, DENSE>
+                                                   : k_gj_pivot<T, false, DENSE>)
+                                       : (any_sign ? k_gj_pivot<T, true, 2>
+                                                   : k_gj_pivot<T, false, 2>);
   for (int p = 0; p < nt; ++p) {
     const bool fused = p > 0 && look;  // the pivot kernel applies step p - 1 to its block
     if (p > 0 && !look) {
@@ -1579,8 +1590,7 @@ static hipError_t invert_block(void *const *mats, int nmat, int ld, int o, int n
       GJCHK(hipEventRecord(gs.upd, gs.h));
     }
     ProfSpan ps = prof_open(KK_GJ_PANEL);
-    hipExtLaunchKernelGGL(any_sign ? k_gj_pivot<T, true> : k_gj_pivot<T, false>, dim3(nmat),
-                          dim3(320), 0, s, ps.a, ps.b, 0, mats, PinvT,
+    hipExtLaunchKernelGGL(pivot, dim3(nmat), dim3(320), 0, s, ps.a, ps.b, 0, mats, PinvT,
                           fused ? (const T *)Rb[(p - 1) & 1] : nullptr,
                           (const T *)Cb[(p - 1) & 1], ld, o, lw, p, M, flag);
     prof_close(ps, KK_GJ_PANEL, (fused ? 4.0 : 2.0) * nmat * (double)kNB * kNB * kNB);

@@ -84,6 +84,13 @@ inline bool outer_blocks(int nmat, int ld, size_t esz, bool sym) {
   return esz == 4 && ld >= kOuterRows && nmat * side * side >= (sym ? 2 : 1) * kOuterTiles;
 }
 
+// Whether the pivots' work-groups (one per matrix) share CUs two by two: where
+// there are more of them than CUs, a second round takes as long as the first.
+// With fewer, the registers that this costs buy nothing (builds of 15 to 255
+// matrices within 2% either way).
+constexpr int kCus = 256;
+inline bool pivots_share_cus(int nmat) { return nmat > kCus; }
+
 // ---- sampled (HBS) product ------------------------------------------------------
 // Most rows that a group of lanes of the product's kernels takes at a time, for
 // nodes of up to `rows` rows.  Four rows' loads pay for their registers (more

@@ -69,3 +69,9 @@ def test_rows_in_flight_of_the_sampled_product(tmp_path, rows, most):
 def test_columns_of_the_matrix_vector_product(tmp_path, njobs, ld, wide):
     got = evaluate(tmp_path, f'std::printf("%d", (int)gemv_wide({njobs}, {ld}));')
     assert got == [str(wide)]
+
+
+def test_pivots_share_cus_beyond_one_each(tmp_path):
+    got = evaluate(tmp_path, 'std::printf("%d %d %d", (int)pivots_share_cus(63), '
+                             "(int)pivots_share_cus(256), (int)pivots_share_cus(257));")
+    assert got == ["0", "0", "1"]

@@ -149,3 +149,21 @@ def test_wide_matrix_vector_products(n, slabs):
             y -= (b * x[j + 1]).sum(1)
         assert float((out[j] - y).abs().max()) <= 1e-12 * float(y.abs().max())
     op.close()
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("batch,ld,M", [(256, 128, 100), (257, 128, 100), (300, 256, 200),
+                                        (260, 640, 520)])
+def test_more_matrices_than_cus(batch, ld, M, symmetric):
+    """Inverses in FP32 with the pivots' work-groups one and two on a CU: the same
+    arithmetic, so the inverses of one matrix by both are equal."""
+    print(f"\n[gpu] inverses {batch} x {ld}", flush=True)
+    one = torch.eye(ld, device="cuda", dtype=torch.float32)
+    one[:M, :M] = plane_schur(M, 0.0 if symmetric else 1.0).float()
+    if symmetric:
+        one[:M, :M] = torch.tril(one[:M, :M]) + torch.tril(one[:M, :M], -1).T
+    few = one.repeat(2, 1, 1)
+    many = one.repeat(batch, 1, 1)
+    ddst().kernel_invert(few, symmetric=symmetric)
+    ddst().kernel_invert(many, symmetric=symmetric)
+    assert torch.equal(many, few[:1].expand_as(many))
