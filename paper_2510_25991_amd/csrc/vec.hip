@@ -575,11 +575,13 @@ constexpr int kDotWaves = 16;  // wavefronts per work-group
 constexpr int kDotVecs = 8;    // basis vectors per wavefront and round
 constexpr int kDotRound = kDotWaves * kDotVecs;
 
-// Entries of the work-group's chunk of `chunk`.  In 32 bits: the compiler takes
-// a uniform 64-bit minimum's select from a condition that its comparison does
-// not set, and the last chunk then came out whole.
-__device__ __forceinline__ int chunk_len(int chunk, size_t len) {
-  return blockIdx.x + 1 < gridDim.x ? chunk : (int)(len - (size_t)blockIdx.x * chunk);
+// Entries of the work-group's chunk of 64 T.  Lengths are multiples of 128
+// (with_dot_width checks), so that only chunks of 256 can be partial.  In 32
+// bits: the compiler takes a uniform 64-bit minimum's select from a condition
+// that its comparison does not set, and the last chunk then came out whole.
+template <int T> __device__ __forceinline__ int chunk_len(size_t len) {
+  if constexpr (128 % (64 * T) == 0) return 64 * T;
+  return blockIdx.x + 1 < gridDim.x ? 64 * T : (int)(len - (size_t)blockIdx.x * 64 * T);
 }
 
 // T entries of v from e0 (FULL: all inside the chunk; else those past its cn
@@ -689,7 +691,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_mgs_update_dots(
     const double *__restrict__ h, double sign, size_t len, int ndot, double *__restrict__ part) {
   __shared__ double red[kDotWaves * 64 * T], ws[64 * T], sh[T];
   const size_t base = (size_t)blockIdx.x * 64 * T;
-  const int cn = chunk_len(64 * T, len);
+  const int cn = chunk_len<T>(len);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const B *v = V + base;
@@ -953,7 +955,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_lag_dots(const B *__restrict
                                                              double *__restrict__ part) {
   constexpr int T = kLagChunk / 64;
   const size_t base = (size_t)blockIdx.x * kLagChunk;
-  const int cn = chunk_len(kLagChunk, len);
+  const int cn = chunk_len<T>(len);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nq = m - 1;
@@ -1105,7 +1107,7 @@ __global__ __launch_bounds__(64 * kDotWaves) void k_lag_update(B *V, size_t stri
                                                                double *__restrict__ part) {
   __shared__ double red[2 * kDotWaves * 64 * T], sh[T];
   const size_t base = (size_t)blockIdx.x * 64 * T;
-  const int cn = chunk_len(64 * T, len);
+  const int cn = chunk_len<T>(len);
   const int tid = threadIdx.x;
   double sum[2][T], r[2] = {0.0, 0.0};
   const double *const coef[2] = {d.dA, d.cf};
@@ -1360,6 +1362,7 @@ void launch_fill(double *y, double v, size_t len, hipStream_t s) {
 namespace {
 // f(std::integral_constant<int, T>) for vectors of len entries
 template <typename F> void with_dot_width(size_t len, F f) {
+  if (len % kTile) throw std::invalid_argument("Krylov passes: length not a multiple of 128");
   switch (dot_width(len)) {
     case 1: return f(std::integral_constant<int, 1>{});
     case 2: return f(std::integral_constant<int, 2>{});

@@ -167,3 +167,47 @@ def test_more_matrices_than_cus(batch, ld, M, symmetric):
     ddst().kernel_invert(few, symmetric=symmetric)
     ddst().kernel_invert(many, symmetric=symmetric)
     assert torch.equal(many, few[:1].expand_as(many))
+
+
+@pytest.mark.parametrize("n,slabs", [(383, 192), (511, 256)])
+def test_fp32_basis_with_a_partial_chunk(n, slabs):
+    """Passes over an FP32 basis of 573 x 128 entries (the last chunk of 256 half
+    full) and of whole chunks, classical and lagged steps: as many refinement
+    passes as with the FP64 basis, and the same solution."""
+    print(f"\n[gpu] FP32 basis n={n} slabs={slabs}", flush=True)
+    mod = ddst()
+    op = mod.Operator(2, n, slabs, bvec=(4.0, 1.0, 0.0), precision="fp64")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    f = torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
+    opts = dict(tol=1e-10, inner_tol=1e-6, max_iter=1500, max_outer=6)
+    u64, _, s64 = op.solve(f, opts=mod.SolveOptions(**opts))
+    u32, _, s32 = op.solve(f, opts=mod.SolveOptions(basis_fp32=True, **opts))
+    op.close()
+    assert s64["gmres_iters"] > 128 * s64["outer_iters"]  # lagged steps on both
+    assert s32["outer_iters"] == s64["outer_iters"]
+    assert float((u32 - u64).abs().max()) <= 1e-9 * float(u64.abs().max())
+
+
+@pytest.mark.parametrize("factors", ["bf16", "fp32"])
+@pytest.mark.parametrize("n,slabs,leaf", [(299, 10, 32), (511, 128, 128), (2303, 8, 128)])
+def test_compressed_product_against_its_transpose(n, slabs, leaf, factors):
+    """y = S x through the compressed blocks (rows at any alignment, planes that do
+    and do not fit LDS) and z = S^T x, which another kernel forms from the same
+    factors: x1.(S x2) = x2.(S^T x1) up to the FP32 sums of both, some 300 terms of
+    norm 1 each."""
+    print(f"\n[gpu] compressed product n={n} leaf={leaf} {factors}", flush=True)
+    op = ddst().Operator(2, n, slabs, bvec=(3.0, 1.0, 0.0), precision="fp32", keep_factors=False)
+    op.compress(tol=1e-5, leaf=leaf, oversample=10, max_rank=100, factor_dtype=factors)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    M, J = op.M, op.n_ds
+    x1 = torch.randn(J * M, generator=g, device="cuda", dtype=torch.float64)
+    z = op.apply(x1, which="hodlr", transpose=True).reshape(-1)
+    for c in (0, 1, leaf - 1, leaf, M // 2, M - 1, M, J * M // 2 + 3, J * M - 1):
+        e = torch.zeros_like(x1)
+        e[c] = 1.0
+        col = op.apply(e, which="hodlr").reshape(-1)
+        assert abs(float(col @ x1) - float(z[c])) <= 300 * 2.0 ** -24 * float(x1.norm())
+    x2 = torch.randn(J * M, generator=g, device="cuda", dtype=torch.float64)
+    y = op.apply(x2, which="hodlr").reshape(-1)
+    assert abs(float(y @ x1 - z @ x2)) <= 300 * 2.0 ** -24 * float(x1.norm() * x2.norm())
+    op.close()
