@@ -83,8 +83,6 @@ struct Contrib {
   int c0, c1;      // input columns (cluster order)
   int rank;        // -1 dense
   long long off_u, off_v;
-  int trans;       // apply the transpose of the stored block
-  int pad_;
 };
 // A contribution to the rows [r0, r1) of a leaf cluster: a dense leaf
 // (rank -1, rows x rows, row stride lds), or the rows roff .. roff + (r1 - r0)
@@ -93,7 +91,7 @@ struct Contrib {
 struct FContrib {
   int in_iface, c0, c1, rank;
   long long off_u, off_v;
-  int trans, roff, rfull, lds;
+  int roff, rfull, lds, pad_;
 };
 
 namespace {
@@ -1423,7 +1421,6 @@ int compress_impl(ddst_op *op, const ddst_compress_opts_t &o, hipStream_t st, in
             c.rank = b.rank;
             c.off_u = (long long)b.off_u;
             c.off_v = (long long)b.off_v;
-            c.trans = dir;
             con.push_back(c);
           }
           jobs.push_back(jb);
@@ -1466,7 +1463,6 @@ int compress_impl(ddst_op *op, const ddst_compress_opts_t &o, hipStream_t st, in
             x.rank = c.rank;
             x.off_u = c.off_u;
             x.off_v = c.off_v;
-            x.trans = c.trans;
             x.roff = roff;
             x.rfull = rfull;
             x.lds = (int)pad8(c.c1 - c.c0);

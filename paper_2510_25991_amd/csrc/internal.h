@@ -124,8 +124,9 @@ void prof_end(int kind, hipStream_t s, double work);
 template <typename T>
 void launch_assemble(const AsmJob *jobs, int njobs, const double *coef, int n, int dim,
                      int M, int ld, hipStream_t s);
-// M (the unpadded size) only enters the algorithmic work recorded by the
-// profiler: 2 M^3 flops per GEMM, 2 M^2 kNB per Gauss-Jordan update.
+// M: the rows and columns that are not padding.  Products take the first M rows,
+// columns and depths only, so what lies past them must be padding (zero in the
+// products' operands, identity in the matrices to invert).
 // C = alpha diag(cscale) A diag(bscale) (cscale null: 1)
 template <typename T>
 void launch_scale_cols(const GemmJob *jobs, int njobs, int ld, double alpha, hipStream_t s);
@@ -133,7 +134,8 @@ void launch_scale_cols(const GemmJob *jobs, int njobs, int ld, double alpha, hip
 template <typename T>
 void launch_gemm(const GemmJob *jobs, int njobs, int ld, int M, double alpha, bool trans_b,
                  hipStream_t s);
-// C = alpha A diag(bscale) B + beta C; bscale: whether the jobs have one
+// C = alpha A diag(bscale) B + beta C (bscale: whether the jobs have one), the
+// form of the C-ABI's unit hook; the build's products are those above
 template <typename T>
 void launch_gemm_full(const GemmJob *jobs, int njobs, int ld, bool bscale, double alpha,
                       double beta, hipStream_t s);

@@ -565,7 +565,7 @@ __global__ void k_fill(double *__restrict__ y, double v, size_t len) {
 // 10^6.  What bounds them is the loads in flight: a work-group takes a chunk of
 // 64 T entries (T per lane) and its 16 wavefronts share the vectors, eight at
 // a time with their loads issued together, so that short vectors still fill
-// the chip.  A classical step's passes over FP32 bases of 15841 entries and
+// the chip.  A classical step's passes over FP32 bases of 15872 entries and
 // about 240 vectors take 4.6 us each; with 256 entries per work-group and
 // every vector in turn, by one thread an entry (updates) or by four
 // wavefronts (products), they took 15 and 19.  T = 1, 2, 4, the largest that
@@ -943,7 +943,7 @@ __global__ __launch_bounds__(256) void k_norm_scale_givens(const double *__restr
 // kLagChunk-entry chunk: part[chunk][i] = V_i . u, part[chunk][m + i] =
 // V_i . w (i < m - 1), part[chunk][m - 1] = u . u, part[chunk][2 m - 1] =
 // u . w.  Work-group (chunk, g): vectors g kDotRound .., eight per wavefront;
-// group 0 also forms the products of u.  FP64 bases of 64449 entries, 500
+// group 0 also forms the products of u.  FP64 bases of 64512 entries, 500
 // vectors on average: 47 us, 5.4 TB/s (54 with chunks of 2048 and 32 vectors
 // per work-group).
 constexpr int kLagChunk = 256;
