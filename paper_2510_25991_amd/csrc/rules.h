@@ -114,9 +114,23 @@ inline int hbs_rows_in_flight(int rows) { return rows > 64 ? 4 : 2; }
 //   2D 1023 on 128 slabs 537 MB    164  160
 // FP64, twice the loads per column: 152 and 149 at 537 MB, 95.5 and 96.5 at 2047
 // on 16 slabs, so 512.
-constexpr double kGemvWideBytes = 192e6;
+constexpr double kGemvLargeBytes = 192e6;
 inline bool gemv_wide(int njobs, int ld) {
-  return 4.0 * njobs * ld * ld >= kGemvWideBytes;
+  return 4.0 * njobs * ld * ld >= kGemvLargeBytes;
+}
+// Whether a transposed launch (partial sums over strips of 256 columns and chunks
+// of rows) runs strip by strip over whole rows, or through all chunks of all
+// matrices for the first strip, then for the next.  The second way reads a
+// quarter of every row at a time, which matters where the matrices come from
+// memory rather than from the last-level cache (256 MB).  us, both passes,
+// sweeps, strips of all chunks first against whole rows:
+//   FP32 2D 1023 on 16 slabs   67 MB   20.6 21.6   FP64 511 on 64   134 MB   45.1 46.5
+//   FP32 2D 1023 on 32 slabs  134 MB   37.1 37.5   FP64 1023 on 32  268 MB   81.5 75.4
+//   FP32 3D 63 on 4 slabs     252 MB   71.6 68.3   FP64 767 on 64   302 MB    111  108
+//   FP32 2D 2047 on 16 slabs  268 MB   70.9 64.5   FP64 1023 on 64  537 MB    208  173
+//   FP32 2D 1023 on 128 slabs 537 MB    210  191   FP64 1023 on 128 1.1 GB    405  358
+inline bool gemv_t_rows(int njobs, int ld, size_t esz) {
+  return (double)esz * njobs * ld * ld >= kGemvLargeBytes;
 }
 
 }  // namespace ddst

@@ -453,26 +453,25 @@ __global__ __launch_bounds__(64 * W * H) void k_gemv_mfma(const GemvJob *__restr
 
 // Transposed product, partial sums over row chunks:
 // part[(job*nchunk + chunk)*ld + c] = sum_{r in chunk} G[r,c] xe[r] + G2[r,c] x3[r]
-// Work-group (z, chunk, job): 256 columns, a quarter of the chunk's rows per
-// wavefront, eight rows' loads in flight; rows and columns of padding are not
-// read.  The work-groups of a chunk's columns follow one another, so that whole
-// rows are read at a time: with all chunks of all jobs for the first 256
-// columns, then for the next, large launches took longer than one row at a
-// time over all columns and chunks of 32 rows (both passes, FP64 planes of 1023
-// rows on 64 slabs: 208 us, so 173, one row at a time 192; 24 planes of 767 rows
-// in FP32 20, 20 and 31).
-template <typename T>
+// A work-group takes 256 columns (a strip) of a chunk's rows, a quarter of them
+// per wavefront, eight rows' loads in flight; rows and columns of padding are not
+// read.  Its place in the grid: (strip, chunk, job) with ROWS, so that whole rows
+// are read at a time, else (chunk, job, strip); gemv_t_rows (rules.h) says when.
+// 24 planes of 767 rows in FP32: 15 us and 5 for the reduction (one row at a
+// time over all columns in chunks of 32 rows 23 and 8).
+template <typename T, bool ROWS>
 __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__ jobs, int ld,
                                                      int M, int rows_per_chunk,
                                                      double *__restrict__ part) {
   constexpr int U = 8;
   __shared__ double red[4][256];
   extern __shared__ double sh[];
-  const int chunk = blockIdx.y, job = blockIdx.z, nchunk = gridDim.y;
+  const int strip = ROWS ? blockIdx.x : blockIdx.z, chunk = ROWS ? blockIdx.y : blockIdx.x;
+  const int job = ROWS ? blockIdx.z : blockIdx.y, nchunk = ROWS ? gridDim.y : gridDim.x;
   const GemvJob J = jobs[job];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r0 = chunk * rows_per_chunk, rn = max(0, min(rows_per_chunk, M - r0));
-  const int c = blockIdx.x * 256 + lane * 4;
+  const int c = strip * 256 + lane * 4;
   double *xs[2] = {sh, sh + rows_per_chunk};
   for (int r = threadIdx.x; r < rn; r += 256) {
     double v = J.x1 ? gp(J.x1)[r0 + r] : 0.0;
@@ -508,7 +507,7 @@ __global__ __launch_bounds__(256) void k_gemv_t_part(const GemvJob *__restrict__
 #pragma unroll
   for (int e = 0; e < 4; ++e) red[wave][lane * 4 + e] = s[e];
   __syncthreads();
-  const int cc = blockIdx.x * 256 + threadIdx.x;
+  const int cc = strip * 256 + threadIdx.x;
   if (cc < ld)
     part[((size_t)job * nchunk + chunk) * ld + cc] =
         (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
@@ -1296,9 +1295,12 @@ void launch_gemv(const GemvJob *jobs, int njobs, int ld, int M, int transpose, d
     const int nchunk = std::min(ld / 64, 64);  // 64 rows and more
     const int rpc = ld / nchunk;
     static_assert(kGemvChunk <= 64, "the partial sums fit the workspace");
-    hipExtLaunchKernelGGL(k_gemv_t_part<T>, dim3((ld + 255) / 256, nchunk, njobs), dim3(256),
-                          2 * rpc * sizeof(double), s, ps.a, nullptr, 0, jobs, ld, M, rpc,
-                          partial);
+    const bool rows = gemv_t_rows(njobs, ld, sizeof(T));
+    const unsigned strips = nblk(ld);
+    hipExtLaunchKernelGGL((rows ? k_gemv_t_part<T, true> : k_gemv_t_part<T, false>),
+                          rows ? dim3(strips, nchunk, njobs) : dim3(nchunk, njobs, strips),
+                          dim3(256), 2 * rpc * sizeof(double), s, ps.a, nullptr, 0, jobs, ld, M,
+                          rpc, partial);
     hipExtLaunchKernelGGL(k_gemv_t_reduce, dim3(nblk(ld), njobs), dim3(256), 0, s, nullptr, ps.b,
                           0, jobs, ld, nchunk, partial, alpha);
   }

@@ -75,3 +75,11 @@ def test_pivots_share_cus_beyond_one_each(tmp_path):
     got = evaluate(tmp_path, 'std::printf("%d %d %d", (int)pivots_share_cus(63), '
                              "(int)pivots_share_cus(256), (int)pivots_share_cus(257));")
     assert got == ["0", "0", "1"]
+
+
+@pytest.mark.parametrize("njobs,ld,esz,rows", [(16, 1024, 4, 0), (64, 512, 8, 0), (32, 1024, 4, 0),
+                                               (32, 1024, 8, 1), (64, 768, 8, 1),
+                                               (16, 2048, 4, 1), (4, 3968, 4, 1)])
+def test_order_of_the_transposed_product(tmp_path, njobs, ld, esz, rows):
+    got = evaluate(tmp_path, f'std::printf("%d", (int)gemv_t_rows({njobs}, {ld}, {esz}));')
+    assert got == [str(rows)]

@@ -211,3 +211,25 @@ def test_compressed_product_against_its_transpose(n, slabs, leaf, factors):
     y = op.apply(x2, which="hodlr").reshape(-1)
     assert abs(float(y @ x1 - z @ x2)) <= 300 * 2.0 ** -24 * float(x1.norm() * x2.norm())
     op.close()
+
+
+@pytest.mark.parametrize("n,slabs,precision", [(511, 32, "fp32"), (1023, 64, "fp32"),
+                                               (899, 60, "fp64"), (1151, 32, "fp64")])
+def test_transposed_products_in_both_orders(n, slabs, precision):
+    """y = S^T x of small and large launches, against the blocks themselves (FP64
+    sums, 1e-12): strips of 256 columns with 127, 255 and none in the last."""
+    print(f"\n[gpu] transposed products n={n} slabs={slabs} {precision}", flush=True)
+    op = ddst().Operator(2, n, slabs, bvec=(5.0, 1.0, 0.0), precision=precision,
+                         keep_factors=False)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    J, M = op.n_ds, op.M
+    x = torch.randn(J, M, generator=g, device="cuda", dtype=torch.float64)
+    out = op.apply(x.reshape(-1), transpose=True).reshape(J, M)
+    for j in (0, 1, J // 2, J - 1):
+        y = x[j].clone()
+        if j > 0:
+            y -= (op.transfer(j)[1] * x[j - 1][:, None]).sum(0)
+        if j < J - 1:
+            y -= (op.transfer(j + 2)[0] * x[j + 1][:, None]).sum(0)
+        assert float((out[j] - y).abs().max()) <= 1e-12 * float(y.abs().max())
+    op.close()
