@@ -122,7 +122,9 @@ def timed(dd, torch, dev, precision, opts, steps, warmup, profile):
 
 
 PMC_COPY_BYTES = 256 << 20  # calibration copy of the counter passes
-PMC_KERNEL = "k_gj_update"
+# the kernels of the update class: rank-128 updates, and the products of the
+# outer blocks
+PMC_KERNELS = ("k_gj_update", "k_gj_left", "k_gj_right")
 
 
 def _pmc_rows(outdir):
@@ -136,13 +138,13 @@ def _pmc_rows(outdir):
     return rows
 
 
-def _per_dispatch(rows, kernel_sub, counter):
+def _per_dispatch(rows, kernel_subs, counter):
     """{dispatch id: summed counter value} of the dispatches whose kernel name
-    contains kernel_sub."""
+    contains one of kernel_subs."""
     out = {}
     for r in rows:
         name = r.get("Kernel_Name", "")
-        if kernel_sub not in name or r.get("Counter_Name") != counter:
+        if not any(k in name for k in kernel_subs) or r.get("Counter_Name") != counter:
             continue
         d = r.get("Dispatch_Id") or r.get("Correlation_Id")
         out[d] = out.get(d, 0.0) + float(r.get("Counter_Value", 0.0))
@@ -191,12 +193,12 @@ def pmc_measure(root):
     shutil.rmtree(tmp, ignore_errors=True)
 
     def scale(counter, rws):
-        copy = _per_dispatch(rws, "copyBuffer", counter)
+        copy = _per_dispatch(rws, ("copyBuffer",), counter)
         big = [v for v in copy.values() if v * 1024 > PMC_COPY_BYTES / 4]
         return PMC_COPY_BYTES / (big[0] * 1024) if big else None
 
-    f = _per_dispatch(rows.get("fetch", []), PMC_KERNEL, "FETCH_SIZE")
-    w = _per_dispatch(rows.get("write", []), PMC_KERNEL, "WRITE_SIZE")
+    f = _per_dispatch(rows.get("fetch", []), PMC_KERNELS, "FETCH_SIZE")
+    w = _per_dispatch(rows.get("write", []), PMC_KERNELS, "WRITE_SIZE")
     fs, ws = scale("FETCH_SIZE", rows.get("fetch", [])), scale("WRITE_SIZE", rows.get("write", []))
     res["fetch_scale"], res["write_scale"] = fs, ws
     if f and w and fs and ws:
@@ -204,10 +206,10 @@ def pmc_measure(root):
         res["traffic_bytes_per_launch"] = (sum(f.values()) / len(f) * fs
                                            + sum(w.values()) / len(w) * ws) * 1024.0
     mr = rows.get("mfma", [])
-    mops = _per_dispatch(mr, PMC_KERNEL, "SQ_INSTS_VALU_MFMA_MOPS_F32")
-    mops16 = _per_dispatch(mr, PMC_KERNEL, "SQ_INSTS_VALU_MFMA_MOPS_BF16")
-    busy = _per_dispatch(mr, PMC_KERNEL, "SQ_VALU_MFMA_BUSY_CYCLES")
-    act = _per_dispatch(mr, PMC_KERNEL, "GRBM_GUI_ACTIVE")
+    mops = _per_dispatch(mr, PMC_KERNELS, "SQ_INSTS_VALU_MFMA_MOPS_F32")
+    mops16 = _per_dispatch(mr, PMC_KERNELS, "SQ_INSTS_VALU_MFMA_MOPS_BF16")
+    busy = _per_dispatch(mr, PMC_KERNELS, "SQ_VALU_MFMA_BUSY_CYCLES")
+    act = _per_dispatch(mr, PMC_KERNELS, "GRBM_GUI_ACTIVE")
     # the counters count matrix-core operations in units of 512 flops
     if mops:
         res["mfma_flops_per_launch"] = 512.0 * sum(mops.values()) / len(mops)
@@ -239,23 +241,60 @@ def pmc_child():
     torch.cuda.synchronize()
 
 
-def roofline(prof, precision, M, pmc=None):
+def outer_blocks(nmat, M, symmetric):
+    """Whether FP32 matrices are eliminated in outer blocks (the rule and its
+    constants: csrc/rules.h)."""
+    import re
+    text = open(os.path.join(ROOT, "paper_2510_25991_amd", "csrc", "rules.h")).read()
+    rows, tiles = (int(re.search(r"constexpr int %s = (\d+);" % k, text).group(1))
+                   for k in ("kOuterRows", "kOuterTiles"))
+    ld = (M + 127) // 128 * 128
+    return ld >= rows and nmat * (ld / 256.0) ** 2 >= tiles * (2 if symmetric else 1)
+
+
+def gj_update_bytes_per_flop(M, esz, outer):
+    """Algorithmic bytes per flop of the Gauss-Jordan updates of one M x M
+    inverse.  One level: every step is a rank-r update (r = GJ_RANK) of the
+    M - r rows outside the pivot block, 2 r M (M - r) flops; it reads and writes
+    those rows once, writes the r pivot rows and reads the two panels,
+    esz (2 M^2 + r M - r^2) bytes.  Outer blocks of w <= 512: the steps of one
+    level on the w x w block, the rank-w update of the other rows and columns
+    (2 w (M - w)^2 flops; they are read and written, the panels read), and the
+    products of both panels with the block's inverse (2 w^2 (M - w) flops each;
+    the panel is read and written, the inverse read)."""
+    def level(m):  # m rows in all their steps
+        steps = (m + GJ_RANK - 1) // GJ_RANK
+        r = GJ_RANK
+        return (steps * 2.0 * r * m * max(m - r, 0),
+                steps * esz * (2.0 * m * m + r * m - r * r))
+    if not outer:
+        f, b = level(M)
+        return b / f
+    f = b = 0.0
+    for p0 in range(0, M, 512):
+        w = min(512, M - p0)
+        o = M - w
+        fi, bi = level(w)
+        f += fi + 2.0 * w * o * o + 4.0 * w * w * o
+        b += bi + esz * (2.0 * o * o + 2.0 * w * o + 2 * (2.0 * w * o + w * w))
+    return b / f
+
+
+def roofline(prof, precision, M, pmc=None, outer=False):
     """Dominant kernel class (the only class timed in the timed region, else
     the longest); achieved = algorithmic work per launch / average launch
     duration (HIP events on the stream each launch runs on).
 
-    The Gauss-Jordan update of one step is a rank-r update (r = GJ_RANK) of
-    the M - r rows outside the pivot block: per matrix 2 r M (M - r) flops;
-    it reads and writes those rows once, writes the r pivot rows and reads
-    the two panels, esize (2 M^2 + r M - r^2) bytes.  Its bound is whichever
-    floor is higher: HBM (algorithmic bytes / 8 TB/s) or the matrix cores
-    (flops / dense MFMA peak of the precision).  At r = 128 and M = 1023 the
-    intensity is about 26.5 flop/B in FP32 and 13.3 in FP64, above both
-    ridges of the FP32 and FP64 instructions (157.3 / 8 and 78.6 / 8).  The
-    FP32 products run as six BF16 products each (three-part split), so the
-    matrix-core ceiling of the FP32 path is the BF16 dense peak / 6 =
-    416.7 TFLOP/s of FP32 work, ridge 52 flop/B: at M = 1023 the FP32 update
-    is then HBM-bound (its D read-modify-write), the FP64 one MFMA-bound.
+    The bound of the Gauss-Jordan updates (gj_update_bytes_per_flop) is
+    whichever floor is higher: HBM (algorithmic bytes / 8 TB/s) or the matrix
+    cores (flops / dense MFMA peak of the precision).  At M = 1023 the
+    intensity is about 26.5 flop/B in FP32 by one level, 51 by outer blocks,
+    and 13.3 in FP64, above the ridges of the FP32 and FP64 instructions (157.3
+    / 8 and 78.6 / 8).  The FP32 products run as six BF16 products each
+    (three-part split), so the matrix-core ceiling of the FP32 path is the BF16
+    dense peak / 6 = 416.7 TFLOP/s of FP32 work, ridge 52 flop/B: at M = 1023
+    the FP32 updates are HBM-bound by one level, and near both bounds by outer
+    blocks; the FP64 ones are MFMA-bound.
     The rate against the FP32 instruction's own peak is given beside it.
     Launches
     of the look-ahead schedule cover subsets of the tiles; their work is
@@ -275,8 +314,7 @@ def roofline(prof, precision, M, pmc=None):
                      "achieved_union": round(ach_u, 3), "frac_union": round(ach_u / mpeak, 4)})
     if name == "gj_update":
         flops_per_launch = work / max(n, 1)
-        r = GJ_RANK
-        bytes_per_flop = esz * (2.0 * M * M + r * M - r * r) / (2.0 * r * M * (M - r))
+        bytes_per_flop = gj_update_bytes_per_flop(M, esz, outer)
         bytes_per_launch = flops_per_launch * bytes_per_flop
         hbm_floor = bytes_per_launch / (PEAK["hbm_gbs"] * 1e9)
         mfma_floor = flops_per_launch / (mpeak * 1e12)
@@ -662,7 +700,10 @@ def main():
                                                 args.warmup, True)
     tb = float(np.mean([s["t_build_ms"] for s in st_mix])) / 1e3
     ts = float(np.mean([s["t_solve_ms"] for s in st_mix])) / 1e3
-    kname, roof = roofline(prof_mix, "fp32", M, pmc)
+    # every sweep's matrices at once: left-to-right of all slabs, right-to-left
+    # of all but the first
+    outer = outer_blocks(2 * prob.n_slabs - 1, M, not any(prob.bvec))
+    kname, roof = roofline(prof_mix, "fp32", M, pmc, outer)
     out_fp64 = None
     u64 = None
     if not args.no_fp64:
