@@ -114,6 +114,10 @@ inline int hbs_rows_in_flight(int rows) { return rows > 64 ? 4 : 2; }
 //   2D 1023 on 128 slabs 537 MB    164  160
 // FP64, twice the loads per column: 152 and 149 at 537 MB, 95.5 and 96.5 at 2047
 // on 16 slabs, so 512.
+// Four rows and 1024 columns, three wavefronts per SIMD, against this rule's two
+// rows: sweeps of 2D 1023 on 64 slabs 72 and 69 us, 2047 on 16 51 and 47, 3D 63 on 4
+// 59 and 47; large interface products are faster so (2D 1023 on 128 slabs 171 and
+// 179, on 512 slabs 669 and 697).
 constexpr double kGemvLargeBytes = 192e6;
 inline bool gemv_wide(int njobs, int ld) {
   return 4.0 * njobs * ld * ld >= kGemvLargeBytes;

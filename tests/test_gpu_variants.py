@@ -29,7 +29,7 @@ def plane_schur(M, skew, dtype=torch.float64):
 
 @pytest.mark.parametrize("symmetric", [False, True])
 @pytest.mark.parametrize("ld,M,tiles", [(896, 800, 74), (1152, 1025, 45), (1280, 1225, 36),
-                                        (1664, 1536, 22)])
+                                        (1664, 1536, 22), (896, 896, 260)])
 def test_outer_elimination_is_as_accurate(ld, M, tiles, symmetric):
     """Many matrices are eliminated in outer blocks, two of them in one level:
     the same sums in another order, so the same error, up to a factor of 2 in
